@@ -47,6 +47,7 @@ hipError_t launch_pack_weight(const bf16_t* W, void* packed, int N, int K, int K
 // loads stay in flight across chunk boundaries.
 // ---------------------------------------------------------------------------------------------
 constexpr int kLdsRow = 512;
+constexpr int kF32Cols = 16;   // columns of an fp32-mode workgroup
 #ifndef CERB_ROWS_RING
 #define CERB_ROWS_RING 8
 #endif
@@ -257,9 +258,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 }
 
 // ---------------------------------------------------------------------------------------------
-// fp32 reference-mode GEMM (small models only): one thread per output column, 4 rows per block
-// pass, plain sequential fp32 accumulation.  Workgroup = 64 columns x 16 rows.
+// fp32 reference-mode GEMM (small models): one workgroup per 16 columns x 16 rows, its four waves a
+// quarter of K each, on the fp32 matrix instruction (fp32 products and sums).  What bounds these
+// launches is the chain of memory round trips, not bytes or products (a layer of the small shape is
+// 0.8 MB of weights), so the tile is small, K is cut four ways and a wave keeps eight 16-byte loads in flight.
+// A 16-byte load covers columns k0 + 4g .. + 3 of its row for lane group g; product e of the four
+// that follow takes element e of every group, i.e. columns {k0 + 4g + e}: the order of a sum over k
+// is free, A and W only have to agree on it.
+// At d = 256, 16 rows a launch takes 5.7 us on average, which is what any kernel takes; one thread per column
+// walking all of K alone took 128 us.
 // ---------------------------------------------------------------------------------------------
+typedef float f32x4u_t __attribute__((ext_vector_type(4), aligned(4)));   // the caller's weights: aligned to their elements only
+
 __global__ __launch_bounds__(256) void k_gemm_f32(const GemmBatch g) {
   if (gemm_skip(g)) return;
   const int rows = g.n_rows ? *g.n_rows : g.rows_static;
@@ -268,20 +278,39 @@ __global__ __launch_bounds__(256) void k_gemm_f32(const GemmBatch g) {
   int pi = 0;
   while (pi + 1 < g.n_prob && (int)blockIdx.x >= g.tile0[pi + 1]) ++pi;
   const GemmProb P = g.p[pi];
-  const int ntile = (int)blockIdx.x - g.tile0[pi];
-  const int col = ntile * 64 + (threadIdx.x & 63);
-  if (col >= P.N) return;
-  const float* A = reinterpret_cast<const float*>(P.A);
-  const float* Wr = reinterpret_cast<const float*>(P.W) + (size_t)col * P.K;
-  for (int r = m0 + (threadIdx.x >> 6); r < min(m0 + 16, rows); r += 4) {
-    const float* a = A + (size_t)r * P.lda;
-    float acc = 0.f;
-    for (int k = 0; k < P.K; ++k) acc = fmaf(a[k], Wr[k], acc);
-    P.out[(size_t)r * P.N + col] = acc;
+  const int n0 = ((int)blockIdx.x - g.tile0[pi]) * kF32Cols;   // N is a multiple of 16
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, i = lane & 15, grp = lane >> 4;
+  const float* A = reinterpret_cast<const float*>(P.A) + (size_t)min(m0 + i, rows - 1) * P.lda + grp * 4;
+  const float* W = reinterpret_cast<const float*>(P.W) + (size_t)(n0 + i) * P.K + grp * 4;
+  const int units = (P.K + 15) / 16;         // of 16 columns; K is a multiple of 8, so a 4-column piece lies inside or outside
+  const int u0 = wave * units / 4, u1 = (wave + 1) * units / 4;
+  f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+  for (int u = u0; u < u1; u += 4) {
+    f32x4_t a[4], w[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int k = (u + q) * 16;
+      const bool in = u + q < u1 && k + grp * 4 < P.K;
+      const int kc = in ? k : -grp * 4;      // (outside: the row's first piece, not used)
+      const f32x4_t av = *reinterpret_cast<const f32x4u_t*>(A + kc), wv = *reinterpret_cast<const f32x4u_t*>(W + kc);
+      const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+      a[q] = in ? av : zero;
+      w[q] = in ? wv : zero;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q][e], w[q][e], acc, 0, 0, 0);
   }
+  __shared__ float red[4][256];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) red[wave][(grp * 4 + v) * 16 + i] = acc[v];   // lane holds column i, rows 4 grp + v
+  __syncthreads();
+  const int t = threadIdx.x, row = m0 + (t >> 4);
+  if (row < rows) P.out[(size_t)row * P.N + n0 + (t & 15)] = (red[0][t] + red[1][t]) + (red[2][t] + red[3][t]);
 }
 
-int gemm_cols_per_wg(int dtype, int nsub) { return dtype == 0 ? 64 : 64 * nsub; }
+int gemm_cols_per_wg(int dtype, int nsub) { return dtype == 0 ? kF32Cols : 64 * nsub; }
 
 template <int MT>
 static void launch_bf16(const GemmBatch& g, dim3 grid, hipStream_t s) {
