@@ -21,8 +21,15 @@ __global__ __launch_bounds__(256) void k_attn_simple(const AttnArgs a) {
   constexpr int LPK = DH / 4, KPW = 64 / LPK, SLOTS = 4 * KPW;   // lanes per key, keys per wave, key slots
   const int r = blockIdx.x, h = blockIdx.y;
   if (r >= *a.rm.n_rows) return;
-  const int b = a.rm.row_seq[r], node = a.rm.row_node[r];
-  const int L = a.rm.seq_L[b], Tb = a.rm.seq_T[b];
+  const int b = a.rm.row_seq[r];
+  int node = a.rm.row_node[r], L = a.rm.seq_L[b], Tb = a.rm.seq_T[b], row0 = a.rm.seq_row0[b];
+  if (a.piece) {                        // the piece the row belongs to, as a sequence of its own
+    const int r0 = node / a.piece * a.piece;
+    node -= r0;
+    L += r0;
+    row0 += r0;
+    Tb = min(a.piece, Tb - r0);
+  }
   constexpr int dh = DH;
   const int slot = threadIdx.x / LPK, e0 = (threadIdx.x % LPK) * 4;
   const unsigned long long* mask = a.anc + (size_t)node * a.aw;
@@ -39,7 +46,6 @@ __global__ __launch_bounds__(256) void k_attn_simple(const AttnArgs a) {
     o[e] = 0.f;
   }
   float m = -INFINITY, l = 0.f;
-  const int row0 = a.rm.seq_row0[b];
   const T* Kt = reinterpret_cast<const T*>(a.ktree);   // null in fp32 mode
   const T* Vt = reinterpret_cast<const T*>(a.vtree);
   const int nk = L + Tb;
@@ -158,9 +164,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     const int L = e.y, Tb = e.z >> 16, row0 = e.z & 0xffff;
     const int npi = e.w >> 16, cps = e.w & 0xffff;
     if (qb * 64 >= Tb) continue;                      // uniform over the workgroup
-    // Items npi.. of a sequence are its tree chunks.
+    // Items npi.. of a sequence are its tree chunks.  Under a chain's mask (a prompt pass) a chunk after the query block's
+    // own is seen by nobody and has no partial (k_attn_combine knows).
     const bool tree = j >= npi;
     const int tci = tree ? j - npi : 0;
+    if (a.piece && tci > qb) continue;                // uniform over the workgroup
     const int k_begin = tree ? 0 : j * cps * a.chunk;                  // first cache row of a cache-range item
     const int k_end = tree ? 0 : min(L, k_begin + cps * a.chunk);
     const int ns = tree ? 2 : (k_end - k_begin + 63) / 64;             // stages (>= 1)
@@ -178,8 +186,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     const unsigned long long amask = a.anc[(size_t)min(qnode, Tb - 1) * a.aw + tci] & (qvalid ? ~0ull : 0ull);
 
     // stage `si` of the item -> LDS rows 64*buf .. 64*buf+63
-    const bf16_t* Kc = reinterpret_cast<const bf16_t*>(a.kv) + (((size_t)(0 * a.Bmax + b) * a.nH + h) * a.cap) * DH;
-    const bf16_t* Vc = reinterpret_cast<const bf16_t*>(a.kv) + (((size_t)(1 * a.Bmax + b) * a.nH + h) * a.cap) * DH;
+    const int cb = a.piece ? a.seq0 : b;
+    const bf16_t* Kc = reinterpret_cast<const bf16_t*>(a.kv) + (((size_t)(0 * a.Bmax + cb) * a.nH + h) * a.cap) * DH;
+    const bf16_t* Vc = reinterpret_cast<const bf16_t*>(a.kv) + (((size_t)(1 * a.Bmax + cb) * a.nH + h) * a.cap) * DH;
     const bf16_t* Kt = reinterpret_cast<const bf16_t*>(a.ktree) + (size_t)(row0 + tci * 64) * a.nH * DH + h * DH;
     const bf16_t* Vt = reinterpret_cast<const bf16_t*>(a.vtree) + (size_t)(row0 + tci * 64) * a.nH * DH + h * DH;
     auto issue = [&](int si, int buf) {
@@ -349,7 +358,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     }
 
     if (wave_live && qvalid) {
-      const size_t slot = (((size_t)b * a.nH + h) * a.n_chunks_max + j) * a.Tpad + qnode;
+      const size_t slot = (((size_t)b * a.nH + h) * a.n_items_max + j) * a.Tpad + qnode;
       float* po = a.part_o + slot * DH;
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
@@ -369,9 +378,17 @@ template <int DH>
 __global__ __launch_bounds__(DH) void k_attn_combine(const AttnArgs a) {
   const int r = blockIdx.x, h = blockIdx.y, t = threadIdx.x;
   if (r >= *a.rm.n_rows) return;
-  const int b = a.rm.row_seq[r], node = a.rm.row_node[r];
-  const int nch = a.rm.seq_npi[b] + (a.rm.seq_T[b] + 63) / 64;   // the sequence's cache-range items + tree chunks
-  const size_t base = (((size_t)b * a.nH + h) * a.n_chunks_max) * a.Tpad + node;
+  int b = a.rm.row_seq[r], node = a.rm.row_node[r];
+  int chunks;                                // tree chunks that this row's query block has a partial of
+  if (a.piece) {
+    b = node / a.piece;
+    node -= b * a.piece;
+    chunks = (node >> 6) + 1;
+  } else {
+    chunks = (a.rm.seq_T[b] + 63) / 64;
+  }
+  const int nch = a.rm.seq_npi[b] + chunks;   // the sequence's cache-range items + tree chunks
+  const size_t base = (((size_t)b * a.nH + h) * a.n_items_max) * a.Tpad + node;
   constexpr int NB = 8;
   float M = -INFINITY, num = 0.f, den = 0.f;
   for (int c0 = 0; c0 < nch; c0 += NB) {
@@ -415,7 +432,7 @@ hipError_t launch_attention(const AttnArgs& a, int dtype, int use_mfma, hipStrea
     return hipGetLastError();
   }
   if (a.chunk != 128 && a.chunk != 256) return hipErrorInvalidValue;
-  if (a.n_chunks_max != (a.cap + a.chunk - 1) / a.chunk + a.tc_max) return hipErrorInvalidValue;
+  if (a.n_items_max != (a.cap + a.chunk - 1) / a.chunk + a.tc_max) return hipErrorInvalidValue;
   if (a.rm.att_item == nullptr || a.grid_x <= 0 || a.grid_x > a.att_cap) return hipErrorInvalidValue;
   dim3 grid(a.grid_x, a.nH, a.tc_max);   // x: items of the work list; z: block of 64 queries
   dim3 cgrid(a.rows_max, a.nH);

@@ -82,7 +82,7 @@ struct cerberus_ctx {
   const void* lm_head = nullptr;
 
   size_t part_floats = 0;
-  int n_chunks_max = 0, R64 = 0, prompt_rows = 0;
+  int att_cap = 0, R64 = 0, prompt_rows = 0;
   cerberus_taps taps{};
   int use_mfma_attn = 1, target_wgs = 768, max_split = 8, gemm_nsub = 2, gemm_nsub_rows = 0, gemm_team = 3, act_split = 1, attn_chunk = 128, attn_target_wgs = 1024, uneven_split = 0, wg_slots = 512;
   std::vector<GemmBatch> p_qkv, p_o, p_gu, p_down, p_res;
@@ -98,6 +98,17 @@ struct cerberus_ctx {
 };
 
 namespace {
+
+// The prompt phase.  Pieces of CERBERUS_MAX_TREE tokens are the unit of committing and of the output taps; a pass takes up
+// to six of them through the layers at once, so that a prompt of up to 1152 tokens streams the weights once (1024 tokens
+// in passes of 192: 49.2 ms, in one pass: 32.0 ms).  Six: at about a thousand rows the GEMMs are bound by the matrix
+// cores and a pass costs in proportion to its rows.  Prompts of up to two pieces run a piece per pass.
+// Attention treats a piece as a sequence of its own: it reads the rows of earlier pieces from the bf16 cache, in the same
+// pass as in a later one, so the cut into passes changes no operand.  It does change the order of sums, though, and a
+// different last bit flips the bf16 rounding of some cached rows, which a random-init stack amplifies: heads' logits of a
+// 230-token prompt are off by 1.6e-2 with a piece per pass and by 3.2e-2 in one pass, past the 2e-2 that short prompts
+// are held to.
+constexpr int kPromptPiece = CERBERUS_MAX_TREE, kPromptPieces = 6, kPromptSplit = 2 * kPromptPiece;
 
 constexpr int kFusedMaxGrid = 512, kFusedMaxNs = 6;
 constexpr int kFusedGrid = 256;          // one workgroup per compute unit of an MI355X; fixed, so that the workspace
@@ -174,10 +185,10 @@ void fill_dims(cerberus_ctx* c, const cerberus_config* cfg, const cerberus_tree*
   c->elem = cfg->dtype == CERBERUS_F32 ? 4 : 2;
   // A prompt pass is a chain of up to prompt_rows rows of one sequence, whatever the tree's size: room
   // for it in the row buffers, the row map and the attention partials.
-  c->prompt_rows = CERBERUS_MAX_TREE;
+  c->prompt_rows = kPromptPiece * kPromptPieces;
   c->R64 = (int)align_up((size_t)std::max(cfg->max_batch * t->n_nodes, c->prompt_rows), 64);
   D.R64 = c->R64;
-  c->n_chunks_max = ceil_div(cfg->kv_capacity, 128) + ceil_div(std::max(t->n_nodes, c->prompt_rows), 64);  // committed-row chunks + tree chunks
+  c->att_cap = std::max((int)cfg->max_batch, kPromptPieces) * (ceil_div(cfg->kv_capacity, 128) + ceil_div(CERBERUS_MAX_TREE, 64));  // committed-row chunks + tree chunks
 }
 
 int fused_tables(const Dims& D, int grid, std::vector<int>& qkv, int& ns_qkv, std::vector<int>& gu, int& ns_gu);
@@ -188,19 +199,18 @@ size_t layout(cerberus_ctx* c, unsigned char* base) {
   const cerberus_config& cfg = c->cfg;
   Bump b{base, 0};
   const int T = D.T, B = D.Bmax, Rmax = std::max(B * T, c->prompt_rows), R64 = c->R64, d = D.d, el = c->elem;
-  const int P = c->prompt_rows;
   c->tree.T = T;
   c->tree.parent = b.take<int>(T);
   c->tree.rank = b.take<int>(T);
   c->tree.depth = b.take<int>(T);
   c->tree.aw = ceil_div(T, 64);
   c->tree.anc = b.take<unsigned long long>((size_t)T * c->tree.aw);
-  c->chain.T = P;
+  c->chain.T = kPromptPiece;
   c->chain.parent = c->tree.parent;   // not read in a prompt pass
   c->chain.rank = c->tree.rank;       // not read in a prompt pass
-  c->chain.depth = b.take<int>(P);
-  c->chain.aw = ceil_div(P, 64);
-  c->chain.anc = b.take<unsigned long long>((size_t)P * c->chain.aw);
+  c->chain.depth = c->tree.depth;     // not read in a prompt pass
+  c->chain.aw = ceil_div(kPromptPiece, 64);
+  c->chain.anc = b.take<unsigned long long>((size_t)kPromptPiece * c->chain.aw);
   c->inv_freq = b.take<double>(D.dh / 2);
   c->rope_cs = b.take<float2>((size_t)std::max(B * T, c->prompt_rows) * (D.dh / 2));
   c->rm.n_rows = b.take<int>(1);
@@ -211,8 +221,9 @@ size_t layout(cerberus_ctx* c, unsigned char* base) {
   c->rm.row_node = b.take<int>(Rmax);
   c->rm.row_pos = b.take<int>(Rmax);
   c->rm.row_tok = b.take<int>(Rmax);
-  c->rm.att_item = b.take<int4>((size_t)B * c->n_chunks_max);
-  c->rm.seq_npi = b.take<int>(B);
+  c->rm.att_item = b.take<int4>((size_t)c->att_cap);
+  c->rm.seq_npi = b.take<int>(std::max(B, kPromptPieces));
+  c->rm.tail = b.take<int>(2);
   c->last_row = b.take<int>(B);
   c->path = b.take<int>((size_t)B * (D.Hc + 1));
   c->topk_v = b.take<float>((size_t)D.Hc * B * TOPK_MAX_PARTS * CERBERUS_MAX_TOPK);
@@ -235,7 +246,9 @@ size_t layout(cerberus_ctx* c, unsigned char* base) {
   const size_t nmax = (size_t)std::max(std::max(3 * d, 2 * D.F), D.V);
   c->part_floats = 16 * std::max((size_t)R64 * nmax, (size_t)16 * D.Hc * std::max((size_t)2 * d, (size_t)D.V));
   c->part = b.take<float>(c->part_floats);
-  const size_t slots = (size_t)B * D.nH * c->n_chunks_max * align_up((size_t)std::max(D.T, P), 64);
+  // attention partials: a tree step of the whole batch, or a prompt pass of one sequence
+  const int cc = ceil_div(D.cap, 128), Tp = (int)align_up(D.T, 64), Pp = (int)align_up(kPromptPiece, 64);
+  const size_t slots = (size_t)D.nH * std::max((size_t)B * (cc + Tp / 64) * Tp, (size_t)kPromptPieces * (cc + Pp / 64) * Pp);
   c->attn_po = b.take<float>(slots * D.dh);
   c->attn_ml = b.take<float>(slots * 2);
   for (int i = 0; i < 2; ++i) {
@@ -529,16 +542,20 @@ int run_fused_gate_up(const cerberus_ctx* c, int l, hipStream_t s) {
   return CERBERUS_OK;
 }
 
-// Embedding, the decoder layers and, with `head`, final norm + LM head + per-row argmax, over the
-// rows the assembly kernel laid out; `tr` supplies the attention mask (candidate tree, or a chain).
-int forward_rows(cerberus_ctx* c, const cerberus_state* st, int batch, int rows_max, const TreeDev& tr, bool head,
+// How a launch's attention is cut: most rows of one sequence, sequences; prompt pass: rows per piece (each counts as a
+// sequence) and the sequence that owns the cache.
+struct AttnShape { int T, batch, piece, seq0; };
+
+// Embedding and the decoder layers over the rows the assembly kernel laid out; `tr` supplies the attention mask
+// (candidate tree, or a chain).  *pending: the GEMM whose partials are still to be added to x.
+int forward_rows(cerberus_ctx* c, const cerberus_state* st, int rows_max, const TreeDev& tr, const AttnShape& sh, GemmProb* pending,
                  hipStream_t s) {
   const Dims& D = c->D;
   const RowMap& rm = c->rm;
   const size_t kv_layer_bytes = (size_t)2 * D.Bmax * D.nH * D.cap * D.dh * c->elem;
   HIP_TRY(launch_embed(D, rm, c->embed, c->x, c->inv_freq, c->rope_cs, rows_max, s));
 
-  GemmProb pd{};                   // GEMM whose partials are the pending residual
+  GemmProb& pd = *pending;
   const GemmProb* prev = nullptr;
   // launches of up to 64 rows: QKV + RoPE + KV write and gate/up + SwiGLU as one whole-K launch each
   const bool fused = c->use_fused && D.dtype == CERBERUS_BF16 && rows_max <= 64 && c->fused_grid > 0 && c->act_split == 1;
@@ -557,12 +574,13 @@ int forward_rows(cerberus_ctx* c, const cerberus_state* st, int batch, int rows_
     }
     AttnArgs aa{};
     aa.q = c->q; aa.q_lo_off = D.dtype == CERBERUS_BF16 ? (size_t)c->R64 * D.d : 0; aa.kv = kv_layer; aa.ktree = c->ktree; aa.vtree = c->vtree; aa.out = c->attn; aa.out_lo_off = (size_t)c->R64 * D.d; aa.part_o = c->attn_po; aa.part_ml = c->attn_ml; aa.rm = rm;
-    aa.anc = tr.anc; aa.aw = tr.aw; aa.Tpad = (int)align_up((size_t)tr.T, 64); aa.tc_max = ceil_div(tr.T, 64); aa.batch = batch; aa.Bmax = D.Bmax; aa.nH = D.nH; aa.dh = D.dh; aa.cap = D.cap; aa.T = tr.T;
-    aa.chunk = c->attn_chunk; aa.n_chunks_max = ceil_div(D.cap, c->attn_chunk) + aa.tc_max;   // <= c->n_chunks_max, which sized the partial buffers
+    aa.anc = tr.anc; aa.aw = tr.aw; aa.Tpad = (int)align_up((size_t)sh.T, 64); aa.tc_max = ceil_div(sh.T, 64); aa.piece = sh.piece; aa.seq0 = sh.seq0;
+    aa.batch = sh.batch; aa.Bmax = D.Bmax; aa.nH = D.nH; aa.dh = D.dh; aa.cap = D.cap;
+    aa.chunk = c->attn_chunk; aa.n_items_max = ceil_div(D.cap, c->attn_chunk) + aa.tc_max;   // (layout sized the partial buffers for the smaller chunk)
     // every item gets a workgroup per head: at most target / nH cache-range items plus one per sequence from
     // rounding, and the tree chunks
-    aa.att_cap = D.Bmax * c->n_chunks_max;
-    aa.grid_x = std::min(batch * aa.n_chunks_max, std::max(1, c->attn_target_wgs / D.nH) + batch * (1 + aa.tc_max));
+    aa.att_cap = c->att_cap;
+    aa.grid_x = std::min(sh.batch * aa.n_items_max, std::max(1, c->attn_target_wgs / D.nH) + sh.batch * (1 + aa.tc_max));
     aa.rows_max = rows_max; aa.status = st->status;
     HIP_TRY(launch_attention(aa, D.dtype, c->use_mfma_attn, s));
     TRY(run_gemm(c, c->p_o[l], rm.n_rows, 0, rows_max, nullptr, 0, s, &po));
@@ -576,13 +594,17 @@ int forward_rows(cerberus_ctx* c, const cerberus_state* st, int batch, int rows_
     TRY(run_gemm(c, c->p_down[l], rm.n_rows, 0, rows_max, nullptr, 0, s, &pd));
     prev = &pd;
   }
-  if (!head) return CERBERUS_OK;
-  HIP_TRY(launch_add_rmsnorm(D, rm, c->x, prev->out, prev->S, (size_t)prev->out_rows * prev->N, c->final_norm, c->xn,
-                             c->h_last, c->taps.h_last, rows_max, s));
-  GemmProb pl;
-  TRY(run_gemm(c, c->p_lm, rm.n_rows, 0, rows_max, nullptr, 0, s, &pl));
-  HIP_TRY(launch_row_argmax(D, rm, pl.out, pl.S, (size_t)pl.out_rows * pl.N, c->g, c->taps, rows_max, s));
+  return CERBERUS_OK;
+}
 
+// Final norm, LM head and per-row argmax over the rows of the row map, which are the layers' rows from *src0 on (null: 0)
+int run_lm_head(cerberus_ctx* c, const GemmProb& pd, const int* src0, int rows_max, hipStream_t s) {
+  const Dims& D = c->D;
+  HIP_TRY(launch_add_rmsnorm(D, c->rm, c->x, pd.out, pd.S, (size_t)pd.out_rows * pd.N, c->final_norm, c->xn,
+                             c->h_last, c->taps.h_last, src0, rows_max, s));
+  GemmProb pl;
+  TRY(run_gemm(c, c->p_lm, c->rm.n_rows, 0, rows_max, nullptr, 0, s, &pl));
+  HIP_TRY(launch_row_argmax(D, c->rm, pl.out, pl.S, (size_t)pl.out_rows * pl.N, c->g, c->taps, rows_max, s));
   return CERBERUS_OK;
 }
 
@@ -620,7 +642,7 @@ int run_heads(cerberus_ctx* c, const cerberus_state* st, int batch, hipStream_t 
 // the attention work list is built only for the MFMA kernel; the plain one walks rows and heads
 AttnPlanCfg attn_plan_cfg(const cerberus_ctx* c) {
   const bool mfma = c->cfg.dtype == CERBERUS_BF16 && c->use_mfma_attn;
-  return AttnPlanCfg{mfma ? c->attn_chunk : 0, c->attn_target_wgs, c->D.Bmax * c->n_chunks_max};
+  return AttnPlanCfg{mfma ? c->attn_chunk : 0, c->attn_target_wgs, c->att_cap};
 }
 
 int run_step(cerberus_ctx* c, const cerberus_state* st, int batch, void* stream, int mode) {
@@ -630,8 +652,11 @@ int run_step(cerberus_ctx* c, const cerberus_state* st, int batch, void* stream,
   const RowMap& rm = c->rm;
   const int rows_max = (mode == ASSEMBLE_FORCE_AR) ? batch : batch * D.T;
 
+  const AttnShape sh{D.T, batch, 0, 0};
   HIP_TRY(launch_assemble(D, c->tree, rm, *st, c->taps, batch, mode, PromptArgs{}, attn_plan_cfg(c), s));
-  TRY(forward_rows(c, st, batch, rows_max, c->tree, true, s));
+  GemmProb pd{};
+  TRY(forward_rows(c, st, rows_max, c->tree, sh, &pd, s));
+  TRY(run_lm_head(c, pd, nullptr, rows_max, s));
 
   HIP_TRY(launch_accept(D, c->tree, rm, c->g, rm.row_tok, *st, c->path, c->last_row, batch, s));
   if (mode != ASSEMBLE_FORCE_AR) HIP_TRY(launch_compact(D, rm, *st, c->path, batch, s));
@@ -640,8 +665,8 @@ int run_step(cerberus_ctx* c, const cerberus_state* st, int batch, void* stream,
   return run_heads(c, st, batch, s);
 }
 
-// Prompt phase for one sequence: passes of up to prompt_rows rows, each a chain (causal mask, positions
-// L, L+1, ...) whose K/V rows land where they stay.
+// Prompt phase for one sequence: passes of whole pieces, each a chain (causal mask, positions
+// L, L+1, ...) whose K/V rows land where they stay; only the rows of the prompt's last piece need the LM head.
 int run_prompt(cerberus_ctx* c, const cerberus_state* st, int batch, int seq, const int* tokens, int n_tokens, hipStream_t s) {
   const Dims& D = c->D;
   const RowMap& rm = c->rm;
@@ -652,13 +677,19 @@ int run_prompt(cerberus_ctx* c, const cerberus_state* st, int batch, int seq, co
   } restore{c->taps, c->taps};
   c->taps.forced_node_argmax = nullptr;
   c->taps.forced_gate_hidden = nullptr;
-  for (int off = 0; off < n_tokens; off += c->chain.T) {
-    const int n = std::min(c->chain.T, n_tokens - off);
+  const int pass = n_tokens <= kPromptSplit ? kPromptPiece : c->prompt_rows;
+  for (int off = 0; off < n_tokens; off += pass) {
+    const int n = std::min(pass, n_tokens - off);
     const bool last = off + n >= n_tokens;
-    HIP_TRY(launch_assemble(D, c->chain, rm, *st, c->taps, batch, ASSEMBLE_PROMPT, PromptArgs{tokens + off, n, seq}, attn_plan_cfg(c), s));
-    TRY(forward_rows(c, st, batch, n, c->chain, last, s));
-    HIP_TRY(launch_prompt_commit(rm, *st, c->g, c->last_row, batch, seq, last ? 1 : 0, s));
+    const AttnShape sh{std::min(n, kPromptPiece), ceil_div(n, kPromptPiece), kPromptPiece, seq};
+    HIP_TRY(launch_assemble(D, c->chain, rm, *st, c->taps, batch, ASSEMBLE_PROMPT, PromptArgs{tokens + off, n, seq, kPromptPiece, last ? 1 : 0},
+                            attn_plan_cfg(c), s));
+    GemmProb pd{};
+    TRY(forward_rows(c, st, n, c->chain, sh, &pd, s));
+    HIP_TRY(launch_prompt_commit(rm, *st, c->last_row, batch, seq, last ? 1 : 0, s));
     if (last) {
+      TRY(run_lm_head(c, pd, rm.tail, (n - 1) % kPromptPiece + 1, s));
+      HIP_TRY(launch_prompt_root(*st, c->g, c->last_row, seq, s));
       HIP_TRY(launch_gate(D.d, D.threshold, c->h_last, c->last_row, nullptr, rm.seq_T, batch, st->entropy, st->gate_flag,
                           heads_prep(c), D.dtype, s));
       TRY(run_heads(c, st, batch, s));
@@ -745,13 +776,10 @@ int cerberus_init(cerberus_ctx** out, const cerberus_config* cfg, const cerberus
   HIP_INIT(hipMemcpy(c->inv_freq, inv.data(), inv.size() * sizeof(double), hipMemcpyHostToDevice));
   {
     const int P = c->chain.T, caw = c->chain.aw;
-    std::vector<int> cd(P);
     std::vector<unsigned long long> ca((size_t)P * caw, 0ull);
     for (int n = 0; n < P; ++n) {
-      cd[n] = n;
       for (int m = 0; m <= n; ++m) ca[(size_t)n * caw + (m >> 6)] |= 1ull << (m & 63);
     }
-    HIP_INIT(hipMemcpy((void*)c->chain.depth, cd.data(), P * sizeof(int), hipMemcpyHostToDevice));
     HIP_INIT(hipMemcpy((void*)c->chain.anc, ca.data(), ca.size() * sizeof(unsigned long long), hipMemcpyHostToDevice));
   }
 

@@ -78,7 +78,9 @@ struct RowMap {
                   // cache-range items, then its tree chunks), y = kv_len, z = (rows of the sequence << 16) | its
                   // first row, w = (cache-range items of the sequence << 16) | chunks per cache-range item;
                   // x = -1 from the end of the list on
-  int* seq_npi;   // [B] cache-range items of the sequence
+  int* seq_npi;   // [B or pieces] cache-range items of the sequence (of a prompt pass: of the piece)
+  // prompt passes only: the rows of the pass that go on to the final norm and the LM head (see PromptArgs)
+  int* tail;      // [2] first row, rows
 };
 
 struct AttnPlanCfg {
@@ -166,16 +168,19 @@ struct AttnArgs {
   const void* vtree; //            the tree keys are read from here, the cache only serves rows < L
   void* out;         // [rows][nH*dh] attention output (GEMM A operand; bf16: lo plane out_lo_off elements later)
   size_t out_lo_off;
-  float* part_o;     // [B][nH][n_chunks_max][Tpad][dh]; slot j of a (seq, head) belongs to the sequence's work item j
-  float* part_ml;    // [B][nH][n_chunks_max][Tpad][2]
+  float* part_o;     // [B][nH][n_items_max][Tpad][dh]; slot j of a (seq, head) belongs to the sequence's work item j
+  float* part_ml;    // [B][nH][n_items_max][Tpad][2]
   RowMap rm;
   const unsigned long long* anc;   // [T][aw]
   int aw;            // mask words per node
-  int Tpad;          // tree size rounded up to 64: query rows per partial slot
-  int tc_max;        // tree chunks (64 of this step's rows each) at the end of the chunk grid, ceil(T / 64)
-  int batch, Bmax, nH, dh, cap, T;
+  int Tpad;          // rows of a sequence at most (tree size, rows of a prompt piece) rounded up to 64: query rows per partial slot
+  int tc_max;        // blocks of 64 queries and chunks of 64 of this step's rows, Tpad / 64
+  int piece;         // prompt pass: its rows come in pieces of this many, each attended to like a sequence of its own whose
+                     // committed rows are all the cache rows before it; 0: a decoding step
+  int seq0;          // prompt pass: the sequence whose cache the pieces share
+  int batch, Bmax, nH, dh, cap;
   int chunk;         // committed cache rows per chunk of the work list
-  int n_chunks_max;
+  int n_items_max;   // partial slots of a (seq, head): cache chunks of the whole cache + tree items
   int grid_x;        // workgroups along the item axis (the kernel strides over the list if it is longer)
   int att_cap;       // entries of the work list
   int rows_max;

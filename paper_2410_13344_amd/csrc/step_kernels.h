@@ -13,10 +13,13 @@ struct Dims {
 
 enum { ASSEMBLE_BY_FLAG = 0, ASSEMBLE_FORCE_AR = 1, ASSEMBLE_FULL_TREE = 2, ASSEMBLE_PROMPT = 3 };
 
-// prompt pass: sequence `seq` runs `n` rows carrying tokens[0..n), every other sequence sits out
+// Prompt pass: sequence `seq` runs `n` rows carrying tokens[0..n), every other sequence sits out.  The prompt counts in
+// pieces of `piece` tokens (the last one may be shorter): a piece is committed whole or, where the cache has no room for
+// it, not at all, and the output taps see the rows of the prompt's last piece, from slot 0 on.  A pass holds whole
+// pieces; with `last` it holds the prompt's last piece, whose rows alone go on to the LM head.
 struct PromptArgs {
   const int* tokens;
-  int n, seq;
+  int n, seq, piece, last;
 };
 
 struct ResFinishArgs {
@@ -37,13 +40,16 @@ struct TopkArgs {
 
 hipError_t launch_assemble(const Dims& D, const TreeDev& tr, const RowMap& rm, const cerberus_state& st,
                            const cerberus_taps& tp, int batch, int mode, const PromptArgs& pa, const AttnPlanCfg& ap, hipStream_t s);
-hipError_t launch_prompt_commit(const RowMap& rm, const cerberus_state& st, const int* g, int* last_row, int batch, int seq,
-                                int last_pass, hipStream_t s);
+// after the layers of a prompt pass: commits the rows; in the last pass the row map becomes that of the tail rows
+hipError_t launch_prompt_commit(const RowMap& rm, const cerberus_state& st, int* last_row, int batch, int seq, int last_pass,
+                                hipStream_t s);
+// after the LM head of the last pass: the pending token
+hipError_t launch_prompt_root(const cerberus_state& st, const int* g, const int* last_row, int seq, hipStream_t s);
 // also fills rope_cs[row][j] = (cos, sin)(pos(row) * inv_freq[j]), j < dh/2, the angle formed in double
 hipError_t launch_embed(const Dims& D, const RowMap& rm, const void* embed, float* x, const double* inv_freq, float2* rope_cs,
                         int rows_max, hipStream_t s);
 hipError_t launch_add_rmsnorm(const Dims& D, const RowMap& rm, float* x, const float* part, int S, size_t pstride,
-                              const float* gain, void* out, float* out_f32, float* tap, int rows_max, hipStream_t s);
+                              const float* gain, void* out, float* out_f32, float* tap, const int* src0, int rows_max, hipStream_t s);
 // residual add + x * gain + per-block sums of x^2 (the RMSNorm scalar is applied by the consumer of the next GEMM)
 int add_gain_blocks(int d);   // sums per row
 // a_tiled: write the GEMM input in MFMA A-fragment order (64 rows, see FusedQkvArgs) instead of row-major planes

@@ -99,16 +99,32 @@ __device__ __forceinline__ float4 add_parts(float4 a, const Parts<MAXS, float4>&
 // Tree assembly (Algorithm 1 line 1 and the Candidates tuple of lines 11-12): which rows this step
 // has, and the token / position of each.  One block; sequences pack their rows back to back.
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(64) void k_assemble(const Dims D, const TreeDev tr, const RowMap rm, const cerberus_state st,
+__global__ __launch_bounds__(256) void k_assemble(const Dims D, const TreeDev tr, const RowMap rm, const cerberus_state st,
                                                  const cerberus_taps tp, int batch, int mode, const PromptArgs pa,
                                                  const AttnPlanCfg ap) {
   __shared__ int sT[CERBERUS_MAX_BATCH], sL[CERBERUS_MAX_BATCH], sRow0[CERBERUS_MAX_BATCH];
+  __shared__ int sFull, sTail;            // prompt pass: rows of whole pieces that fit, rows of the prompt's last piece
   const int t = threadIdx.x;
   if (t < batch) {
     const int L = st.kv_len[t];
     int Tb = tr.T;
     if (mode == ASSEMBLE_FORCE_AR || (mode == ASSEMBLE_BY_FLAG && st.gate_flag[t] != 0)) Tb = 1;
-    if (mode == ASSEMBLE_PROMPT) Tb = (t == pa.seq) ? pa.n : 0;   // a chain of prompt tokens (tr is the chain's tables)
+    if (mode == ASSEMBLE_PROMPT) {        // a chain of prompt tokens (tr is the chain's tables)
+      Tb = 0;
+      if (t == pa.seq) {                  // piece by piece: one that does not fit is left out, a shorter one after it may fit
+        const int n_full = pa.last ? (pa.n - 1) / pa.piece * pa.piece : pa.n;
+        int full = 0, tail = pa.n - n_full;
+        const int room = L < 0 ? 0 : D.cap - L;
+        while (full < n_full && full + pa.piece <= room) full += pa.piece;
+        if (full + tail > room) tail = 0;
+        if (full + tail < pa.n) atomicOr(st.status, (int)CERBERUS_DEV_KV_OVERFLOW);
+        Tb = full + tail;
+        sFull = full;
+        sTail = tail;
+        rm.tail[0] = full;
+        rm.tail[1] = tail;
+      }
+    }
     if (Tb > 0 && (L < 0 || L + Tb > D.cap)) {  // the sequence sits this step out
       Tb = 0;
       atomicOr(st.status, (int)CERBERUS_DEV_KV_OVERFLOW);
@@ -134,18 +150,26 @@ __global__ __launch_bounds__(64) void k_assemble(const Dims D, const TreeDev tr,
     // the step's own rows.  cps grows with the total length so that the list stays near the workgroup
     // target: a long cache is walked inside a workgroup (one partial result per item) instead of being cut
     // into a partial per chunk.  Every thread derives the same plan; thread i writes entries i, i + 64, ...
+    // A prompt pass is listed piece by piece: piece p is a sequence of its own whose committed rows are the cache rows
+    // before it (the earlier pieces of the pass among them: the layer's K/V rows are all in the cache by then).
+    const bool prompt = mode == ASSEMBLE_PROMPT;
+    const int nseq = prompt ? (sT[pa.seq] + pa.piece - 1) / pa.piece : batch;
+    auto rows_of = [&](int b) { return prompt ? min(pa.piece, sT[pa.seq] - b * pa.piece) : sT[b]; };
+    auto len_of = [&](int b) { return prompt ? sL[pa.seq] + b * pa.piece : sL[b]; };
+    auto row0_of = [&](int b) { return prompt ? sRow0[pa.seq] + b * pa.piece : sRow0[b]; };
     int chunks = 0;
-    for (int b = 0; b < batch; ++b)
-      if (sT[b] > 0) chunks += (sL[b] + ap.chunk - 1) / ap.chunk;
+    for (int b = 0; b < nseq; ++b)
+      if (rows_of(b) > 0) chunks += (len_of(b) + ap.chunk - 1) / ap.chunk;
     const int per_head = max(1, ap.target_wgs / D.nH);
     const int cps = min(0xffff, max(1, (chunks + per_head - 1) / per_head));
     int n = 0;
-    for (int b = 0; b < batch; ++b) {
-      const int npi = sT[b] > 0 ? ((sL[b] + ap.chunk - 1) / ap.chunk + cps - 1) / cps : 0;
-      const int ntree = (sT[b] + 63) / 64;
+    for (int b = 0; b < nseq; ++b) {
+      const int Tb = rows_of(b), Lb = len_of(b);
+      const int npi = Tb > 0 ? ((Lb + ap.chunk - 1) / ap.chunk + cps - 1) / cps : 0;
+      const int ntree = (Tb + 63) / 64;
       if (t == 0) rm.seq_npi[b] = npi;
       for (int j = t; j < npi + ntree; j += blockDim.x)
-        if (n + j < ap.att_cap) rm.att_item[n + j] = make_int4((b << 16) | j, sL[b], (sT[b] << 16) | sRow0[b], (npi << 16) | cps);
+        if (n + j < ap.att_cap) rm.att_item[n + j] = make_int4((b << 16) | j, Lb, (Tb << 16) | row0_of(b), (npi << 16) | cps);
       n += npi + ntree;
     }
     for (int i = n + t; i < ap.att_cap; i += blockDim.x) rm.att_item[i] = make_int4(-1, 0, 0, 0);
@@ -155,17 +179,24 @@ __global__ __launch_bounds__(64) void k_assemble(const Dims D, const TreeDev tr,
   for (int b = 0; b < batch; ++b) {
     for (int node = t; node < sT[b]; node += blockDim.x) {
       const int r = sRow0[b] + node;
-      const int dep = tr.depth[node];
+      const int dep = mode == ASSEMBLE_PROMPT ? node : tr.depth[node];
       rm.row_seq[r] = b;
       rm.row_node[r] = node;
       rm.row_pos[r] = sL[b] + dep;
       if (mode != ASSEMBLE_FULL_TREE) {
         int tok;
-        if (mode == ASSEMBLE_PROMPT) tok = pa.tokens[node];
-        else tok = node == 0 ? st.root_token[b] : st.cand[(b * D.Hc + dep - 1) * D.topk + tr.rank[node]];
+        int slot = node;                       // of the tap
+        if (mode == ASSEMBLE_PROMPT) {
+          // tail rows carry the last tokens of the pass, also where a piece before them was left out
+          const bool in_tail = node >= sFull;
+          tok = pa.tokens[in_tail ? pa.n - sTail + node - sFull : node];
+          // a slot shows the latest piece that has a row there: the tail, else the last whole piece
+          slot = in_tail ? node - sFull : node - (sFull - pa.piece);
+          if (!in_tail && (slot < sTail)) slot = D.T;
+        } else tok = node == 0 ? st.root_token[b] : st.cand[(b * D.Hc + dep - 1) * D.topk + tr.rank[node]];
         if (tok < 0 || tok >= D.V) { atomicOr(st.status, (int)CERBERUS_DEV_BAD_TOKEN); tok = 0; }
         rm.row_tok[r] = tok;
-        if (tp.node_token && node < D.T) tp.node_token[b * D.T + node] = tok;   // the taps hold T rows per sequence
+        if (tp.node_token && slot < D.T) tp.node_token[b * D.T + slot] = tok;   // the taps hold T rows per sequence
       }
     }
   }
@@ -173,32 +204,48 @@ __global__ __launch_bounds__(64) void k_assemble(const Dims D, const TreeDev tr,
 
 hipError_t launch_assemble(const Dims& D, const TreeDev& tr, const RowMap& rm, const cerberus_state& st,
                            const cerberus_taps& tp, int batch, int mode, const PromptArgs& pa, const AttnPlanCfg& ap, hipStream_t s) {
-  hipLaunchKernelGGL(k_assemble, dim3(1), dim3(64), 0, s, D, tr, rm, st, tp, batch, mode, pa, ap);
+  hipLaunchKernelGGL(k_assemble, dim3(1), dim3(256), 0, s, D, tr, rm, st, tp, batch, mode, pa, ap);
   return hipGetLastError();
 }
 
-// End of a prompt pass: the rows are where they belong already (row L + i), so committing them is
-// advancing kv_len.  After the last pass the pending token is the base model's choice at the last
-// prompt position, and that row feeds the gate and the heads.
-__global__ void k_prompt_commit(const RowMap rm, const cerberus_state st, const int* __restrict__ g, int* __restrict__ last_row,
-                                int batch, int seq, int last_pass) {
-  const int b = threadIdx.x;
-  if (b >= batch) return;
-  const int n = rm.seq_T[b];              // 0 for every sequence but `seq` (and for `seq` when it did not fit)
-  last_row[b] = -1;
-  if (b != seq || n <= 0) return;
-  st.kv_len[b] = rm.seq_L[b] + n;
-  st.accept_len[b] = 0;
-  if (last_pass) {
-    const int r = rm.seq_row0[b] + n - 1;
-    st.root_token[b] = g[r];
-    last_row[b] = r;
+// End of a prompt pass's layers: the rows are where they belong already (row L + i), so committing them is advancing
+// kv_len.  In the last pass the row map then becomes that of the tail (the rows of the prompt's last piece, which alone
+// go through the final norm and the LM head): rows 0.. of the head's buffers are the pass's rows tail[0]... ; the last of
+// them feeds the gate and the heads.
+__global__ __launch_bounds__(256) void k_prompt_commit(const RowMap rm, const cerberus_state st, int* __restrict__ last_row, int batch,
+                                                       int seq, int last_pass) {
+  const int t = threadIdx.x, tail = rm.tail[1];
+  if (t < batch) {
+    const int n = rm.seq_T[t];              // 0 for every sequence but `seq` (and for `seq` when nothing fitted)
+    last_row[t] = -1;
+    if (t == seq && n > 0) {
+      st.kv_len[t] = rm.seq_L[t] + n;
+      st.accept_len[t] = 0;
+    }
+    if (t == seq && last_pass) {
+      if (tail > 0) last_row[t] = tail - 1;
+      rm.seq_T[t] = tail;
+      rm.seq_row0[t] = 0;
+      *rm.n_rows = tail;
+    }
   }
+  if (last_pass)
+    for (int i = t; i < tail; i += blockDim.x) { rm.row_seq[i] = seq; rm.row_node[i] = i; }
 }
 
-hipError_t launch_prompt_commit(const RowMap& rm, const cerberus_state& st, const int* g, int* last_row, int batch, int seq,
-                                int last_pass, hipStream_t s) {
-  hipLaunchKernelGGL(k_prompt_commit, dim3(1), dim3(64), 0, s, rm, st, g, last_row, batch, seq, last_pass);
+hipError_t launch_prompt_commit(const RowMap& rm, const cerberus_state& st, int* last_row, int batch, int seq, int last_pass,
+                                hipStream_t s) {
+  hipLaunchKernelGGL(k_prompt_commit, dim3(1), dim3(256), 0, s, rm, st, last_row, batch, seq, last_pass);
+  return hipGetLastError();
+}
+
+// the pending token is the base model's choice at the last prompt position
+__global__ void k_prompt_root(const cerberus_state st, const int* __restrict__ g, const int* __restrict__ last_row, int seq) {
+  if (last_row[seq] >= 0) st.root_token[seq] = g[last_row[seq]];
+}
+
+hipError_t launch_prompt_root(const cerberus_state& st, const int* g, const int* last_row, int seq, hipStream_t s) {
+  hipLaunchKernelGGL(k_prompt_root, dim3(1), dim3(1), 0, s, st, g, last_row, seq);
   return hipGetLastError();
 }
 
@@ -253,11 +300,13 @@ template <typename T, int MAXS>
 __global__ __launch_bounds__(1024) void k_add_rmsnorm(float* __restrict__ x, const float* __restrict__ part, int S,
                                                       size_t pstride, const float* __restrict__ gain, float eps,
                                                       T* __restrict__ out, size_t lo_off, float* __restrict__ out_f32,
-                                                      float* __restrict__ tap, const RowMap rm, int d, int T_tree) {
+                                                      float* __restrict__ tap, const int* __restrict__ src0, const RowMap rm, int d,
+                                                      int T_tree) {
   __shared__ float sh[16];
   const int r = blockIdx.x;
   if (r >= *rm.n_rows) return;
-  float* xr = x + (size_t)r * d;
+  const size_t rs = r + (src0 ? *src0 : 0);            // the layers' row that row r of the head is
+  float* xr = x + rs * d;
   float4 v[2], g[2];
   float ss = 0.f;
 #pragma unroll
@@ -267,7 +316,7 @@ __global__ __launch_bounds__(1024) void k_add_rmsnorm(float* __restrict__ x, con
     g[it] = v[it];
     if (c < d) {
       Parts<MAXS, float4> P;
-      P.load(part + (size_t)r * d + c, pstride, S);
+      P.load(part + rs * d + c, pstride, S);
       v[it] = *reinterpret_cast<const float4*>(xr + c);
       g[it] = *reinterpret_cast<const float4*>(gain + c);
       v[it] = add_parts(v[it], P, S);
@@ -294,14 +343,14 @@ __global__ __launch_bounds__(1024) void k_add_rmsnorm(float* __restrict__ x, con
 }
 
 hipError_t launch_add_rmsnorm(const Dims& D, const RowMap& rm, float* x, const float* part, int S, size_t pstride,
-                              const float* gain, void* out, float* out_f32, float* tap, int rows_max, hipStream_t s) {
+                              const float* gain, void* out, float* out_f32, float* tap, const int* src0, int rows_max, hipStream_t s) {
 #define CERB_CALL(MS)                                                                                                   \
   if (D.dtype == 0)                                                                                                     \
     hipLaunchKernelGGL((k_add_rmsnorm<float, MS>), dim3(rows_max), dim3(1024), 0, s, x, part, S, pstride, gain, D.eps,  \
-                       (float*)out, (size_t)0, out_f32, tap, rm, D.d, D.T);                                             \
+                       (float*)out, (size_t)0, out_f32, tap, src0, rm, D.d, D.T);                                             \
   else                                                                                                                  \
     hipLaunchKernelGGL((k_add_rmsnorm<bf16_t, MS>), dim3(rows_max), dim3(1024), 0, s, x, part, S, pstride, gain, D.eps, \
-                       (bf16_t*)out, (size_t)D.R64 * D.d, out_f32, tap, rm, D.d, D.T)
+                       (bf16_t*)out, (size_t)D.R64 * D.d, out_f32, tap, src0, rm, D.d, D.T)
   CERB_S_BUCKET(S, CERB_CALL);
 #undef CERB_CALL
   return hipGetLastError();
