@@ -150,14 +150,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   __shared__ __attribute__((aligned(16))) unsigned char sK[128 * ROWB];
   __shared__ __attribute__((aligned(16))) unsigned char sV[128 * ROWB];
 
-  const int h = blockIdx.y, qb = blockIdx.z;        // head; block of 64 queries
+  const int h = blockIdx.x, qb = blockIdx.y;        // head; block of 64 queries (see the launch)
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int lq = lane & 15, g = lane >> 4;
   const int st_row = lane / PPR, st_sw = lane % PPR;   // staging: row within the instruction's rows, LDS piece slot
   const float scale = rsqrtf((float)DH);
   const unsigned sK_base = lds_offset_of(sK), sV_base = lds_offset_of(sV);
 
-  for (int item = blockIdx.x; item < a.att_cap; item += gridDim.x) {   // the grid covers the list; the stride is a safety net
+  for (int item = blockIdx.z; item < a.att_cap; item += gridDim.z) {   // the grid covers the list; the stride is a safety net
     const int4 e = a.rm.att_item[item];
     if (e.x < 0) break;                               // end of the list (uniform)
     const int b = e.x >> 16, j = e.x & 0xffff;
@@ -438,7 +438,13 @@ hipError_t launch_attention(const AttnArgs& a, int dtype, int use_mfma, hipStrea
   if (a.chunk != 128 && a.chunk != 256) return hipErrorInvalidValue;
   if (a.n_items_max != (a.cap + a.chunk - 1) / a.chunk + a.tc_max) return hipErrorInvalidValue;
   if (a.rm.att_item == nullptr || a.grid_x <= 0 || a.grid_x > a.att_cap) return hipErrorInvalidValue;
-  dim3 grid(a.grid_x, a.nH, a.tc_max);   // x: items of the work list; z: block of 64 queries
+  // Heads vary fastest, items slowest.  Consecutive workgroup ids go to the 8 XCDs in turn: with the items fastest and
+  // their number a multiple of 8, an item ran on one XCD for every head, and the XCDs with the long items finished last
+  // (half of the places stood empty over the launch).  This way every XCD gets each item for an eighth of the heads, long
+  // items start first (the list's order), and the query blocks of an item read the same K/V rows from the same L2 soon
+  // after each other.  32 heads, 16 sequences of 256..2048 rows: 123 -> 98 us; 8 of 831..3312: 90 -> 76; a 1024-token
+  // prompt: 68 -> 57; one of 1024 with 121 tree rows: 20.9 -> 19.6.
+  dim3 grid(a.nH, a.tc_max, a.grid_x < 65535 ? a.grid_x : 65535);
   const int hpw = 128 / (a.dh / 4);
   dim3 cgrid(a.rows_max, (a.nH + hpw - 1) / hpw);
   if (a.dh == 64) {
