@@ -210,7 +210,7 @@ int cerberus_set_taps(cerberus_ctx *ctx, const cerberus_taps *taps);
  *   "gemm_team"       (0..3, default 3)        bf16 launches of more than 128 rows run, on the kernel that deals
  *                                              (column block, k) ranges to teams of one workgroup per 128-row
  *                                              block: 1 the gate/up projection, 2 also QKV and 3 also the LM head
- *                                              (these two only past 256 rows);
+ *                                              (these two only past 256 rows) and the down projection (past 768);
  *                                              0: everything on the 64-row blocks of the split-K kernel
  *   "act_split"       (0 or 1, default 1)      1: GEMM inputs as hi + lo bf16 planes; 0: hi plane only
  *                                              (bf16-rounded GEMM inputs: faster, less accurate)

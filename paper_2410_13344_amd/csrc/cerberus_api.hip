@@ -432,12 +432,12 @@ void build_plans(cerberus_ctx* c) {
   const int d = D.d, L = D.n_layers;
   c->p_qkv.resize(L); c->p_o.resize(L); c->p_gu.resize(L); c->p_down.resize(L);
   for (int l = 0; l < L; ++l) {
-    { const void* A = c->xn; int lda = d, N = 3 * d, K = d; plan_gemm(c, c->p_qkv[l], 1, &A, &lda, (size_t)c->R64 * d, &c->wqkv[l], &N, &K, 64, false); c->p_qkv[l].team_rows = 2; }
+    { const void* A = c->xn; int lda = d, N = 3 * d, K = d; plan_gemm(c, c->p_qkv[l], 1, &A, &lda, (size_t)c->R64 * d, &c->wqkv[l], &N, &K, 64, false); c->p_qkv[l].team_rows = 2; c->p_qkv[l].team_above = 256; }
     { const void* A = c->attn; int lda = d, N = d, K = d; plan_gemm(c, c->p_o[l], 1, &A, &lda, (size_t)c->R64 * d, &c->wo[l], &N, &K, 64, false); }
-    { const void* A = c->xn; int lda = d, N = 2 * D.F, K = d; plan_gemm(c, c->p_gu[l], 1, &A, &lda, (size_t)c->R64 * d, &c->wgu[l], &N, &K, 64, false); c->p_gu[l].team_rows = 1; }
-    { const void* A = c->act; int lda = D.Fpad, N = d, K = D.F; plan_gemm(c, c->p_down[l], 1, &A, &lda, (size_t)c->R64 * D.Fpad, &c->wdown[l], &N, &K, 64, false); c->p_down[l].wide_rows = 1; }
+    { const void* A = c->xn; int lda = d, N = 2 * D.F, K = d; plan_gemm(c, c->p_gu[l], 1, &A, &lda, (size_t)c->R64 * d, &c->wgu[l], &N, &K, 64, false); c->p_gu[l].team_rows = 1; c->p_gu[l].team_above = 128; }
+    { const void* A = c->act; int lda = D.Fpad, N = d, K = D.F; plan_gemm(c, c->p_down[l], 1, &A, &lda, (size_t)c->R64 * D.Fpad, &c->wdown[l], &N, &K, 64, false); c->p_down[l].wide_rows = 1; c->p_down[l].team_rows = 3; c->p_down[l].team_above = 768; }
   }
-  { const void* A = c->xn; int lda = d, N = D.V, K = d; plan_gemm(c, c->p_lm, 1, &A, &lda, (size_t)c->R64 * d, &c->lm_head, &N, &K, 64, false); c->p_lm.wide_rows = 1; c->p_lm.team_rows = 3; }
+  { const void* A = c->xn; int lda = d, N = D.V, K = d; plan_gemm(c, c->p_lm, 1, &A, &lda, (size_t)c->R64 * d, &c->lm_head, &N, &K, 64, false); c->p_lm.wide_rows = 1; c->p_lm.team_rows = 3; c->p_lm.team_above = 256; }
   c->p_res.resize(D.R);
   const void* A[CERBERUS_MAX_HEADS]; const void* W[CERBERUS_MAX_HEADS];
   int lda[CERBERUS_MAX_HEADS], N[CERBERUS_MAX_HEADS], K[CERBERUS_MAX_HEADS];
@@ -476,11 +476,15 @@ int run_gemm(const cerberus_ctx* c, const GemmBatch& plan, const int* n_rows, in
   GemmBatch g = plan;
   // Above 128 rows the problems the planner marked (wide weights: gate/up, QKV, the LM head, in the order of what
   // they gain; the knob says how far down that list to go) run on the team kernel, which streams the weights once
-  // per team of row blocks; its partial planes are the split of the launch.  Narrow weights (O, down) would need
-  // more planes than the consumers sum and stay on the 64-row blocks (the plan refuses them).  QKV and the LM head
-  // change over only past 256 rows: with two row blocks their extra planes cost what the kernel gains.
+  // per team of row blocks; its partial planes are the split of the launch.  QKV and the LM head change over
+  // only past 256 rows: with two row blocks their extra planes cost what the kernel gains.  The down projection has
+  // few columns, so few row blocks mean many teams and planes (8 planes at 640 rows, where the kernel gains nothing);
+  // from seven row blocks on it takes 4 to 5 and wins: 162 us against 200 at 1024 rows of the 7B shape
+  // (+ 7 us for the consumer of the planes).  With a sixteenth of the bound's rows live it loses (16 sequences of 64 nodes,
+  // all on the one-token path: at most 0.7 of 12.4 ms per step), with half of them it wins (21.5 -> 20.4 ms).  The O
+  // projection, with a third of the K for the same planes, stays on the 64-row blocks (69 us + planes against 80).
   TeamPlan tp;
-  if (launched && plan.team_rows && c->gemm_team >= plan.team_rows && (plan.team_rows == 1 || rows_max > 256) && c->cfg.dtype == CERBERUS_BF16 && g.split && g.n_prob == 1 && !skip_flags &&
+  if (launched && plan.team_rows && c->gemm_team >= plan.team_rows && rows_max > plan.team_above && c->cfg.dtype == CERBERUS_BF16 && g.split && g.n_prob == 1 && !skip_flags &&
       c->fused_grid >= 8 && g.p[0].lda >= g.p[0].K &&   // (the kernel reads whole padded rows)
       plan_team_gemm(rows_max, g.p[0].N, g.p[0].K, c->fused_grid, c->max_split, &tp) &&
       (size_t)tp.planes * align_up((size_t)rows_max, 64) * g.p[0].N <= c->part_floats) {
@@ -939,9 +943,9 @@ int cerberus_bench_gemm(cerberus_ctx* ctx, int32_t kind, int32_t rows, void* str
     const bool f = ctx->use_fused && D.dtype == CERBERUS_BF16 && rows >= 1 && rows <= 64 && ctx->fused_grid > 0 && ctx->act_split == 1 &&
                    ((kind == 100 && ctx->ns_qkv) || (kind == 102 && ctx->ns_gu));
     TeamPlan tp;   // (2 + NT: the team kernel with NT row tiles per workgroup)
-    const int level = kind == 102 ? 1 : kind == 100 ? 2 : kind == 104 ? 3 : 99, N = kind == 102 ? 2 * D.F : kind == 100 ? 3 * D.d : D.V;
-    const bool team = ctx->gemm_team >= level && (level == 1 || rows > 256) && D.dtype == CERBERUS_BF16 && ctx->act_split == 1 && ctx->fused_grid >= 8 &&
-                      plan_team_gemm(rows, N, kpad(ctx->cfg, D.d), ctx->fused_grid, ctx->max_split, &tp);
+    const GemmBatch* g = kind == 100 ? &ctx->p_qkv[0] : kind == 102 ? &ctx->p_gu[0] : kind == 103 ? &ctx->p_down[0] : kind == 104 ? &ctx->p_lm : nullptr;
+    const bool team = g && g->team_rows && ctx->gemm_team >= g->team_rows && rows > g->team_above && D.dtype == CERBERUS_BF16 && ctx->act_split == 1 &&
+                      ctx->fused_grid >= 8 && plan_team_gemm(rows, g->p[0].N, g->p[0].K, ctx->fused_grid, ctx->max_split, &tp);
     if (bytes) *bytes = f ? 1.0 : team ? 2.0 + tp.NT : 0.0;
     return CERBERUS_OK;
   }

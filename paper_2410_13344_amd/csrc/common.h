@@ -129,7 +129,8 @@ struct GemmBatch {
   int row_blocks;                // bf16: blocks of 64 rows in the launch (set by the launcher)
   int fixed_s1;                  // host side: the planner keeps split-K off (the consumer reads out[0] as the result)
   int wide_rows;                 // host side: launches of more than 256 rows take the 4-slab instance (down projection, LM head)
-  int team_rows;                 // host side: launches of more than 128 rows go to the team kernel (gate/up projection)
+  int team_rows;                 // host side: launches of more than team_above rows go to the team kernel when the knob is at least this (0: never)
+  int team_above;
 };
 
 // GEMM of one problem over more than 128 rows by teams of workgroups (gemm_team.hip)

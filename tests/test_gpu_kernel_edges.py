@@ -94,3 +94,30 @@ def test_long_prompts_run_several_pieces_per_pass(dtype, attn_mfma, n_prompt, L0
             # (piece by piece over several calls the gate runs after every piece; in one call only after the prompt's last)
             assert last_fits or int(got.gate_flag[1]) == 1
     pair.engine.close()
+
+
+@pytest.mark.parametrize("one_token", [(), (0, 2, 3, 5, 6, 7, 9, 10, 12, 13, 15)])
+def test_down_projection_of_a_large_batch(one_token):
+    """16 sequences of a 192-node tree at d = 1024: the down projection runs on the team kernel (two column blocks, ten
+    teams), with all 3072 rows and with 971 of them.  One workgroup per (item, head) of sequences of many lengths in
+    attention.  Every row of every sequence against the oracle; the bars are those of the 7B shape, whose sums are longer."""
+    print(f"down projection, one-token sequences {one_token}", flush=True)
+    pair = H.Pair("tiny", B.CERBERUS_BF16, "bfs4x192", seed=4, max_batch=16, kv_capacity=512, d_model=1024, n_heads=8, head_dim=128, d_ffn=1000)
+    assert B.cerberus_bench_gemm(pair.engine.ctx, 103, 16 * pair.T) >= 2.0          # the team kernel takes it
+    assert B.cerberus_bench_gemm(pair.engine.ctx, 103, 768) == 0.0
+    taps, st = pair.taps(), pair.engine.new_state()
+    osts = []
+    for b in range(16):
+        ost = orc.prefill(pair.cfg, pair.W, synth.make_token_ids(3 + 19 * b, pair.cfg["vocab"], seed=60 + b).numpy(), capacity=pair.kv_capacity)
+        ost["flag"] = 1 if b in one_token else 0
+        H.round_oracle_kv(ost, B.CERBERUS_BF16)
+        H.upload_sequence(st, b, ost, B.CERBERUS_BF16)
+        osts.append(ost)
+    outs = [pair.oracle_step(ost) for ost in osts]
+    pair.engine.verify_step(st, 16)
+    torch.cuda.synchronize()
+    assert int(st.status[0]) == 0
+    for b, (ost, out) in enumerate(zip(osts, outs)):
+        rep = H.compare_step(pair.cfg, out, st, taps, b, pair.T, B.CERBERUS_BF16, ost, tol=H.TOL_BF16)
+        assert not rep.failures, f"seq {b}: " + "; ".join(rep.failures)
+    pair.engine.close()
