@@ -148,14 +148,15 @@ int cerberus_verify_step(cerberus_ctx *ctx, const cerberus_state *st, int32_t ba
 int cerberus_ar_step(cerberus_ctx *ctx, const cerberus_state *st, int32_t batch, void *stream);
 
 /* Prompt phase of Algorithm 1 (lines 1-5) for sequence `seq` of the batch: a causal forward of
- * `n_tokens` prompt tokens (DEVICE int32) appended at cache rows kv_len.., in passes of up to
- * CERBERUS_MAX_TREE rows (the result does not depend on the pass size up to the rounding of the cache: rows
- * of earlier passes are read back from the cache in its storage type), then on the last position the LM head (-> root_token), the
- * gate (-> gate_flag, entropy) and, where the gate says parallel, the heads (-> cand): the state a
- * first decoding step starts from.  kv_len[seq] advances by n_tokens; accept_len[seq] is set to 0;
- * the other sequences of the batch are not touched.  Tokens outside the vocabulary count as token 0
- * and set CERBERUS_DEV_BAD_TOKEN; a prompt that does not fit the cache sets CERBERUS_DEV_KV_OVERFLOW
- * and stops at the first pass that no longer fits.                                             */
+ * `n_tokens` prompt tokens (DEVICE int32) appended at cache rows kv_len.., then on the last position the LM head
+ * (-> root_token), the gate (-> gate_flag, entropy) and, where the gate says parallel, the heads (-> cand): the state a
+ * first decoding step starts from.  The prompt is cut into pieces of CERBERUS_MAX_TREE rows: the rows of a piece attend to
+ * each other at the precision of the computation and to all rows before the piece as the cache holds them, in its storage
+ * type.  Several pieces may run in one pass through the layers.  kv_len[seq] advances by n_tokens; accept_len[seq] is set
+ * to 0; the other sequences of the batch are not touched.  Taps show the rows of the prompt's last piece, from slot 0 on.
+ * Tokens outside the vocabulary count as token 0 and set CERBERUS_DEV_BAD_TOKEN; a prompt that does not fit the cache sets
+ * CERBERUS_DEV_KV_OVERFLOW and stops at the first piece that no longer fits: the pieces before it stay committed, nothing
+ * after it is, and root_token, gate_flag, entropy and cand keep their values.                                            */
 int cerberus_prefill(cerberus_ctx *ctx, const cerberus_state *st, int32_t batch, int32_t seq,
                      const int32_t *tokens, int32_t n_tokens, void *stream);
 

@@ -223,7 +223,7 @@ size_t layout(cerberus_ctx* c, unsigned char* base) {
   c->rm.row_tok = b.take<int>(Rmax);
   c->rm.att_item = b.take<int4>((size_t)c->att_cap);
   c->rm.seq_npi = b.take<int>(std::max(B, kPromptPieces));
-  c->rm.tail = b.take<int>(2);
+  c->rm.tail = b.take<int>(3);
   c->last_row = b.take<int>(B);
   c->path = b.take<int>((size_t)B * (D.Hc + 1));
   c->topk_v = b.take<float>((size_t)D.Hc * B * TOPK_MAX_PARTS * CERBERUS_MAX_TOPK);
@@ -686,7 +686,7 @@ int run_prompt(cerberus_ctx* c, const cerberus_state* st, int batch, int seq, co
     const int n = std::min(pass, n_tokens - off);
     const bool last = off + n >= n_tokens;
     const AttnShape sh{std::min(n, kPromptPiece), ceil_div(n, kPromptPiece), kPromptPiece, seq};
-    HIP_TRY(launch_assemble(D, c->chain, rm, *st, c->taps, batch, ASSEMBLE_PROMPT, PromptArgs{tokens + off, n, seq, kPromptPiece, last ? 1 : 0},
+    HIP_TRY(launch_assemble(D, c->chain, rm, *st, c->taps, batch, ASSEMBLE_PROMPT, PromptArgs{tokens + off, n, seq, kPromptPiece, off == 0 ? 1 : 0, last ? 1 : 0},
                             attn_plan_cfg(c), s));
     GemmProb pd{};
     TRY(forward_rows(c, st, n, c->chain, sh, &pd, s));

@@ -79,8 +79,9 @@ struct RowMap {
                   // first row, w = (cache-range items of the sequence << 16) | chunks per cache-range item;
                   // x = -1 from the end of the list on
   int* seq_npi;   // [B or pieces] cache-range items of the sequence (of a prompt pass: of the piece)
-  // prompt passes only: the rows of the pass that go on to the final norm and the LM head (see PromptArgs)
-  int* tail;      // [2] first row, rows
+  // prompt passes only: the rows of the pass that go on to the final norm and the LM head, and whether the prompt has ended
+  // for want of room (see PromptArgs)
+  int* tail;      // [3] first row, rows, ended
 };
 
 struct AttnPlanCfg {

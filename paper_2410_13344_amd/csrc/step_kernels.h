@@ -14,12 +14,13 @@ struct Dims {
 enum { ASSEMBLE_BY_FLAG = 0, ASSEMBLE_FORCE_AR = 1, ASSEMBLE_FULL_TREE = 2, ASSEMBLE_PROMPT = 3 };
 
 // Prompt pass: sequence `seq` runs `n` rows carrying tokens[0..n), every other sequence sits out.  The prompt counts in
-// pieces of `piece` tokens (the last one may be shorter): a piece is committed whole or, where the cache has no room for
-// it, not at all, and the output taps see the rows of the prompt's last piece, from slot 0 on.  A pass holds whole
-// pieces; with `last` it holds the prompt's last piece, whose rows alone go on to the LM head.
+// pieces of `piece` tokens (the last one may be shorter): a piece is committed whole, the first one that the cache has no
+// room for ends the prompt (the rest of its pass and the passes after it commit nothing), and the output taps see the rows
+// of the prompt's last piece, from slot 0 on.  A pass holds whole pieces; the `first` one starts the prompt, and `last` holds
+// its last piece, whose rows alone go on to the LM head.
 struct PromptArgs {
   const int* tokens;
-  int n, seq, piece, last;
+  int n, seq, piece, first, last;
 };
 
 struct ResFinishArgs {

@@ -103,7 +103,7 @@ __global__ __launch_bounds__(256) void k_assemble(const Dims D, const TreeDev tr
                                                  const cerberus_taps tp, int batch, int mode, const PromptArgs pa,
                                                  const AttnPlanCfg ap) {
   __shared__ int sT[CERBERUS_MAX_BATCH], sL[CERBERUS_MAX_BATCH], sRow0[CERBERUS_MAX_BATCH];
-  __shared__ int sFull, sTail;            // prompt pass: rows of whole pieces that fit, rows of the prompt's last piece
+  __shared__ int sFull;                   // prompt pass: its rows before the prompt's last piece
   const int t = threadIdx.x;
   if (t < batch) {
     const int L = st.kv_len[t];
@@ -111,18 +111,17 @@ __global__ __launch_bounds__(256) void k_assemble(const Dims D, const TreeDev tr
     if (mode == ASSEMBLE_FORCE_AR || (mode == ASSEMBLE_BY_FLAG && st.gate_flag[t] != 0)) Tb = 1;
     if (mode == ASSEMBLE_PROMPT) {        // a chain of prompt tokens (tr is the chain's tables)
       Tb = 0;
-      if (t == pa.seq) {                  // piece by piece: one that does not fit is left out, a shorter one after it may fit
-        const int n_full = pa.last ? (pa.n - 1) / pa.piece * pa.piece : pa.n;
-        int full = 0, tail = pa.n - n_full;
+      if (t == pa.seq) {                  // piece by piece, up to the first one without room: it ends the prompt
         const int room = L < 0 ? 0 : D.cap - L;
-        while (full < n_full && full + pa.piece <= room) full += pa.piece;
-        if (full + tail > room) tail = 0;
-        if (full + tail < pa.n) atomicOr(st.status, (int)CERBERUS_DEV_KV_OVERFLOW);
-        Tb = full + tail;
-        sFull = full;
-        sTail = tail;
-        rm.tail[0] = full;
+        if (pa.first || rm.tail[2] == 0)
+          while (Tb < pa.n && min(Tb + pa.piece, pa.n) <= room) Tb = min(Tb + pa.piece, pa.n);
+        const bool cut = Tb < pa.n;
+        if (cut) atomicOr(st.status, (int)CERBERUS_DEV_KV_OVERFLOW);
+        const int tail = pa.last && !cut ? (pa.n - 1) % pa.piece + 1 : 0;
+        sFull = Tb - tail;
+        rm.tail[0] = Tb - tail;
         rm.tail[1] = tail;
+        rm.tail[2] = cut;
       }
     }
     if (Tb > 0 && (L < 0 || L + Tb > D.cap)) {  // the sequence sits this step out
@@ -149,7 +148,7 @@ __global__ __launch_bounds__(256) void k_assemble(const Dims D, const TreeDev tr
     // capacity: a cache-range item covers `cps` chunks of one sequence's committed rows, a tree item 64 of
     // the step's own rows.  cps grows with the total length so that the list stays near the workgroup
     // target: a long cache is walked inside a workgroup (one partial result per item) instead of being cut
-    // into a partial per chunk.  Every thread derives the same plan; thread i writes entries i, i + 64, ...
+    // into a partial per chunk.  Every thread derives the same plan; thread i writes entries i, i + blockDim.x, ...
     // A prompt pass is listed piece by piece: piece p is a sequence of its own whose committed rows are the cache rows
     // before it (the earlier pieces of the pass among them: the layer's K/V rows are all in the cache by then).
     const bool prompt = mode == ASSEMBLE_PROMPT;
@@ -194,16 +193,14 @@ __global__ __launch_bounds__(256) void k_assemble(const Dims D, const TreeDev tr
         int tok;
         int slot = node;                       // of the tap
         if (mode == ASSEMBLE_PROMPT) {
-          // tail rows carry the last tokens of the pass, also where a piece before them was left out
-          const bool in_tail = node >= sFull;
-          tok = pa.tokens[in_tail ? pa.n - sTail + node - sFull : node];
-          // a slot shows the latest piece that has a row there: the tail, else the last whole piece
-          slot = in_tail ? node - sFull : node - (sFull - pa.piece);
-          if (!in_tail && (slot < sTail)) slot = D.T;
+          tok = pa.tokens[node];
+          // a slot shows the latest piece that has a row there: the prompt's last one, else the last whole piece
+          slot = node >= sFull ? node - sFull : node - (sFull - pa.piece);
+          if (node < sFull && slot < sT[b] - sFull) slot = D.T;
         } else tok = node == 0 ? st.root_token[b] : st.cand[(b * D.Hc + dep - 1) * D.topk + tr.rank[node]];
         if (tok < 0 || tok >= D.V) { atomicOr(st.status, (int)CERBERUS_DEV_BAD_TOKEN); tok = 0; }
         rm.row_tok[r] = tok;
-        if (tp.node_token && slot < D.T) tp.node_token[b * D.T + slot] = tok;   // the taps hold T rows per sequence
+        if (tp.node_token && slot >= 0 && slot < D.T) tp.node_token[b * D.T + slot] = tok;   // the taps hold T rows per sequence
       }
     }
   }

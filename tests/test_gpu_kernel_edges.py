@@ -40,22 +40,27 @@ def test_fp32_kernels_at_the_edges_of_their_tiles(tree, n_prompt, over):
     pair.engine.close()
 
 
-@pytest.mark.parametrize("n_prompt,L0", [(385, 0), (576, 1), (700, 130), (1152, 0), (1153, 3)])
+@pytest.mark.parametrize("n_prompt,L0", [(385, 0), (420, 7), (576, 1), (700, 130), (1152, 0), (1153, 3)])
 @pytest.mark.parametrize("dtype,attn_mfma", [(B.CERBERUS_F32, 0), (B.CERBERUS_BF16, 1), (B.CERBERUS_BF16, 0)])
 def test_long_prompts_run_several_pieces_per_pass(dtype, attn_mfma, n_prompt, L0):
     """A prompt of more than two pieces of 192 tokens goes through the layers in passes of up to six pieces: the cache
-    rows, the pending token and the tapped rows (the last piece's, from slot 0) against the same prompt handed over piece
-    by piece (each call a pass of its own); then the same with a cache that lacks room for the later pieces.  The pieces'
-    operands are the same either way and only sums change order: fp32 5e-5; bf16 within the bars of a prompt of two
-    passes (a different last bit flips the bf16 rounding of a cached row now and then)."""
+    rows, the pending token, the gate, the heads and the tapped rows (the last piece's, from slot 0) against the same prompt
+    handed over piece by piece (each call a pass of its own).  Then the same with a cache that has room for the first half
+    of the prompt and 24 rows: the pieces before the first one that does not fit are committed and nothing else, also where
+    the prompt's last piece would fit, in the same pass or in a later one.  The pieces' operands are the same either way and only
+    sums change order: fp32 5e-5; bf16 within the bars of a prompt of two passes (a different last bit flips the bf16
+    rounding of a cached row now and then)."""
     print(f"prompt of {n_prompt} after {L0} rows, dtype={dtype}, attn_mfma={attn_mfma}", flush=True)
     P = B.CERBERUS_MAX_TREE
     tol = H.TOL_F32 if dtype == B.CERBERUS_F32 else H.TOL_BF16
-    tokens = synth.make_token_ids(n_prompt, 1024, seed=5).cuda()
-    pair = H.Pair("tiny", dtype, "p63", seed=2, max_batch=2, kv_capacity=1280, topk=6)
+    tokens = synth.make_token_ids(n_prompt, 1024, seed=5)
+    pair = H.Pair("tiny", dtype, "p63", seed=2, max_batch=2, kv_capacity=1280, topk=6, entropy_threshold=float("inf"))
     pair.engine.set_param("attn_mfma", attn_mfma)
+    base = pair.T                                      # taps: T rows per sequence, sequence 1
+    n_last = (n_prompt - 1) % P + 1
+    kept = ("root_token", "gate_flag", "entropy", "cand")
 
-    def run(start, pieces):
+    def run(start, n_tokens, pieces):
         taps, st = pair.taps(), pair.engine.new_state()
         g = torch.Generator(device="cuda")
         g.manual_seed(1)
@@ -63,36 +68,43 @@ def test_long_prompts_run_several_pieces_per_pass(dtype, attn_mfma, n_prompt, L0
             layer.normal_(0.0, 1.0, generator=g)
         st.kv_len.copy_(torch.tensor([17, start], dtype=torch.int32))
         st.gate_flag[:] = 1
-        for i in range(0, n_prompt, pieces or n_prompt):
-            pair.engine.prefill(st, 2, 1, tokens[i:i + (pieces or n_prompt)])
+        st.root_token[:], st.entropy[:], st.cand[:] = 7, 0.25, 9
+        taps.node_token[:] = -5
+        before = {k: getattr(st, k).clone() for k in kept}
+        for i in range(0, n_tokens, pieces or n_tokens):
+            pair.engine.prefill(st, 2, 1, tokens[i:min(i + (pieces or n_tokens), n_tokens)].cuda())
         torch.cuda.synchronize()
-        return st, taps
+        return st, taps, before
 
-    for start in (L0, 1280 - n_prompt // 2):          # the second start leaves room for about half of the prompt
-        got, gt = run(start, None)
-        want, wt = run(start, P)
-        fits = start + n_prompt <= 1280
-        last_fits = int(want.kv_len[1]) >= n_prompt - (n_prompt - 1) // P * P + start and int(want.gate_flag[1]) == 0
-        assert int(got.kv_len[1]) == int(want.kv_len[1]) and int(got.kv_len[0]) == 17
-        assert (int(got.kv_len[1]) == start + n_prompt) == fits
-        assert int(got.status[0]) == int(want.status[0]) == (0 if fits else B.CERBERUS_DEV_KV_OVERFLOW)
-        n = int(want.kv_len[1])
+    for start in (L0, 1280 - n_prompt // 2 - 24):
+        fit = n_prompt if start + n_prompt <= 1280 else (1280 - start) // P * P     # rows of the pieces that fit
+        got, gt, before = run(start, n_prompt, None)
+        want, wt, _ = run(start, fit, P)
+        n = start + fit
+        assert (fit == n_prompt) == (start == L0) and 0 < fit
+        assert got.kv_len.tolist() == want.kv_len.tolist() == [17, n]
+        assert int(got.status[0]) == (0 if fit == n_prompt else B.CERBERUS_DEV_KV_OVERFLOW)
         assert torch.equal(got.kv[:, :, 0], want.kv[:, :, 0]) and torch.equal(got.kv[:, :, 1, :, n:], want.kv[:, :, 1, :, n:])
         mm = H.kv_mismatch(got.kv[:, :, 1, :, :n].double().cpu().numpy(), want.kv[:, :, 1, :, :n].double().cpu().numpy(), tol)
         assert mm is None, mm
-        if fits:
-            k = min((n_prompt - 1) % P + 1, pair.T)
-            base = pair.T                              # taps: T rows per sequence, sequence 1
-            assert float((gt.logits[base:base + k] - wt.logits[base:base + k]).abs().max()) <= tol.logits
-            assert float((gt.h_last[base:base + k] - wt.h_last[base:base + k]).abs().max()) <= tol.hidden
-            assert abs(float(got.entropy[1]) - float(want.entropy[1])) <= tol.entropy
-            assert int(got.gate_flag[1]) == int(want.gate_flag[1])
-            top = wt.logits[base + k - 1].sort().values if k == (n_prompt - 1) % P + 1 else None
-            if top is not None and float(top[-1] - top[-2]) > 2 * tol.logits:
+        # the token of a slot is that of the latest piece which has a row there
+        tail = n_last if fit == n_prompt else 0
+        expect = [int(tokens[fit - tail + i]) if i < tail else int(tokens[fit - tail - P + i]) for i in range(pair.T)]
+        assert gt.node_token.tolist() == [-5] * base + expect
+        if fit < n_prompt:
+            for name in kept:
+                assert torch.equal(getattr(got, name), before[name]), name
+            continue
+        k = min(n_last, pair.T)
+        assert float((gt.logits[base:base + k] - wt.logits[base:base + k]).abs().max()) <= tol.logits
+        assert float((gt.h_last[base:base + k] - wt.h_last[base:base + k]).abs().max()) <= tol.hidden
+        assert float((gt.head_logits[1] - wt.head_logits[1]).abs().max()) <= tol.logits
+        assert abs(float(got.entropy[1]) - float(want.entropy[1])) <= tol.entropy
+        assert got.gate_flag.tolist() == [1, 0] and torch.equal(got.cand[0], before["cand"][0])
+        if k == n_last:                                # the last row is tapped
+            top = wt.logits[base + k - 1].sort().values
+            if float(top[-1] - top[-2]) > 2 * tol.logits:
                 assert int(got.root_token[1]) == int(want.root_token[1])
-        else:
-            # (piece by piece over several calls the gate runs after every piece; in one call only after the prompt's last)
-            assert last_fits or int(got.gate_flag[1]) == 1
     pair.engine.close()
 
 
