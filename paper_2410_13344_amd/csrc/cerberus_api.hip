@@ -62,7 +62,7 @@ struct cerberus_ctx {
   RowMap rm{};
   double* inv_freq = nullptr;
   float2* rope_cs = nullptr;   // [rows][dh/2] (cos, sin) of this launch's row positions
-  int *last_row = nullptr, *path = nullptr, *g = nullptr;
+  int *last_row = nullptr, *path = nullptr, *g = nullptr, *down_planes = nullptr;
   float* topk_v = nullptr;   // per-slice candidate lists of the heads' top-k: [Hc][Bmax][TOPK_MAX_PARTS][CERBERUS_MAX_TOPK]
   int* topk_i = nullptr;
   float *x = nullptr, *h_last = nullptr, *part = nullptr, *attn_po = nullptr, *attn_ml = nullptr, *ssq = nullptr;
@@ -226,6 +226,7 @@ size_t layout(cerberus_ctx* c, unsigned char* base) {
   c->rm.tail = b.take<int>(3);
   c->last_row = b.take<int>(B);
   c->path = b.take<int>((size_t)B * (D.Hc + 1));
+  c->down_planes = b.take<int>(1);
   c->topk_v = b.take<float>((size_t)D.Hc * B * TOPK_MAX_PARTS * CERBERUS_MAX_TOPK);
   c->topk_i = b.take<int>((size_t)D.Hc * B * TOPK_MAX_PARTS * CERBERUS_MAX_TOPK);
   c->g = b.take<int>(Rmax);
@@ -435,7 +436,7 @@ void build_plans(cerberus_ctx* c) {
     { const void* A = c->xn; int lda = d, N = 3 * d, K = d; plan_gemm(c, c->p_qkv[l], 1, &A, &lda, (size_t)c->R64 * d, &c->wqkv[l], &N, &K, 64, false); c->p_qkv[l].team_rows = 2; c->p_qkv[l].team_above = 256; }
     { const void* A = c->attn; int lda = d, N = d, K = d; plan_gemm(c, c->p_o[l], 1, &A, &lda, (size_t)c->R64 * d, &c->wo[l], &N, &K, 64, false); }
     { const void* A = c->xn; int lda = d, N = 2 * D.F, K = d; plan_gemm(c, c->p_gu[l], 1, &A, &lda, (size_t)c->R64 * d, &c->wgu[l], &N, &K, 64, false); c->p_gu[l].team_rows = 1; c->p_gu[l].team_above = 128; }
-    { const void* A = c->act; int lda = D.Fpad, N = d, K = D.F; plan_gemm(c, c->p_down[l], 1, &A, &lda, (size_t)c->R64 * D.Fpad, &c->wdown[l], &N, &K, 64, false); c->p_down[l].wide_rows = 1; c->p_down[l].team_rows = 3; c->p_down[l].team_above = 768; }
+    { const void* A = c->act; int lda = D.Fpad, N = d, K = D.F; plan_gemm(c, c->p_down[l], 1, &A, &lda, (size_t)c->R64 * D.Fpad, &c->wdown[l], &N, &K, 64, false); c->p_down[l].wide_rows = 1; c->p_down[l].team_rows = 3; c->p_down[l].team_above = 768; c->p_down[l].team_live = 1; }
   }
   { const void* A = c->xn; int lda = d, N = D.V, K = d; plan_gemm(c, c->p_lm, 1, &A, &lda, (size_t)c->R64 * d, &c->lm_head, &N, &K, 64, false); c->p_lm.wide_rows = 1; c->p_lm.team_rows = 3; c->p_lm.team_above = 256; }
   c->p_res.resize(D.R);
@@ -480,13 +481,13 @@ int run_gemm(const cerberus_ctx* c, const GemmBatch& plan, const int* n_rows, in
   // only past 256 rows: with two row blocks their extra planes cost what the kernel gains.  The down projection has
   // few columns, so few row blocks mean many teams and planes (8 planes at 640 rows, where the kernel gains nothing);
   // from seven row blocks on it takes 4 to 5 and wins: 162 us against 200 at 1024 rows of the 7B shape
-  // (+ 7 us for the consumer of the planes).  With a sixteenth of the bound's rows live it loses (16 sequences of 64 nodes,
-  // all on the one-token path: at most 0.7 of 12.4 ms per step), with half of them it wins (21.5 -> 20.4 ms).  The O
-  // projection, with a third of the K for the same planes, stays on the 64-row blocks (69 us + planes against 80).
+  // (+ 7 us for the consumer of the planes).  How many of those rows are live the gate decides on the device, so its
+  // teams and planes follow the live rows (see plan_team_gemm).  The O projection, with a third of the K for the same
+  // planes, stays on the 64-row blocks (69 us + planes against 80).
   TeamPlan tp;
   if (launched && plan.team_rows && c->gemm_team >= plan.team_rows && rows_max > plan.team_above && c->cfg.dtype == CERBERUS_BF16 && g.split && g.n_prob == 1 && !skip_flags &&
       c->fused_grid >= 8 && g.p[0].lda >= g.p[0].K &&   // (the kernel reads whole padded rows)
-      plan_team_gemm(rows_max, g.p[0].N, g.p[0].K, c->fused_grid, c->max_split, &tp) &&
+      plan_team_gemm(rows_max, g.p[0].N, g.p[0].K, c->fused_grid, c->max_split, plan.team_live != 0, &tp) &&
       (size_t)tp.planes * align_up((size_t)rows_max, 64) * g.p[0].N <= c->part_floats) {
     GemmProb& P = g.p[0];
     P.out_rows = (int)align_up((size_t)rows_max, 64);
@@ -495,7 +496,11 @@ int run_gemm(const cerberus_ctx* c, const GemmBatch& plan, const int* n_rows, in
     TeamGemmArgs ta{};
     ta.W = reinterpret_cast<const uint4*>(P.W); ta.A = reinterpret_cast<const bf16_t*>(P.A); ta.lo_off = P.lo_off; ta.lda = P.lda;
     ta.out = P.out; ta.out_rows = P.out_rows; ta.N = P.N; ta.ksteps = P.K / 32;
-    ta.n_rows = n_rows; ta.rows_static = rows_static; ta.rows_cap = rows_max; ta.rb_min = tp.rb_min; ta.P = tp.planes;
+    ta.n_rows = n_rows; ta.rows_static = rows_static; ta.rows_cap = rows_max; ta.rb_min = tp.rb_min; ta.t_max = tp.t_max; ta.P = tp.planes;
+    if (plan.team_live) {
+      P.S_dev = ta.planes_out = c->down_planes;
+      std::memcpy(ta.planes_of, tp.planes_of, sizeof ta.planes_of);
+    }
     *launched = P;
     HIP_TRY(launch_team_gemm(ta, tp, s));
     return CERBERUS_OK;
@@ -565,7 +570,7 @@ int forward_rows(cerberus_ctx* c, const cerberus_state* st, int rows_max, const 
   const bool fused = c->use_fused && D.dtype == CERBERUS_BF16 && rows_max <= 64 && c->fused_grid > 0 && c->act_split == 1;
   const bool fq = fused && c->ns_qkv > 0, fg = fused && c->ns_gu > 0;
   for (int l = 0; l < D.n_layers; ++l) {
-    HIP_TRY(launch_add_gain(D, rm, c->x, prev ? prev->out : nullptr, prev ? prev->S : 0,
+    HIP_TRY(launch_add_gain(D, rm, c->x, prev ? prev->out : nullptr, prev ? prev->S : 0, prev ? prev->S_dev : nullptr,
                             prev ? (size_t)prev->out_rows * prev->N : 0, c->attn_norm[l], c->xn, c->ssq, rows_max, s, fq));
     GemmProb pq, po, pg;
     void* kv_layer = (unsigned char*)st->kv + (size_t)l * kv_layer_bytes;
@@ -588,7 +593,7 @@ int forward_rows(cerberus_ctx* c, const cerberus_state* st, int rows_max, const 
     aa.rows_max = rows_max; aa.status = st->status;
     HIP_TRY(launch_attention(aa, D.dtype, c->use_mfma_attn, s));
     TRY(run_gemm(c, c->p_o[l], rm.n_rows, 0, rows_max, nullptr, 0, s, &po));
-    HIP_TRY(launch_add_gain(D, rm, c->x, po.out, po.S, (size_t)po.out_rows * po.N, c->ffn_norm[l], c->xn, c->ssq, rows_max, s, fg));
+    HIP_TRY(launch_add_gain(D, rm, c->x, po.out, po.S, po.S_dev, (size_t)po.out_rows * po.N, c->ffn_norm[l], c->xn, c->ssq, rows_max, s, fg));
     if (fg) {
       TRY(run_fused_gate_up(c, l, s));
     } else {
@@ -604,7 +609,7 @@ int forward_rows(cerberus_ctx* c, const cerberus_state* st, int rows_max, const 
 // Final norm, LM head and per-row argmax over the rows of the row map, which are the layers' rows from *src0 on (null: 0)
 int run_lm_head(cerberus_ctx* c, const GemmProb& pd, const int* src0, int rows_max, hipStream_t s) {
   const Dims& D = c->D;
-  HIP_TRY(launch_add_rmsnorm(D, c->rm, c->x, pd.out, pd.S, (size_t)pd.out_rows * pd.N, c->final_norm, c->xn,
+  HIP_TRY(launch_add_rmsnorm(D, c->rm, c->x, pd.out, pd.S, pd.S_dev, (size_t)pd.out_rows * pd.N, c->final_norm, c->xn,
                              c->h_last, c->taps.h_last, src0, rows_max, s));
   GemmProb pl;
   TRY(run_gemm(c, c->p_lm, c->rm.n_rows, 0, rows_max, nullptr, 0, s, &pl));
@@ -945,7 +950,7 @@ int cerberus_bench_gemm(cerberus_ctx* ctx, int32_t kind, int32_t rows, void* str
     TeamPlan tp;   // (2 + NT: the team kernel with NT row tiles per workgroup)
     const GemmBatch* g = kind == 100 ? &ctx->p_qkv[0] : kind == 102 ? &ctx->p_gu[0] : kind == 103 ? &ctx->p_down[0] : kind == 104 ? &ctx->p_lm : nullptr;
     const bool team = g && g->team_rows && ctx->gemm_team >= g->team_rows && rows > g->team_above && D.dtype == CERBERUS_BF16 && ctx->act_split == 1 &&
-                      ctx->fused_grid >= 8 && plan_team_gemm(rows, g->p[0].N, g->p[0].K, ctx->fused_grid, ctx->max_split, &tp);
+                      ctx->fused_grid >= 8 && plan_team_gemm(rows, g->p[0].N, g->p[0].K, ctx->fused_grid, ctx->max_split, g->team_live != 0, &tp);
     if (bytes) *bytes = f ? 1.0 : team ? 2.0 + tp.NT : 0.0;
     return CERBERUS_OK;
   }

@@ -113,6 +113,7 @@ struct GemmProb {
   int S;          // split-K factor
   int kps;        // k-steps (of 32) per split, a multiple of the kernel's LDS chunk (4 with both activation planes, 8 with one)
   int rem;        // the first `rem` splits take one LDS chunk more than kps (a split count that does not divide the chunks)
+  const int* S_dev;   // as launched: if set, the launch leaves the number of planes to sum here, at most S
 };
 
 enum { GEMM_MAX_PROB = 8 };
@@ -132,9 +133,11 @@ struct GemmBatch {
   int wide_rows;                 // host side: launches of more than 256 rows take the 4-slab instance (down projection, LM head)
   int team_rows;                 // host side: launches of more than team_above rows go to the team kernel when the knob is at least this (0: never)
   int team_above;
+  int team_live;                 // host side: the team kernel's teams follow the rows that are live, not the bound (TeamPlan)
 };
 
 // GEMM of one problem over more than 128 rows by teams of workgroups (gemm_team.hip)
+enum { TEAM_MAX_RB = 31 };
 struct TeamGemmArgs {
   const uint4* W;        // pre-tiled weights: piece (slab, k-step) at (slab * ksteps + ks) * 64 sixteen-byte pieces
   const bf16_t* A;       // [rows][lda] hi plane, the lo plane lo_off elements later
@@ -146,14 +149,19 @@ struct TeamGemmArgs {
   int rows_static;
   int rows_cap;          // upper bound of the row count the plan was made for
   int rb_min;            // least number of row blocks (>= 2)
+  int t_max;             // most teams
   int P;                 // partial planes the consumer sums (an upper bound of what any row count needs)
+  int* planes_out;       // if set: the consumer sums planes_of(row blocks) planes instead, a number that is left here
+  unsigned long long planes_of[2];
 };
 struct TeamPlan {
-  int NT, planes, grid;    // row tiles per workgroup, partial planes, workgroups
-  int rb_min;              // least number of row blocks the device may form
+  int NT, planes, grid;    // row tiles per workgroup, partial planes (the most that any row count takes), workgroups
+  int rb_min, t_max;       // least number of row blocks the device may form, most teams
+  unsigned long long planes_of[2];   // of a plan with `live`, partial planes by row blocks: 4 bits each, one less than the planes
   int RB, rows_per, T;     // row blocks, rows per block and teams if the launch has as many rows as the plan allows
 };
-bool plan_team_gemm(int rows_max, int N, int Kpad, int cus, int max_planes, TeamPlan* tp);
+// live: few rows of a large bound are dealt to more teams and planes than the bound's own shape has
+bool plan_team_gemm(int rows_max, int N, int Kpad, int cus, int max_planes, bool live, TeamPlan* tp);
 hipError_t init_team_gemm();
 hipError_t launch_team_gemm(const TeamGemmArgs& a, const TeamPlan& tp, hipStream_t s);
 

@@ -69,7 +69,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int nslab = a.N >> 4;
   const int CB = (nslab + kSPT - 1) / kSPT;
   const long long V = (long long)CB * nst;
-  const int T = (int)min((long long)((int)gridDim.x / RB), V);
+  const int T = (int)min((long long)min((int)gridDim.x / RB, a.t_max), V);
+  const int P = a.planes_out ? (int)(((RB < 16 ? a.planes_of[0] : a.planes_of[1]) >> ((RB & 15) * 4)) & 15) + 1 : a.P;
+  if (a.planes_out && blockIdx.x == 0 && threadIdx.x == 0) *a.planes_out = P;
   // consecutive workgroup ids go to the 8 XCDs in turn: logical ids put a team's workgroups on one XCD
   const int G = gridDim.x;                 // a multiple of 8
   const int L = ((int)blockIdx.x & 7) * (G >> 3) + ((int)blockIdx.x >> 3);
@@ -194,7 +196,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
           }
         }
         if (tile_end) {   // the team that finishes a block clears the planes nobody writes there
-          for (int pp = plane + 1; pp < a.P; ++pp) {
+          for (int pp = plane + 1; pp < P; ++pp) {
             float* o = a.out + (size_t)pp * a.out_rows * a.N;
 #pragma unroll 1
             for (int j = 0; j < jlim; ++j)
@@ -239,12 +241,12 @@ hipError_t launch_nt(const TeamGemmArgs& a, int grid, hipStream_t s) {
 
 // The shape a launch takes for `rows` rows with NT row tiles per workgroup on `cus` workgroups (the kernel forms the
 // same on the device): row blocks, rows per block, teams, partial planes.
-static void team_shape(int rows, int NT, int rb_min, int N, int Kpad, int cus, int* RB, int* rows_per, int* T, int* planes) {
+static void team_shape(int rows, int NT, int rb_min, int t_max, int N, int Kpad, int cus, int* RB, int* rows_per, int* T, int* planes) {
   *RB = std::max(rb_min, (rows + NT * 16 - 1) / (NT * 16));
   *rows_per = ((rows + *RB - 1) / *RB + 15) / 16 * 16;
   const int nst = Kpad / 32 / kKC, CB = (N / 16 + kSPT - 1) / kSPT;
   const long long V = (long long)CB * nst;
-  *T = (int)std::min<long long>(cus / *RB, V);
+  *T = (int)std::min<long long>(std::min(cus / *RB, t_max), V);
   *planes = 1;
   if (*T < 1) return;
   for (int c = 0; c < CB; ++c)
@@ -254,24 +256,45 @@ static void team_shape(int rows, int NT, int rb_min, int N, int Kpad, int cus, i
 // Plan for a launch of up to rows_max rows on `cus` compute units (a multiple of 8): the row tiles per workgroup and
 // the number of partial planes a consumer has to sum whatever the row count turns out to be; false where the kernel
 // does not apply (few rows, a shape it cannot tile, more planes than max_planes).
-bool plan_team_gemm(int rows_max, int N, int Kpad, int cus, int max_planes, TeamPlan* tp) {
+//
+// The planes depend on the teams only, and the teams on the row blocks.  Without `live`, small row counts keep nearly as
+// many row blocks as the bound, so that one plane count, close to the one of the full launch, does for all of them; a
+// launch with few rows then runs on the few teams of the bound's shape.  With `live` the row blocks go down to four (64
+// workgroups of different column blocks and k ranges per row block, as many planes as max_planes allows) and the consumer
+// reads the number of planes from the device.  Down projection of the 7B shape in a launch planned for 1024 rows, us (the
+// 64-row blocks; teams of the bound's shape; with `live`): 16 live rows 45 / 65 / 41, 128: 58 / 67 / 46-49, 205: 62 / 72 /
+// 60-63, 256: 64 / 78 / 65-69, 323: 111 / 84 / 77, 512: 122 / 109 / 94, 768: 178 / 132 / 133, 1024: 198 / 157 / 157.  Three
+// or fewer row blocks would leave more than a quarter of the workgroups without work for the same planes (205 rows: 76).
+bool plan_team_gemm(int rows_max, int N, int Kpad, int cus, int max_planes, bool live, TeamPlan* tp) {
   if (rows_max <= 128 || N % 16 != 0 || Kpad % (32 * kKC) != 0 || cus < 8 || cus % 8 != 0) return false;
   const int RBmax = (rows_max + 127) / 128;
   const int NT = (((rows_max + RBmax - 1) / RBmax) + 15) / 16;
   if (NT < 5 || NT > 8 || cus / RBmax < 1) return false;      // (NT < 5 cannot happen above 128 rows)
-  // the planes depend on the teams only, and the teams on the row blocks: every count the device may choose
-  // fewer row blocks mean more teams and more planes: small row counts keep nearly as many row blocks as the bound
-  const int rb_min = std::max(2, RBmax - 1);
-  int planes = 1;
-  for (int RB = rb_min; RB <= std::max(rb_min, (rows_max + NT * 16 - 1) / (NT * 16)); ++RB) {
+  int rb_min = std::max(2, RBmax - 1), t_max = cus;
+  const int rb_hi = std::max(rb_min, (rows_max + NT * 16 - 1) / (NT * 16));
+  auto planes_at = [&](int RB) {
     int rb, rp, T, pl;
-    team_shape(RB * NT * 16, NT, rb_min, N, Kpad, cus, &rb, &rp, &T, &pl);
-    if (T < 1) return false;
-    planes = std::max(planes, pl);
+    team_shape(RB * NT * 16, NT, rb_min, t_max, N, Kpad, cus, &rb, &rp, &T, &pl);
+    return T < 1 ? max_planes + 1 : pl;
+  };
+  auto most_planes = [&]() {
+    int most = 1;
+    for (int RB = rb_min; RB <= rb_hi; ++RB) most = std::max(most, planes_at(RB));
+    return most;
+  };
+  if (most_planes() > max_planes) return false;
+  if (live && rb_hi <= TEAM_MAX_RB && max_planes <= 16) {
+    rb_min = std::min(rb_min, 4);
+    t_max = cus / rb_min;
+    while (most_planes() > max_planes) --t_max;               // (ends: one team needs one plane)
+    tp->planes_of[0] = tp->planes_of[1] = 0;
+    for (int RB = rb_min; RB <= rb_hi; ++RB) tp->planes_of[RB >> 4] |= (unsigned long long)(planes_at(RB) - 1) << ((RB & 15) * 4);
+  } else if (live) {
+    return false;
   }
-  if (planes > max_planes) return false;
-  tp->NT = NT; tp->planes = planes; tp->grid = cus; tp->rb_min = rb_min;
-  team_shape(rows_max, NT, rb_min, N, Kpad, cus, &tp->RB, &tp->rows_per, &tp->T, &planes);   // (the shape at the bound, for reference)
+  tp->NT = NT; tp->planes = most_planes(); tp->grid = cus; tp->rb_min = rb_min; tp->t_max = t_max;
+  int planes;
+  team_shape(rows_max, NT, rb_min, t_max, N, Kpad, cus, &tp->RB, &tp->rows_per, &tp->T, &planes);   // (the shape at the bound, for reference)
   return true;
 }
 

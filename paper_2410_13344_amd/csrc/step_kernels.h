@@ -49,12 +49,13 @@ hipError_t launch_prompt_root(const cerberus_state& st, const int* g, const int*
 // also fills rope_cs[row][j] = (cos, sin)(pos(row) * inv_freq[j]), j < dh/2, the angle formed in double
 hipError_t launch_embed(const Dims& D, const RowMap& rm, const void* embed, float* x, const double* inv_freq, float2* rope_cs,
                         int rows_max, hipStream_t s);
-hipError_t launch_add_rmsnorm(const Dims& D, const RowMap& rm, float* x, const float* part, int S, size_t pstride,
+// S_dev: if set, the number of partial planes is read from there (at most S)
+hipError_t launch_add_rmsnorm(const Dims& D, const RowMap& rm, float* x, const float* part, int S, const int* S_dev, size_t pstride,
                               const float* gain, void* out, float* out_f32, float* tap, const int* src0, int rows_max, hipStream_t s);
 // residual add + x * gain + per-block sums of x^2 (the RMSNorm scalar is applied by the consumer of the next GEMM)
 int add_gain_blocks(int d);   // sums per row
 // a_tiled: write the GEMM input in MFMA A-fragment order (64 rows, see FusedQkvArgs) instead of row-major planes
-hipError_t launch_add_gain(const Dims& D, const RowMap& rm, float* x, const float* part, int S, size_t pstride,
+hipError_t launch_add_gain(const Dims& D, const RowMap& rm, float* x, const float* part, int S, const int* S_dev, size_t pstride,
                            const float* gain, void* out, float* ssq, int rows_max, hipStream_t s, bool a_tiled = false);
 hipError_t launch_rope_kv(const Dims& D, const RowMap& rm, const float* part, int S, size_t pstride,
                           const float2* rope_cs, void* q, void* kv_layer, void* ktree, void* vtree, const float* ssq,

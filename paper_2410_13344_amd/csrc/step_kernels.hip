@@ -302,13 +302,14 @@ hipError_t launch_embed(const Dims& D, const RowMap& rm, const void* embed, floa
 // every partial of a group in flight together, so the row is read exactly once, in one round trip.
 template <typename T, int MAXS>
 __global__ __launch_bounds__(1024) void k_add_rmsnorm(float* __restrict__ x, const float* __restrict__ part, int S,
-                                                      size_t pstride, const float* __restrict__ gain, float eps,
+                                                      const int* __restrict__ S_dev, size_t pstride, const float* __restrict__ gain, float eps,
                                                       T* __restrict__ out, size_t lo_off, float* __restrict__ out_f32,
                                                       float* __restrict__ tap, const int* __restrict__ src0, const RowMap rm, int d,
                                                       int T_tree) {
   __shared__ float sh[16];
   const int r = blockIdx.x;
   if (r >= *rm.n_rows) return;
+  if (S_dev) S = *S_dev;
   const size_t rs = r + (src0 ? *src0 : 0);            // the layers' row that row r of the head is
   float* xr = x + rs * d;
   float4 v[2], g[2];
@@ -346,14 +347,14 @@ __global__ __launch_bounds__(1024) void k_add_rmsnorm(float* __restrict__ x, con
   }
 }
 
-hipError_t launch_add_rmsnorm(const Dims& D, const RowMap& rm, float* x, const float* part, int S, size_t pstride,
+hipError_t launch_add_rmsnorm(const Dims& D, const RowMap& rm, float* x, const float* part, int S, const int* S_dev, size_t pstride,
                               const float* gain, void* out, float* out_f32, float* tap, const int* src0, int rows_max, hipStream_t s) {
 #define CERB_CALL(MS)                                                                                                   \
   if (D.dtype == 0)                                                                                                     \
-    hipLaunchKernelGGL((k_add_rmsnorm<float, MS>), dim3(rows_max), dim3(1024), 0, s, x, part, S, pstride, gain, D.eps,  \
+    hipLaunchKernelGGL((k_add_rmsnorm<float, MS>), dim3(rows_max), dim3(1024), 0, s, x, part, S, S_dev, pstride, gain, D.eps,  \
                        (float*)out, (size_t)0, out_f32, tap, src0, rm, D.d, D.T);                                             \
   else                                                                                                                  \
-    hipLaunchKernelGGL((k_add_rmsnorm<bf16_t, MS>), dim3(rows_max), dim3(1024), 0, s, x, part, S, pstride, gain, D.eps, \
+    hipLaunchKernelGGL((k_add_rmsnorm<bf16_t, MS>), dim3(rows_max), dim3(1024), 0, s, x, part, S, S_dev, pstride, gain, D.eps, \
                        (bf16_t*)out, (size_t)D.R64 * D.d, out_f32, tap, src0, rm, D.d, D.T)
   CERB_S_BUCKET(S, CERB_CALL);
 #undef CERB_CALL
@@ -371,12 +372,14 @@ hipError_t launch_add_rmsnorm(const Dims& D, const RowMap& rm, float* x, const f
 // TILED (bf16 only): the GEMM input goes out in MFMA A-fragment order for the whole-K GEMMs: the 8 values of
 // row r at columns ks*32 + g*8.. form 16-byte piece ((ks*2 + plane)*4 + r/16)*64 + r%16 + 16*g, 64 rows in all.
 template <typename T, int MAXS, bool TILED>
-__global__ __launch_bounds__(256) void k_add_gain(float* __restrict__ x, const float* __restrict__ part, int S, size_t pstride,
+__global__ __launch_bounds__(256) void k_add_gain(float* __restrict__ x, const float* __restrict__ part, int S,
+                                                  const int* __restrict__ S_dev, size_t pstride,
                                                   const float* __restrict__ gain, T* __restrict__ out, size_t lo_off,
                                                   float* __restrict__ ssq, const RowMap rm, int d) {
   __shared__ float sh[4];
   const int r = blockIdx.x, nb = gridDim.y;
   if (r >= *rm.n_rows) return;
+  if (S_dev) S = *S_dev;
   const int c = (blockIdx.y * 256 + threadIdx.x) * 4;
   float ss = 0.f;
   if (c < d) {
@@ -410,19 +413,19 @@ __global__ __launch_bounds__(256) void k_add_gain(float* __restrict__ x, const f
 
 int add_gain_blocks(int d) { return (d + 1023) / 1024; }
 
-hipError_t launch_add_gain(const Dims& D, const RowMap& rm, float* x, const float* part, int S, size_t pstride,
+hipError_t launch_add_gain(const Dims& D, const RowMap& rm, float* x, const float* part, int S, const int* S_dev, size_t pstride,
                            const float* gain, void* out, float* ssq, int rows_max, hipStream_t s, bool a_tiled) {
   const dim3 grid(rows_max, add_gain_blocks(D.d));
   if (a_tiled && (D.dtype == 0 || rows_max > 64)) return hipErrorInvalidValue;
 #define CERB_CALL(MS)                                                                                                  \
   if (D.dtype == 0)                                                                                                    \
-    hipLaunchKernelGGL((k_add_gain<float, MS, false>), grid, dim3(256), 0, s, x, part, S, pstride, gain, (float*)out,  \
+    hipLaunchKernelGGL((k_add_gain<float, MS, false>), grid, dim3(256), 0, s, x, part, S, S_dev, pstride, gain, (float*)out,  \
                        (size_t)0, ssq, rm, D.d);                                                                       \
   else if (a_tiled)                                                                                                    \
-    hipLaunchKernelGGL((k_add_gain<bf16_t, MS, true>), grid, dim3(256), 0, s, x, part, S, pstride, gain, (bf16_t*)out, \
+    hipLaunchKernelGGL((k_add_gain<bf16_t, MS, true>), grid, dim3(256), 0, s, x, part, S, S_dev, pstride, gain, (bf16_t*)out, \
                        (size_t)D.R64 * D.d, ssq, rm, D.d);                                                             \
   else                                                                                                                 \
-    hipLaunchKernelGGL((k_add_gain<bf16_t, MS, false>), grid, dim3(256), 0, s, x, part, S, pstride, gain, (bf16_t*)out,\
+    hipLaunchKernelGGL((k_add_gain<bf16_t, MS, false>), grid, dim3(256), 0, s, x, part, S, S_dev, pstride, gain, (bf16_t*)out,\
                        (size_t)D.R64 * D.d, ssq, rm, D.d)
   CERB_S_BUCKET(S, CERB_CALL);
 #undef CERB_CALL

@@ -108,10 +108,12 @@ def test_long_prompts_run_several_pieces_per_pass(dtype, attn_mfma, n_prompt, L0
     pair.engine.close()
 
 
-@pytest.mark.parametrize("one_token", [(), (0, 2, 3, 5, 6, 7, 9, 10, 12, 13, 15)])
+@pytest.mark.parametrize("one_token", [(), (0, 2, 3, 5, 6, 7, 9, 10, 12, 13, 15), tuple(range(16)), tuple(range(1, 16)),
+                                       tuple(range(15)), (0, 1, 2, 4, 5, 6, 7, 9, 10, 11, 13, 14, 15)])
 def test_down_projection_of_a_large_batch(one_token):
-    """16 sequences of a 192-node tree at d = 1024: the down projection runs on the team kernel (two column blocks, ten
-    teams), with all 3072 rows and with 971 of them.  One workgroup per (item, head) of sequences of many lengths in
+    """16 sequences of a 192-node tree at d = 1024: the down projection runs on the team kernel (two column blocks, from 10 teams
+    at the bound to 16 with few rows), with all 3072 rows, with 971, 589 and 207 of them and with 16, where every sequence
+    brings one; the consumer sums as many planes as the launch took.  One workgroup per (item, head) of sequences of many lengths in
     attention.  Every row of every sequence against the oracle; the bars are those of the 7B shape, whose sums are longer."""
     print(f"down projection, one-token sequences {one_token}", flush=True)
     pair = H.Pair("tiny", B.CERBERUS_BF16, "bfs4x192", seed=4, max_batch=16, kv_capacity=512, d_model=1024, n_heads=8, head_dim=128, d_ffn=1000)
