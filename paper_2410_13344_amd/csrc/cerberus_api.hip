@@ -101,13 +101,17 @@ namespace {
 
 // The prompt phase.  Pieces of CERBERUS_MAX_TREE tokens are the unit of committing and of the output taps; a pass takes up
 // to six of them through the layers at once, so that a prompt of up to 1152 tokens streams the weights once (1024 tokens
-// in passes of 192: 49.2 ms, in one pass: 32.0 ms).  Six: at about a thousand rows the GEMMs are bound by the matrix
+// in passes of 192: 49.2 ms, in one pass: 30.8 ms).  Six: at about a thousand rows the GEMMs are bound by the matrix
 // cores and a pass costs in proportion to its rows.  Prompts of up to two pieces run a piece per pass.
 // Attention treats a piece as a sequence of its own: it reads the rows of earlier pieces from the bf16 cache, in the same
-// pass as in a later one, so the cut into passes changes no operand.  It does change the order of sums, though, and a
-// different last bit flips the bf16 rounding of some cached rows, which a random-init stack amplifies: heads' logits of a
-// 230-token prompt are off by 1.6e-2 with a piece per pass and by 3.2e-2 in one pass, past the 2e-2 that short prompts
-// are held to.
+// pass as in a later one, so the cut into passes changes no operand, only the order of sums.  One order matters: K and V
+// go into the cache rounded to bf16, where an error of the sum before it moves an element by a whole step now and then, and
+// the error of a plane of the QKV projection grows with the length of its sum.  A pass of 192 rows cuts K in three; over 1024
+// rows the same GEMM has work enough without, and with sums over three quarters of K the cache rows and logits of a
+// 1024-token prompt were 4 and 11 % further from float64 (2-norm) than piece by piece, heads' logits of 230 tokens twice as far.
+// So a pass of several pieces sums its QKV planes over no longer ranges than a pass of one piece: 1.07e-3 against 1.08e-3 on
+// the cache rows of 1024 tokens, at a cost of 1.1 of 30.8 ms for the larger planes.  The length of the other projections' sums
+// made no difference.
 constexpr int kPromptPiece = CERBERUS_MAX_TREE, kPromptPieces = 6, kPromptSplit = 2 * kPromptPiece;
 
 constexpr int kFusedMaxGrid = 512, kFusedMaxNs = 6;
@@ -335,8 +339,9 @@ int choose_split(const cerberus_ctx* c, int total_tiles, int chunks, int rows_ma
   return best;
 }
 
-// (Re)computes split, tile numbering and partial buffers of a plan for a launch of up to rows_max rows.
-void split_plan(const cerberus_ctx* c, GemmBatch& g, int rows_max) {
+// (Re)computes split, tile numbering and partial buffers of a plan for a launch of up to rows_max rows; at least min_split
+// splits per problem.
+void split_plan(const cerberus_ctx* c, GemmBatch& g, int rows_max, int min_split = 1) {
   const int cols = gemm_cols_per_wg(c->cfg.dtype, g.nsub);
   int total_tiles = 0;
   for (int p = 0; p < g.n_prob; ++p) total_tiles += ceil_div(g.p[p].N, cols);
@@ -351,7 +356,7 @@ void split_plan(const cerberus_ctx* c, GemmBatch& g, int rows_max) {
       // planes, 8 with one (K is padded to 256, so either divides it)
       const int unit = g.split ? 4 : 8;
       const int chunks = P.K / (32 * unit);
-      const int S = g.fixed_s1 ? 1 : choose_split(c, total_tiles, chunks, rows_max);
+      const int S = g.fixed_s1 ? 1 : std::min(chunks, std::max(min_split, choose_split(c, total_tiles, chunks, rows_max)));
       P.S = S;                              // S <= chunks
       P.kps = (chunks / S) * unit;          // as even as whole chunks allow: the first chunks % S splits take one more
       P.rem = chunks % S;
@@ -470,10 +475,20 @@ int check_state(const cerberus_ctx* c, const cerberus_state* st, int batch) {
   return CERBERUS_OK;
 }
 
+// In how many ranges of K a pass of one prompt piece sums the problem
+int piece_split(const cerberus_ctx* c, const GemmBatch& plan) {
+  if (c->cfg.dtype == CERBERUS_F32) return 1;
+  GemmBatch g = plan;
+  g.nsub = c->gemm_nsub_rows ? c->gemm_nsub_rows : 2;
+  split_plan(c, g, kPromptPiece);
+  return g.p[0].S;
+}
+
 // Launches a planned GEMM over up to rows_max rows and returns the first problem as launched (its
-// split count and partial buffer are what the consumer of the partials needs).
+// split count and partial buffer are what the consumer of the partials needs).  min_split: K is summed in at least as many
+// ranges (launches of more than 64 rows).
 int run_gemm(const cerberus_ctx* c, const GemmBatch& plan, const int* n_rows, int rows_static, int rows_max,
-             const int* skip_flags, int n_skip, hipStream_t s, GemmProb* launched = nullptr) {
+             const int* skip_flags, int n_skip, hipStream_t s, GemmProb* launched = nullptr, int min_split = 1) {
   GemmBatch g = plan;
   // Above 128 rows the problems the planner marked (wide weights: gate/up, QKV, the LM head, in the order of what
   // they gain; the knob says how far down that list to go) run on the team kernel, which streams the weights once
@@ -485,9 +500,10 @@ int run_gemm(const cerberus_ctx* c, const GemmBatch& plan, const int* n_rows, in
   // teams and planes follow the live rows (see plan_team_gemm).  The O projection, with a third of the K for the same
   // planes, stays on the 64-row blocks (69 us + planes against 80).
   TeamPlan tp;
+  const int k_chain = min_split > 1 ? ceil_div(g.p[0].K / 128, min_split) * 128 : 0;   // as long as the longest of min_split ranges
   if (launched && plan.team_rows && c->gemm_team >= plan.team_rows && rows_max > plan.team_above && c->cfg.dtype == CERBERUS_BF16 && g.split && g.n_prob == 1 && !skip_flags &&
       c->fused_grid >= 8 && g.p[0].lda >= g.p[0].K &&   // (the kernel reads whole padded rows)
-      plan_team_gemm(rows_max, g.p[0].N, g.p[0].K, c->fused_grid, c->max_split, plan.team_live != 0, &tp) &&
+      plan_team_gemm(rows_max, g.p[0].N, g.p[0].K, c->fused_grid, c->max_split, plan.team_live != 0, k_chain, &tp) &&
       (size_t)tp.planes * align_up((size_t)rows_max, 64) * g.p[0].N <= c->part_floats) {
     GemmProb& P = g.p[0];
     P.out_rows = (int)align_up((size_t)rows_max, 64);
@@ -496,7 +512,7 @@ int run_gemm(const cerberus_ctx* c, const GemmBatch& plan, const int* n_rows, in
     TeamGemmArgs ta{};
     ta.W = reinterpret_cast<const uint4*>(P.W); ta.A = reinterpret_cast<const bf16_t*>(P.A); ta.lo_off = P.lo_off; ta.lda = P.lda;
     ta.out = P.out; ta.out_rows = P.out_rows; ta.N = P.N; ta.ksteps = P.K / 32;
-    ta.n_rows = n_rows; ta.rows_static = rows_static; ta.rows_cap = rows_max; ta.rb_min = tp.rb_min; ta.t_max = tp.t_max; ta.P = tp.planes;
+    ta.n_rows = n_rows; ta.rows_static = rows_static; ta.rows_cap = rows_max; ta.rb_min = tp.rb_min; ta.t_max = tp.t_max; ta.chain = tp.chain; ta.P = tp.planes;
     if (plan.team_live) {
       P.S_dev = ta.planes_out = c->down_planes;
       std::memcpy(ta.planes_of, tp.planes_of, sizeof ta.planes_of);
@@ -513,7 +529,7 @@ int run_gemm(const cerberus_ctx* c, const GemmBatch& plan, const int* n_rows, in
     // (long K against few columns, or the vocabulary-wide LM head); the knob forces either one.
     if (rows_max > 64) g.nsub = c->gemm_nsub_rows ? c->gemm_nsub_rows : (rows_max > 256 && plan.wide_rows) ? 4 : 2;
     for (int p = 0; p < g.n_prob; ++p) g.p[p].out_rows = (int)align_up((size_t)rows_max, 64);   // partials packed for this launch
-    split_plan(c, g, rows_max);
+    split_plan(c, g, rows_max, min_split);
   }
   if (launched) *launched = g.p[0];
   g.n_rows = n_rows;
@@ -569,6 +585,8 @@ int forward_rows(cerberus_ctx* c, const cerberus_state* st, int rows_max, const 
   // launches of up to 64 rows: QKV + RoPE + KV write and gate/up + SwiGLU as one whole-K launch each
   const bool fused = c->use_fused && D.dtype == CERBERUS_BF16 && rows_max <= 64 && c->fused_grid > 0 && c->act_split == 1;
   const bool fq = fused && c->ns_qkv > 0, fg = fused && c->ns_gu > 0;
+  // QKV of a prompt pass of several pieces (see kPromptPieces)
+  const int qkv_split = sh.piece && rows_max > kPromptPiece ? piece_split(c, c->p_qkv[0]) : 1;
   for (int l = 0; l < D.n_layers; ++l) {
     HIP_TRY(launch_add_gain(D, rm, c->x, prev ? prev->out : nullptr, prev ? prev->S : 0, prev ? prev->S_dev : nullptr,
                             prev ? (size_t)prev->out_rows * prev->N : 0, c->attn_norm[l], c->xn, c->ssq, rows_max, s, fq));
@@ -577,7 +595,7 @@ int forward_rows(cerberus_ctx* c, const cerberus_state* st, int rows_max, const 
     if (fq) {
       TRY(run_fused_qkv(c, l, kv_layer, s));
     } else {
-      TRY(run_gemm(c, c->p_qkv[l], rm.n_rows, 0, rows_max, nullptr, 0, s, &pq));
+      TRY(run_gemm(c, c->p_qkv[l], rm.n_rows, 0, rows_max, nullptr, 0, s, &pq, qkv_split));
       HIP_TRY(launch_rope_kv(D, rm, pq.out, pq.S, (size_t)pq.out_rows * pq.N, c->rope_cs, c->q, kv_layer, c->ktree, c->vtree,
                              c->ssq, rows_max, s));
     }
@@ -950,7 +968,7 @@ int cerberus_bench_gemm(cerberus_ctx* ctx, int32_t kind, int32_t rows, void* str
     TeamPlan tp;   // (2 + NT: the team kernel with NT row tiles per workgroup)
     const GemmBatch* g = kind == 100 ? &ctx->p_qkv[0] : kind == 102 ? &ctx->p_gu[0] : kind == 103 ? &ctx->p_down[0] : kind == 104 ? &ctx->p_lm : nullptr;
     const bool team = g && g->team_rows && ctx->gemm_team >= g->team_rows && rows > g->team_above && D.dtype == CERBERUS_BF16 && ctx->act_split == 1 &&
-                      ctx->fused_grid >= 8 && plan_team_gemm(rows, g->p[0].N, g->p[0].K, ctx->fused_grid, ctx->max_split, g->team_live != 0, &tp);
+                      ctx->fused_grid >= 8 && plan_team_gemm(rows, g->p[0].N, g->p[0].K, ctx->fused_grid, ctx->max_split, g->team_live != 0, 0, &tp);
     if (bytes) *bytes = f ? 1.0 : team ? 2.0 + tp.NT : 0.0;
     return CERBERUS_OK;
   }

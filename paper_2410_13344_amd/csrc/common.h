@@ -150,6 +150,7 @@ struct TeamGemmArgs {
   int rows_cap;          // upper bound of the row count the plan was made for
   int rb_min;            // least number of row blocks (>= 2)
   int t_max;             // most teams
+  int chain;             // most stages that a plane's sum runs over (0: no limit)
   int P;                 // partial planes the consumer sums (an upper bound of what any row count needs)
   int* planes_out;       // if set: the consumer sums planes_of(row blocks) planes instead, a number that is left here
   unsigned long long planes_of[2];
@@ -157,11 +158,13 @@ struct TeamGemmArgs {
 struct TeamPlan {
   int NT, planes, grid;    // row tiles per workgroup, partial planes (the most that any row count takes), workgroups
   int rb_min, t_max;       // least number of row blocks the device may form, most teams
+  int chain;               // most stages per sum (0: no limit)
   unsigned long long planes_of[2];   // of a plan with `live`, partial planes by row blocks: 4 bits each, one less than the planes
   int RB, rows_per, T;     // row blocks, rows per block and teams if the launch has as many rows as the plan allows
 };
 // live: few rows of a large bound are dealt to more teams and planes than the bound's own shape has
-bool plan_team_gemm(int rows_max, int N, int Kpad, int cus, int max_planes, bool live, TeamPlan* tp);
+// k_chain: no partial plane sums over more than this many columns of K (0: no limit)
+bool plan_team_gemm(int rows_max, int N, int Kpad, int cus, int max_planes, bool live, int k_chain, TeamPlan* tp);
 hipError_t init_team_gemm();
 hipError_t launch_team_gemm(const TeamGemmArgs& a, const TeamPlan& tp, hipStream_t s);
 

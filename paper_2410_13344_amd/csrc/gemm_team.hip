@@ -12,7 +12,8 @@
 // XCD: the weights come from HBM once and from that L2 for the other row blocks) and every CU gets the same amount
 // of work whatever the shape.  A column block that several teams touch lands in several partial planes
 // out[p][row][col], p = the team's rank among the teams of that block; the team that finishes a block also clears
-// the planes above the last one written there, so a consumer sums `planes` planes everywhere.
+// the planes above the last one written there, so a consumer sums `planes` planes everywhere.  Where a launch limits the
+// length of a sum, a team's part of a block goes out in several planes, and p counts the planes before it.
 #include "common.h"
 
 #include <algorithm>
@@ -46,6 +47,15 @@ __device__ __forceinline__ const char* uniform_ptr(const char* p) {
   const unsigned long v = reinterpret_cast<unsigned long>(p);
   const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v), hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
   return reinterpret_cast<const char*>(((unsigned long)hi << 32) | lo);
+}
+
+// A team's `ov` stages of a column block in sums of at most `chain` stages: the stages of a sum (the last one may be
+// shorter) and how many sums there are.
+struct TeamSums { int stages, n; };
+__host__ __device__ __forceinline__ TeamSums team_sums(int ov, int chain) {
+  if (chain <= 0 || ov <= chain) return TeamSums{ov, 1};
+  const int n = (ov + chain - 1) / chain, stages = (ov + n - 1) / n;
+  return TeamSums{stages, (ov + stages - 1) / stages};
 }
 
 template <int NT>
@@ -86,7 +96,14 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
   int cb = v0 / nst, st = v0 - cb * nst;   // the unit being multiplied
   // rank of this team among the teams of its first column block; any later block starts inside this team's range
-  int plane = team - ((int)((((long long)cb * nst + 1) * T + V - 1) / V) - 1);
+  const int first = (int)((((long long)cb * nst + 1) * T + V - 1) / V) - 1;
+  int plane = team - first;
+  if (a.chain > 0) {                       // ... of the sums of those teams
+    plane = 0;
+    for (int t = first; t < team; ++t)
+      plane += team_sums((int)(V * (t + 1) / T) - max((int)(V * t / T), cb * nst), a.chain).n;
+  }
+  int sum_stages = team_sums(min(len, nst - st), a.chain).stages, left = sum_stages;   // of the block's sums; to the end of this one
 
   // ---- activations: fragment f = q * 8 + wave of a stage: row tile f >> 2, plane (f >> 1) & 1, k-step f & 1
   const unsigned lds_base = (unsigned)(unsigned long)((__attribute__((address_space(3))) const unsigned char*)team_lds);
@@ -175,8 +192,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       team_wwait<N_W1>(Wr[(u * 2 + 1) % kRW]);
       TEAM_KSTEP((u * 2 + 1) % kRW, sbuf + NT * 2 * 64)
       const bool tile_end = st == nst - 1;
-      if (tile_end || n == len - 1) {
-        // ---- this team's part of column block cb is complete: it goes to plane `plane`.  A lane holds rows
+      if (--left == 0 || tile_end || n == len - 1) {
+        // ---- a sum of this team's part of column block cb is complete: it goes to plane `plane`.  A lane holds rows
         // i*16 + (ln >> 4)*4 + v, column ln & 15 of slab j.
         int ln = lane;
         asm volatile("" : "+v"(ln));                                 // (keeps the address arithmetic inside this branch)
@@ -211,7 +228,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         for (int i = 0; i < NT; ++i)
 #pragma unroll
           for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        plane = 0;
+        plane = tile_end ? 0 : plane + 1;
+        if (tile_end) sum_stages = team_sums(min(len - n - 1, nst), a.chain).stages;
+        left = sum_stages;
       }
       if (tile_end) { st = 0; ++cb; } else { ++st; }
     }
@@ -241,7 +260,7 @@ hipError_t launch_nt(const TeamGemmArgs& a, int grid, hipStream_t s) {
 
 // The shape a launch takes for `rows` rows with NT row tiles per workgroup on `cus` workgroups (the kernel forms the
 // same on the device): row blocks, rows per block, teams, partial planes.
-static void team_shape(int rows, int NT, int rb_min, int t_max, int N, int Kpad, int cus, int* RB, int* rows_per, int* T, int* planes) {
+static void team_shape(int rows, int NT, int rb_min, int t_max, int chain, int N, int Kpad, int cus, int* RB, int* rows_per, int* T, int* planes) {
   *RB = std::max(rb_min, (rows + NT * 16 - 1) / (NT * 16));
   *rows_per = ((rows + *RB - 1) / *RB + 15) / 16 * 16;
   const int nst = Kpad / 32 / kKC, CB = (N / 16 + kSPT - 1) / kSPT;
@@ -249,8 +268,13 @@ static void team_shape(int rows, int NT, int rb_min, int t_max, int N, int Kpad,
   *T = (int)std::min<long long>(std::min(cus / *RB, t_max), V);
   *planes = 1;
   if (*T < 1) return;
-  for (int c = 0; c < CB; ++c)
-    *planes = std::max(*planes, team_of((long long)c * nst + nst - 1, *T, V) - team_of((long long)c * nst, *T, V) + 1);
+  for (int c = 0; c < CB; ++c) {
+    const long long b0 = (long long)c * nst, b1 = b0 + nst;
+    int n = 0;
+    for (int t = team_of(b0, *T, V); t <= team_of(b1 - 1, *T, V); ++t)
+      n += team_sums((int)(std::min(b1, V * (t + 1) / *T) - std::max(b0, V * t / *T)), chain).n;
+    *planes = std::max(*planes, n);
+  }
 }
 
 // Plan for a launch of up to rows_max rows on `cus` compute units (a multiple of 8): the row tiles per workgroup and
@@ -265,16 +289,17 @@ static void team_shape(int rows, int NT, int rb_min, int t_max, int N, int Kpad,
 // 64-row blocks; teams of the bound's shape; with `live`): 16 live rows 45 / 65 / 41, 128: 58 / 67 / 46-49, 205: 62 / 72 /
 // 60-63, 256: 64 / 78 / 65-69, 323: 111 / 84 / 77, 512: 122 / 109 / 94, 768: 178 / 132 / 133, 1024: 198 / 157 / 157.  Three
 // or fewer row blocks would leave more than a quarter of the workgroups without work for the same planes (205 rows: 76).
-bool plan_team_gemm(int rows_max, int N, int Kpad, int cus, int max_planes, bool live, TeamPlan* tp) {
+bool plan_team_gemm(int rows_max, int N, int Kpad, int cus, int max_planes, bool live, int k_chain, TeamPlan* tp) {
   if (rows_max <= 128 || N % 16 != 0 || Kpad % (32 * kKC) != 0 || cus < 8 || cus % 8 != 0) return false;
   const int RBmax = (rows_max + 127) / 128;
   const int NT = (((rows_max + RBmax - 1) / RBmax) + 15) / 16;
   if (NT < 5 || NT > 8 || cus / RBmax < 1) return false;      // (NT < 5 cannot happen above 128 rows)
   int rb_min = std::max(2, RBmax - 1), t_max = cus;
+  const int chain = k_chain <= 0 ? 0 : std::max(1, k_chain / (32 * kKC));
   const int rb_hi = std::max(rb_min, (rows_max + NT * 16 - 1) / (NT * 16));
   auto planes_at = [&](int RB) {
     int rb, rp, T, pl;
-    team_shape(RB * NT * 16, NT, rb_min, t_max, N, Kpad, cus, &rb, &rp, &T, &pl);
+    team_shape(RB * NT * 16, NT, rb_min, t_max, chain, N, Kpad, cus, &rb, &rp, &T, &pl);
     return T < 1 ? max_planes + 1 : pl;
   };
   auto most_planes = [&]() {
@@ -292,9 +317,9 @@ bool plan_team_gemm(int rows_max, int N, int Kpad, int cus, int max_planes, bool
   } else if (live) {
     return false;
   }
-  tp->NT = NT; tp->planes = most_planes(); tp->grid = cus; tp->rb_min = rb_min; tp->t_max = t_max;
+  tp->NT = NT; tp->planes = most_planes(); tp->grid = cus; tp->rb_min = rb_min; tp->t_max = t_max; tp->chain = chain;
   int planes;
-  team_shape(rows_max, NT, rb_min, t_max, N, Kpad, cus, &tp->RB, &tp->rows_per, &tp->T, &planes);   // (the shape at the bound, for reference)
+  team_shape(rows_max, NT, rb_min, t_max, chain, N, Kpad, cus, &tp->RB, &tp->rows_per, &tp->T, &planes);   // (the shape at the bound, for reference)
   return true;
 }
 
