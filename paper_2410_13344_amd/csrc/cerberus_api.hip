@@ -102,17 +102,17 @@ namespace {
 // The prompt phase.  Pieces of CERBERUS_MAX_TREE tokens are the unit of committing and of the output taps; a pass takes up
 // to six of them through the layers at once, so that a prompt of up to 1152 tokens streams the weights once (1024 tokens
 // in passes of 192: 49.2 ms, in one pass: 30.8 ms).  Six: at about a thousand rows the GEMMs are bound by the matrix
-// cores and a pass costs in proportion to its rows.  Prompts of up to two pieces run a piece per pass.
+// cores and a pass costs in proportion to its rows.
 // Attention treats a piece as a sequence of its own: it reads the rows of earlier pieces from the bf16 cache, in the same
 // pass as in a later one, so the cut into passes changes no operand, only the order of sums.  One order matters: K and V
 // go into the cache rounded to bf16, where an error of the sum before it moves an element by a whole step now and then, and
 // the error of a plane of the QKV projection grows with the length of its sum.  A pass of 192 rows cuts K in three; over 1024
 // rows the same GEMM has work enough without, and with sums over three quarters of K the cache rows and logits of a
-// 1024-token prompt were 4 and 11 % further from float64 (2-norm) than piece by piece, heads' logits of 230 tokens twice as far.
+// 1024-token prompt were 4 and 11 % further from float64 (2-norm) than piece by piece, the heads' logits of a 230-token one twice as far.
 // So a pass of several pieces sums its QKV planes over no longer ranges than a pass of one piece: 1.07e-3 against 1.08e-3 on
 // the cache rows of 1024 tokens, at a cost of 1.1 of 30.8 ms for the larger planes.  The length of the other projections' sums
 // made no difference.
-constexpr int kPromptPiece = CERBERUS_MAX_TREE, kPromptPieces = 6, kPromptSplit = 2 * kPromptPiece;
+constexpr int kPromptPiece = CERBERUS_MAX_TREE, kPromptPieces = 6;
 
 constexpr int kFusedMaxGrid = 512, kFusedMaxNs = 6;
 constexpr int kFusedGrid = 256;          // one workgroup per compute unit of an MI355X; fixed, so that the workspace
@@ -704,7 +704,7 @@ int run_prompt(cerberus_ctx* c, const cerberus_state* st, int batch, int seq, co
   } restore{c->taps, c->taps};
   c->taps.forced_node_argmax = nullptr;
   c->taps.forced_gate_hidden = nullptr;
-  const int pass = n_tokens <= kPromptSplit ? kPromptPiece : c->prompt_rows;
+  const int pass = c->prompt_rows;
   for (int off = 0; off < n_tokens; off += pass) {
     const int n = std::min(pass, n_tokens - off);
     const bool last = off + n >= n_tokens;

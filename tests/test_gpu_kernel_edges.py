@@ -41,13 +41,13 @@ def test_fp32_kernels_at_the_edges_of_their_tiles(tree, n_prompt, over):
     pair.engine.close()
 
 
-@pytest.mark.parametrize("n_prompt,L0", [(385, 0), (420, 7), (576, 1), (700, 130), (1152, 0), (1153, 3)])
+@pytest.mark.parametrize("n_prompt,L0", [(193, 0), (256, 700), (384, 5), (385, 0), (420, 7), (576, 1), (700, 130), (1152, 0), (1153, 3)])
 @pytest.mark.parametrize("dtype,attn_mfma", [(B.CERBERUS_F32, 0), (B.CERBERUS_BF16, 1), (B.CERBERUS_BF16, 0)])
 def test_long_prompts_run_several_pieces_per_pass(dtype, attn_mfma, n_prompt, L0):
-    """A prompt of more than two pieces of 192 tokens goes through the layers in passes of up to six pieces: the cache
+    """A prompt of more than one piece of 192 tokens goes through the layers in passes of up to six pieces: the cache
     rows, the pending token, the gate, the heads and the tapped rows (the last piece's, from slot 0) against the same prompt
     handed over piece by piece (each call a pass of its own).  Then the same with a cache that has room for the first half
-    of the prompt and 24 rows: the pieces before the first one that does not fit are committed and nothing else, also where
+    of the prompt and 24 rows (at least a piece): the pieces before the first one that does not fit are committed and nothing else, also where
     the prompt's last piece would fit, in the same pass or in a later one.  The pieces' operands are the same either way and only
     sums change order: fp32 5e-5; bf16 within the bars of a prompt of two passes (a different last bit flips the bf16
     rounding of a cached row now and then)."""
@@ -77,7 +77,7 @@ def test_long_prompts_run_several_pieces_per_pass(dtype, attn_mfma, n_prompt, L0
         torch.cuda.synchronize()
         return st, taps, before
 
-    for start in (L0, 1280 - n_prompt // 2 - 24):
+    for start in (L0, 1280 - min(n_prompt - 1, max(P, n_prompt // 2 + 24))):
         fit = n_prompt if start + n_prompt <= 1280 else (1280 - start) // P * P     # rows of the pieces that fit
         got, gt, before = run(start, n_prompt, None)
         want, wt, _ = run(start, fit, P)
@@ -110,12 +110,12 @@ def test_long_prompts_run_several_pieces_per_pass(dtype, attn_mfma, n_prompt, L0
 
 
 @pytest.mark.parametrize("team", [3, 0])
-@pytest.mark.parametrize("n_prompt", [385, 640, 1024, 1152])
+@pytest.mark.parametrize("n_prompt", [193, 256, 384, 385, 640, 1024, 1152])
 def test_cache_rows_of_a_long_prompt_are_as_close_to_the_oracle_as_piece_by_piece(n_prompt, team):
     """One layer of the 7B width (K = 4096): the cache rows are the QKV projection of the embeddings, whose products are exact
     in the hi and lo planes, so an element differs from the rounded oracle where the error of its fp32 sum crosses a
     rounding boundary, in proportion to that error.  In a pass of several pieces there are to be no more of them than where
-    every piece runs on its own: 1053 to 3269 of 3 to 9 million, whose independent draws differ by 2.5 to 4.4 % (one standard
+    every piece runs on its own: 500 to 3269 of 1.6 to 9 million, whose independent draws differ by 2.5 to 6 % (one standard
     deviation); bar 10 %.  Planes that sum over three quarters of K have 17 % more, over all of K 27 %."""
     print(f"prompt of {n_prompt}, gemm_team {team}", flush=True)
     pair = H.Pair("7b", B.CERBERUS_BF16, "root", seed=3, kv_capacity=1152, n_layers=1, d_ffn=256, vocab=1024, n_cerb_heads=1, special_block=-1)
@@ -137,7 +137,7 @@ def test_cache_rows_of_a_long_prompt_are_as_close_to_the_oracle_as_piece_by_piec
     pair.engine.close()
 
 
-@pytest.mark.parametrize("dtype,n_prompt", [(B.CERBERUS_F32, 700), (B.CERBERUS_BF16, 385), (B.CERBERUS_BF16, 700), (B.CERBERUS_BF16, 1153)])
+@pytest.mark.parametrize("dtype,n_prompt", [(B.CERBERUS_F32, 700), (B.CERBERUS_BF16, 230), (B.CERBERUS_BF16, 384), (B.CERBERUS_BF16, 700), (B.CERBERUS_BF16, 1153)])
 def test_long_prompts_match_the_oracle(dtype, n_prompt):
     """Six layers of width 1024, passes of several pieces against the oracle's causal forward over pieces of 192 tokens, its
     cache rounded to the storage type between them: every cache row, the tapped rows, entropy, the heads' logits, the

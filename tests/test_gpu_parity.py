@@ -305,8 +305,8 @@ def test_generate_from_prompts_equals_greedy_decoding(dtype):
 @pytest.mark.parametrize("n_prompt", [100, 230])
 @pytest.mark.parametrize("dtype", [F32, BF16])
 def test_prefill_seeds_the_first_step(tiny_pairs, dtype, n_prompt):
-    """Algorithm 1 lines 1-5: the prompt's causal forward from an empty cache, in passes of up to 192
-    rows (100 tokens: one pass; 230: a full pass and one of 38), then LM head, gate and heads on the last position.
+    """Algorithm 1 lines 1-5: the prompt's causal forward from an empty cache, in pieces of up to 192
+    rows (100 tokens: one piece; 230: a full piece and one of 38), then LM head, gate and heads on the last position.
     Compared with the oracle's one-shot causal prefill: every K/V row, the logits of the last pass,
     the pending token, entropy and flag, the candidates; then one decoding step taken from the seeded
     state on both sides."""
@@ -1112,7 +1112,7 @@ def test_7b_decode_two_chained_steps_match_oracle(pair_7b):
 
 
 def test_7b_prefill_two_passes_matches_oracle(pair_7b):
-    """cerberus_prefill at the 7B shape: 230 prompt tokens from an empty cache (a pass of 192 rows and
+    """cerberus_prefill at the 7B shape: 230 prompt tokens from an empty cache (a piece of 192 rows and
     one of 38), against the oracle's one-shot causal prefill: cache rows, the last pass's logits and
     hidden states, pending token, gate, the heads' logits and candidates."""
     pair = pair_7b
@@ -1125,8 +1125,8 @@ def test_7b_prefill_two_passes_matches_oracle(pair_7b):
     pair.engine.prefill(st, 1, 0, prompt.cuda())
     torch.cuda.synchronize()
     assert int(st.status[0]) == 0 and int(st.kv_len[0]) == n_prompt
-    # The oracle takes the same two passes, its cache rounded to bf16 between them: the device's
-    # second pass reads the first pass's rows from the bf16 cache, and the storage type of the cache
+    # The oracle takes the two pieces one after the other, its cache rounded to bf16 between them: the device's
+    # second piece reads the first one's rows from the bf16 cache, and the storage type of the cache
     # is part of the configuration, not an error of the path (that passes and a one-shot forward
     # agree is pinned on the oracle itself).
     say("7B prefill: device done; oracle's causal forward over 192 + 38 rows")
