@@ -129,7 +129,9 @@ typedef struct {
   const float *forced_gate_hidden;   /* in [batch][d]: replaces the gate's input vector      */
 } cerberus_taps;
 
-/* Bytes of DEVICE workspace cerberus_init needs for this config and tree (0 on bad input).    */
+/* Bytes of DEVICE workspace cerberus_init needs for this config and tree (0 on bad input): in bf16 mode mostly the repacked
+ * weights, then the buffers of the larger of a step of max_batch whole trees and a prompt pass of up to 1152 rows (no more than
+ * kv_capacity holds, in pieces of CERBERUS_MAX_TREE; 0.2 GB over those of one piece for a 32-layer model of width 4096).  */
 size_t cerberus_workspace_bytes(const cerberus_config *cfg, const cerberus_tree *tree);
 
 /* Validates everything, copies the tree tables, repacks the weight matrices into `workspace`

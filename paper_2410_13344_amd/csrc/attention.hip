@@ -162,7 +162,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     if (e.x < 0) break;                               // end of the list (uniform)
     const int b = e.x >> 16, j = e.x & 0xffff;
     const int L = e.y, Tb = e.z >> 16, row0 = e.z & 0xffff;
-    const int npi = e.w >> 16, cps = e.w & 0xffff;
+    const int npi = e.w >> 16, cps = e.w & 0xffff, slot0 = a.rm.seq_items[b].x;
     if (qb * 64 >= Tb) continue;                      // uniform over the workgroup
     // Items npi.. of a sequence are its tree chunks.  Under a chain's mask (a prompt pass) a chunk after the query block's
     // own is seen by nobody and has no partial (k_attn_combine knows).
@@ -358,7 +358,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     }
 
     if (wave_live && qvalid) {
-      const size_t slot = (((size_t)b * a.nH + h) * a.n_items_max + j) * a.Tpad + qnode;
+      const size_t slot = ((size_t)h * a.grid_x + slot0 + j) * a.Tpad + qnode;
       float* po = a.part_o + slot * DH;
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
@@ -390,8 +390,9 @@ __global__ __launch_bounds__(128) void k_attn_combine(const AttnArgs a) {
   } else {
     chunks = (a.rm.seq_T[b] + 63) / 64;
   }
-  const int nch = a.rm.seq_npi[b] + chunks;   // the sequence's cache-range items + tree chunks
-  const size_t base = (((size_t)b * a.nH + h) * a.n_items_max) * a.Tpad + node;
+  const int2 it = a.rm.seq_items[b];
+  const int nch = it.y + chunks;   // the sequence's cache-range items + tree chunks
+  const size_t base = ((size_t)h * a.grid_x + it.x) * a.Tpad + node;
   constexpr int NB = 8;
   float M = -INFINITY, den = 0.f, num[4] = {0.f, 0.f, 0.f, 0.f};
   for (int c0 = 0; c0 < nch; c0 += NB) {
@@ -436,8 +437,7 @@ hipError_t launch_attention(const AttnArgs& a, int dtype, int use_mfma, hipStrea
     return hipGetLastError();
   }
   if (a.chunk != 128 && a.chunk != 256) return hipErrorInvalidValue;
-  if (a.n_items_max != (a.cap + a.chunk - 1) / a.chunk + a.tc_max) return hipErrorInvalidValue;
-  if (a.rm.att_item == nullptr || a.grid_x <= 0 || a.grid_x > a.att_cap) return hipErrorInvalidValue;
+  if (a.rm.att_item == nullptr || a.grid_x <= 0 || a.grid_x > a.att_cap || (size_t)a.grid_x * a.Tpad > a.part_rows) return hipErrorInvalidValue;
   // Heads vary fastest, items slowest.  Consecutive workgroup ids go to the 8 XCDs in turn: with the items fastest and
   // their number a multiple of 8, an item ran on one XCD for every head, and the XCDs with the long items finished last
   // (half of the places stood empty over the launch).  This way every XCD gets each item for an eighth of the heads, long

@@ -81,8 +81,9 @@ struct cerberus_ctx {
   std::vector<const void*> wqkv, wo, wgu, wdown, res_w, head_fc;
   const void* lm_head = nullptr;
 
-  size_t part_floats = 0;
-  int att_cap = 0, R64 = 0, prompt_rows = 0;
+  size_t part_floats = 0;  // of `part`
+  size_t att_rows = 0;     // attention partials: rows per head
+  int att_cap = 0, R64 = 0, prompt_rows = 0, lm_rows = 0;
   cerberus_taps taps{};
   int use_mfma_attn = 1, target_wgs = 768, max_split = 8, gemm_nsub = 2, gemm_nsub_rows = 0, gemm_team = 3, act_split = 1, attn_chunk = 128, attn_target_wgs = 1024, uneven_split = 0, wg_slots = 512;
   std::vector<GemmBatch> p_qkv, p_o, p_gu, p_down, p_res;
@@ -187,15 +188,26 @@ void fill_dims(cerberus_ctx* c, const cerberus_config* cfg, const cerberus_tree*
   D.sb = cfg->special_block; D.dtype = cfg->dtype; D.Bmax = cfg->max_batch; D.cap = cfg->kv_capacity;
   D.topk = cfg->topk; D.T = t->n_nodes; D.eps = cfg->rms_eps; D.threshold = cfg->entropy_threshold;
   c->elem = cfg->dtype == CERBERUS_F32 ? 4 : 2;
-  // A prompt pass is a chain of up to prompt_rows rows of one sequence, whatever the tree's size: room
-  // for it in the row buffers, the row map and the attention partials.
-  c->prompt_rows = kPromptPiece * kPromptPieces;
+  c->fused_grid = cfg->dtype == CERBERUS_BF16 ? kFusedGrid : 0;
+  // A prompt pass is a chain of up to prompt_rows rows of one sequence, whatever the tree's size (but no more pieces than the
+  // cache has room for): room for it in the row buffers, the row map and the partials; the rows of its last piece alone
+  // go on to the final norm and the LM head.
+  c->prompt_rows = kPromptPiece * std::min(kPromptPieces, ceil_div(cfg->kv_capacity, kPromptPiece));
+  c->lm_rows = (int)align_up((size_t)std::max(cfg->max_batch * t->n_nodes, kPromptPiece), 64);
   c->R64 = (int)align_up((size_t)std::max(cfg->max_batch * t->n_nodes, c->prompt_rows), 64);
   D.R64 = c->R64;
   c->att_cap = std::max((int)cfg->max_batch, kPromptPieces) * (ceil_div(cfg->kv_capacity, 128) + ceil_div(CERBERUS_MAX_TREE, 64));  // committed-row chunks + tree chunks
 }
 
 int fused_tables(const Dims& D, int grid, std::vector<int>& qkv, int& ns_qkv, std::vector<int>& gu, int& ns_gu);
+size_t prompt_part_floats(const cerberus_ctx* c);
+
+// Most items of the attention work list per head: cache ranges (of a whole cache in chunks of 128, or what the workgroup
+// target leaves of them: at most target / nH of all sequences together plus one per sequence from rounding) and tree chunks.
+int att_items(const Dims& D, int sequences, int rows, int chunk, int per_head) {
+  const int tc = ceil_div(rows, 64);
+  return std::min(sequences * (ceil_div(D.cap, chunk) + tc), per_head + sequences * (1 + tc));
+}
 
 // Assigns every workspace pointer of the context; with base == nullptr it only measures.
 size_t layout(cerberus_ctx* c, unsigned char* base) {
@@ -226,7 +238,7 @@ size_t layout(cerberus_ctx* c, unsigned char* base) {
   c->rm.row_pos = b.take<int>(Rmax);
   c->rm.row_tok = b.take<int>(Rmax);
   c->rm.att_item = b.take<int4>((size_t)c->att_cap);
-  c->rm.seq_npi = b.take<int>(std::max(B, kPromptPieces));
+  c->rm.seq_items = b.take<int2>(std::max(B, kPromptPieces));
   c->rm.tail = b.take<int>(3);
   c->last_row = b.take<int>(B);
   c->path = b.take<int>((size_t)B * (D.Hc + 1));
@@ -235,7 +247,7 @@ size_t layout(cerberus_ctx* c, unsigned char* base) {
   c->topk_i = b.take<int>((size_t)D.Hc * B * TOPK_MAX_PARTS * CERBERUS_MAX_TOPK);
   c->g = b.take<int>(Rmax);
   c->x = b.take<float>((size_t)R64 * d);
-  c->h_last = b.take<float>((size_t)R64 * d);
+  c->h_last = b.take<float>((size_t)c->lm_rows * d);
   c->ssq = b.take<float>((size_t)R64 * add_gain_blocks(d));
   const int planes = cfg.dtype == CERBERUS_BF16 ? 2 : 1;  // GEMM inputs: hi and lo plane in bf16 mode
   c->xn = b.take<unsigned char>((size_t)planes * R64 * d * el);
@@ -249,11 +261,16 @@ size_t layout(cerberus_ctx* c, unsigned char* base) {
   }
   c->act = b.take<unsigned char>((size_t)planes * R64 * D.Fpad * el);
   const size_t nmax = (size_t)std::max(std::max(3 * d, 2 * D.F), D.V);
-  c->part_floats = 16 * std::max((size_t)R64 * nmax, (size_t)16 * D.Hc * std::max((size_t)2 * d, (size_t)D.V));
+  // any split of a tree step or of the LM head; prompt passes of several pieces, as long as the shapes need (launches that
+  // want more under other tuning are held to it: see split_plan, run_gemm); the heads
+  c->part_floats = std::max(std::max((size_t)16 * c->lm_rows * nmax, (size_t)256 * D.Hc * std::max((size_t)2 * d, (size_t)D.V)), prompt_part_floats(c));
   c->part = b.take<float>(c->part_floats);
-  // attention partials: a tree step of the whole batch, or a prompt pass of one sequence
-  const int cc = ceil_div(D.cap, 128), Tp = (int)align_up(D.T, 64), Pp = (int)align_up(kPromptPiece, 64);
-  const size_t slots = (size_t)D.nH * std::max((size_t)B * (cc + Tp / 64) * Tp, (size_t)kPromptPieces * (cc + Pp / 64) * Pp);
+  // attention partials (the plain kernel of fp32 mode has none): a tree step of the whole batch, or a prompt pass of one
+  // sequence, at the default workgroup target (a larger one is cut back to what fits: see attn_per_head)
+  const int per_head = std::max(1, cerberus_ctx{}.attn_target_wgs / D.nH), pieces = c->prompt_rows / kPromptPiece;
+  c->att_rows = std::max(align_up(D.T, 64) * att_items(D, B, D.T, 128, per_head),
+                         align_up(kPromptPiece, 64) * att_items(D, pieces, kPromptPiece, 128, per_head));
+  const size_t slots = cfg.dtype == CERBERUS_BF16 ? D.nH * c->att_rows : 0;
   c->attn_po = b.take<float>(slots * D.dh);
   c->attn_ml = b.take<float>(slots * 2);
   for (int i = 0; i < 2; ++i) {
@@ -346,6 +363,7 @@ void split_plan(const cerberus_ctx* c, GemmBatch& g, int rows_max, int min_split
   int total_tiles = 0;
   for (int p = 0; p < g.n_prob; ++p) total_tiles += ceil_div(g.p[p].N, cols);
   float* out = c->part;
+  const size_t room = g.n_prob == 1 && c->part_floats ? c->part_floats / ((size_t)g.p[0].out_rows * g.p[0].N) : 16;   // planes that `part` has room for
   int wg = 0;
   for (int p = 0; p < g.n_prob; ++p) {
     GemmProb& P = g.p[p];
@@ -356,7 +374,7 @@ void split_plan(const cerberus_ctx* c, GemmBatch& g, int rows_max, int min_split
       // planes, 8 with one (K is padded to 256, so either divides it)
       const int unit = g.split ? 4 : 8;
       const int chunks = P.K / (32 * unit);
-      const int S = g.fixed_s1 ? 1 : std::min(chunks, std::max(min_split, choose_split(c, total_tiles, chunks, rows_max)));
+      const int S = g.fixed_s1 ? 1 : std::min(std::min(chunks, (int)std::min<size_t>(room, 16)), std::max(min_split, choose_split(c, total_tiles, chunks, rows_max)));
       P.S = S;                              // S <= chunks
       P.kps = (chunks / S) * unit;          // as even as whole chunks allow: the first chunks % S splits take one more
       P.rem = chunks % S;
@@ -433,15 +451,29 @@ int fused_tables(const Dims& D, int grid, std::vector<int>& qkv, int& ns_qkv, st
   return ns_qkv;
 }
 
+enum LayerGemm { GEMM_QKV, GEMM_O, GEMM_GATE_UP, GEMM_DOWN };
+GemmBatch layer_plan(const cerberus_ctx* c, LayerGemm kind, const void* W) {
+  const Dims& D = c->D;
+  const void* A = kind == GEMM_O ? c->attn : kind == GEMM_DOWN ? c->act : c->xn;
+  const int K = kind == GEMM_DOWN ? D.F : D.d, lda = kind == GEMM_DOWN ? D.Fpad : D.d;
+  const int N = kind == GEMM_QKV ? 3 * D.d : kind == GEMM_GATE_UP ? 2 * D.F : D.d;
+  GemmBatch g;
+  plan_gemm(c, g, 1, &A, &lda, (size_t)c->R64 * lda, &W, &N, &K, 64, false);
+  if (kind == GEMM_GATE_UP) { g.team_rows = 1; g.team_above = 128; }
+  if (kind == GEMM_QKV) { g.team_rows = 2; g.team_above = 256; }
+  if (kind == GEMM_DOWN) { g.wide_rows = 1; g.team_rows = 3; g.team_above = 768; g.team_live = 1; }
+  return g;
+}
+
 void build_plans(cerberus_ctx* c) {
   const Dims& D = c->D;
   const int d = D.d, L = D.n_layers;
   c->p_qkv.resize(L); c->p_o.resize(L); c->p_gu.resize(L); c->p_down.resize(L);
   for (int l = 0; l < L; ++l) {
-    { const void* A = c->xn; int lda = d, N = 3 * d, K = d; plan_gemm(c, c->p_qkv[l], 1, &A, &lda, (size_t)c->R64 * d, &c->wqkv[l], &N, &K, 64, false); c->p_qkv[l].team_rows = 2; c->p_qkv[l].team_above = 256; }
-    { const void* A = c->attn; int lda = d, N = d, K = d; plan_gemm(c, c->p_o[l], 1, &A, &lda, (size_t)c->R64 * d, &c->wo[l], &N, &K, 64, false); }
-    { const void* A = c->xn; int lda = d, N = 2 * D.F, K = d; plan_gemm(c, c->p_gu[l], 1, &A, &lda, (size_t)c->R64 * d, &c->wgu[l], &N, &K, 64, false); c->p_gu[l].team_rows = 1; c->p_gu[l].team_above = 128; }
-    { const void* A = c->act; int lda = D.Fpad, N = d, K = D.F; plan_gemm(c, c->p_down[l], 1, &A, &lda, (size_t)c->R64 * D.Fpad, &c->wdown[l], &N, &K, 64, false); c->p_down[l].wide_rows = 1; c->p_down[l].team_rows = 3; c->p_down[l].team_above = 768; c->p_down[l].team_live = 1; }
+    c->p_qkv[l] = layer_plan(c, GEMM_QKV, c->wqkv[l]);
+    c->p_o[l] = layer_plan(c, GEMM_O, c->wo[l]);
+    c->p_gu[l] = layer_plan(c, GEMM_GATE_UP, c->wgu[l]);
+    c->p_down[l] = layer_plan(c, GEMM_DOWN, c->wdown[l]);
   }
   { const void* A = c->xn; int lda = d, N = D.V, K = d; plan_gemm(c, c->p_lm, 1, &A, &lda, (size_t)c->R64 * d, &c->lm_head, &N, &K, 64, false); c->p_lm.wide_rows = 1; c->p_lm.team_rows = 3; c->p_lm.team_above = 256; }
   c->p_res.resize(D.R);
@@ -475,13 +507,59 @@ int check_state(const cerberus_ctx* c, const cerberus_state* st, int batch) {
   return CERBERUS_OK;
 }
 
+// several row blocks: 2 slabs per wave, or the 4-slab one-workgroup-per-CU instance.  Measured at the 7B
+// shapes: the 4-slab instance wins only past 256 rows and only where the planner marked the problem
+// (long K against few columns, or the vocabulary-wide LM head); the knob forces either one.
+int nsub_rows(const cerberus_ctx* c, const GemmBatch& g, int rows_max) {
+  return c->gemm_nsub_rows ? c->gemm_nsub_rows : (rows_max > 256 && g.wide_rows) ? 4 : 2;
+}
+
 // In how many ranges of K a pass of one prompt piece sums the problem
 int piece_split(const cerberus_ctx* c, const GemmBatch& plan) {
   if (c->cfg.dtype == CERBERUS_F32) return 1;
   GemmBatch g = plan;
-  g.nsub = c->gemm_nsub_rows ? c->gemm_nsub_rows : 2;
+  g.nsub = nsub_rows(c, plan, kPromptPiece);
   split_plan(c, g, kPromptPiece);
   return g.p[0].S;
+}
+
+// Above 128 rows the problems the planner marked (wide weights: gate/up, QKV, the LM head, in the order of what
+// they gain; the knob says how far down that list to go) run on the team kernel, which streams the weights once
+// per team of row blocks; its partial planes are the split of the launch.  QKV and the LM head change over
+// only past 256 rows: with two row blocks their extra planes cost what the kernel gains.  The down projection has
+// few columns, so few row blocks mean many teams and planes (8 planes at 640 rows, where the kernel gains nothing);
+// from seven row blocks on it takes 4 to 5 and wins: 162 us against 200 at 1024 rows of the 7B shape
+// (+ 7 us for the consumer of the planes).  How many of those rows are live the gate decides on the device, so its
+// teams and planes follow the live rows (see plan_team_gemm).  The O projection, with a third of the K for the same
+// planes, stays on the 64-row blocks (69 us + planes against 80).
+bool plan_team(const cerberus_ctx* c, const GemmBatch& g, int rows_max, int min_split, TeamPlan* tp) {
+  const int k_chain = min_split > 1 ? ceil_div(g.p[0].K / 128, min_split) * 128 : 0;   // as long as the longest of min_split ranges
+  return g.team_rows && c->gemm_team >= g.team_rows && rows_max > g.team_above && c->cfg.dtype == CERBERUS_BF16 && g.split && g.n_prob == 1 &&
+         c->fused_grid >= 8 && g.p[0].lda >= g.p[0].K &&   // (the kernel reads whole padded rows)
+         plan_team_gemm(rows_max, g.p[0].N, g.p[0].K, c->fused_grid, c->max_split, g.team_live != 0, k_chain, tp);
+}
+
+// Floats of partial planes that the layers of a prompt pass of several pieces want
+size_t prompt_part_floats(const cerberus_ctx* c) {
+  size_t most = 0;
+  for (LayerGemm kind : {GEMM_QKV, GEMM_O, GEMM_GATE_UP, GEMM_DOWN}) {
+    const GemmBatch plan = layer_plan(c, kind, nullptr);
+    const int min_split = kind == GEMM_QKV ? piece_split(c, plan) : 1;
+    for (int rows = kPromptPiece + 1; rows <= c->prompt_rows; rows += rows % 64 == 0 ? 1 : 63) {   // both ends of every 64-row block
+      GemmBatch g = plan;
+      TeamPlan tp;
+      int planes;
+      if (plan_team(c, plan, rows, min_split, &tp)) {
+        planes = tp.planes;
+      } else {
+        g.nsub = nsub_rows(c, plan, rows);
+        split_plan(c, g, rows, min_split);
+        planes = g.p[0].S;
+      }
+      most = std::max(most, (size_t)planes * align_up((size_t)rows, 64) * g.p[0].N);
+    }
+  }
+  return most;
 }
 
 // Launches a planned GEMM over up to rows_max rows and returns the first problem as launched (its
@@ -490,20 +568,8 @@ int piece_split(const cerberus_ctx* c, const GemmBatch& plan) {
 int run_gemm(const cerberus_ctx* c, const GemmBatch& plan, const int* n_rows, int rows_static, int rows_max,
              const int* skip_flags, int n_skip, hipStream_t s, GemmProb* launched = nullptr, int min_split = 1) {
   GemmBatch g = plan;
-  // Above 128 rows the problems the planner marked (wide weights: gate/up, QKV, the LM head, in the order of what
-  // they gain; the knob says how far down that list to go) run on the team kernel, which streams the weights once
-  // per team of row blocks; its partial planes are the split of the launch.  QKV and the LM head change over
-  // only past 256 rows: with two row blocks their extra planes cost what the kernel gains.  The down projection has
-  // few columns, so few row blocks mean many teams and planes (8 planes at 640 rows, where the kernel gains nothing);
-  // from seven row blocks on it takes 4 to 5 and wins: 162 us against 200 at 1024 rows of the 7B shape
-  // (+ 7 us for the consumer of the planes).  How many of those rows are live the gate decides on the device, so its
-  // teams and planes follow the live rows (see plan_team_gemm).  The O projection, with a third of the K for the same
-  // planes, stays on the 64-row blocks (69 us + planes against 80).
   TeamPlan tp;
-  const int k_chain = min_split > 1 ? ceil_div(g.p[0].K / 128, min_split) * 128 : 0;   // as long as the longest of min_split ranges
-  if (launched && plan.team_rows && c->gemm_team >= plan.team_rows && rows_max > plan.team_above && c->cfg.dtype == CERBERUS_BF16 && g.split && g.n_prob == 1 && !skip_flags &&
-      c->fused_grid >= 8 && g.p[0].lda >= g.p[0].K &&   // (the kernel reads whole padded rows)
-      plan_team_gemm(rows_max, g.p[0].N, g.p[0].K, c->fused_grid, c->max_split, plan.team_live != 0, k_chain, &tp) &&
+  if (launched && !skip_flags && plan_team(c, plan, rows_max, min_split, &tp) &&
       (size_t)tp.planes * align_up((size_t)rows_max, 64) * g.p[0].N <= c->part_floats) {
     GemmProb& P = g.p[0];
     P.out_rows = (int)align_up((size_t)rows_max, 64);
@@ -524,10 +590,7 @@ int run_gemm(const cerberus_ctx* c, const GemmBatch& plan, const int* n_rows, in
   // plans are made for 17..64 rows; other row counts run other kernel instances or several row
   // blocks and get their own split (only where the caller takes the launched description back)
   if (launched && (rows_max > 64 || rows_max <= 16)) {
-    // several row blocks: 2 slabs per wave, or the 4-slab one-workgroup-per-CU instance.  Measured at the 7B
-    // shapes: the 4-slab instance wins only past 256 rows and only where the planner marked the problem
-    // (long K against few columns, or the vocabulary-wide LM head); the knob forces either one.
-    if (rows_max > 64) g.nsub = c->gemm_nsub_rows ? c->gemm_nsub_rows : (rows_max > 256 && plan.wide_rows) ? 4 : 2;
+    if (rows_max > 64) g.nsub = nsub_rows(c, plan, rows_max);
     for (int p = 0; p < g.n_prob; ++p) g.p[p].out_rows = (int)align_up((size_t)rows_max, 64);   // partials packed for this launch
     split_plan(c, g, rows_max, min_split);
   }
@@ -571,6 +634,12 @@ int run_fused_gate_up(const cerberus_ctx* c, int l, hipStream_t s) {
 // sequence) and the sequence that owns the cache.
 struct AttnShape { int T, batch, piece, seq0; };
 
+// Cache-range items per head that a launch's work list aims at: the target's share, as far as the partials have room
+int attn_per_head(const cerberus_ctx* c, const AttnShape& sh) {
+  const int per_head = std::max(1, c->attn_target_wgs / c->D.nH), room = (int)(c->att_rows / align_up((size_t)sh.T, 64));
+  return att_items(c->D, sh.batch, sh.T, c->attn_chunk, per_head) <= room ? per_head : room - sh.batch * (1 + ceil_div(sh.T, 64));
+}
+
 // Embedding and the decoder layers over the rows the assembly kernel laid out; `tr` supplies the attention mask
 // (candidate tree, or a chain).  *pending: the GEMM whose partials are still to be added to x.
 int forward_rows(cerberus_ctx* c, const cerberus_state* st, int rows_max, const TreeDev& tr, const AttnShape& sh, GemmProb* pending,
@@ -603,11 +672,9 @@ int forward_rows(cerberus_ctx* c, const cerberus_state* st, int rows_max, const 
     aa.q = c->q; aa.q_lo_off = D.dtype == CERBERUS_BF16 ? (size_t)c->R64 * D.d : 0; aa.kv = kv_layer; aa.ktree = c->ktree; aa.vtree = c->vtree; aa.out = c->attn; aa.out_lo_off = (size_t)c->R64 * D.d; aa.part_o = c->attn_po; aa.part_ml = c->attn_ml; aa.rm = rm;
     aa.anc = tr.anc; aa.aw = tr.aw; aa.Tpad = (int)align_up((size_t)sh.T, 64); aa.tc_max = ceil_div(sh.T, 64); aa.piece = sh.piece; aa.seq0 = sh.seq0;
     aa.batch = sh.batch; aa.Bmax = D.Bmax; aa.nH = D.nH; aa.dh = D.dh; aa.cap = D.cap;
-    aa.chunk = c->attn_chunk; aa.n_items_max = ceil_div(D.cap, c->attn_chunk) + aa.tc_max;   // (layout sized the partial buffers for the smaller chunk)
-    // every item gets a workgroup per head: at most target / nH cache-range items plus one per sequence from
-    // rounding, and the tree chunks
+    aa.chunk = c->attn_chunk; aa.part_rows = c->att_rows;
     aa.att_cap = c->att_cap;
-    aa.grid_x = std::min(sh.batch * aa.n_items_max, std::max(1, c->attn_target_wgs / D.nH) + sh.batch * (1 + aa.tc_max));
+    aa.grid_x = att_items(D, sh.batch, sh.T, c->attn_chunk, attn_per_head(c, sh));   // every item gets a workgroup per head
     aa.rows_max = rows_max; aa.status = st->status;
     HIP_TRY(launch_attention(aa, D.dtype, c->use_mfma_attn, s));
     TRY(run_gemm(c, c->p_o[l], rm.n_rows, 0, rows_max, nullptr, 0, s, &po));
@@ -667,9 +734,9 @@ int run_heads(cerberus_ctx* c, const cerberus_state* st, int batch, hipStream_t 
 }
 
 // the attention work list is built only for the MFMA kernel; the plain one walks rows and heads
-AttnPlanCfg attn_plan_cfg(const cerberus_ctx* c) {
+AttnPlanCfg attn_plan_cfg(const cerberus_ctx* c, const AttnShape& sh) {
   const bool mfma = c->cfg.dtype == CERBERUS_BF16 && c->use_mfma_attn;
-  return AttnPlanCfg{mfma ? c->attn_chunk : 0, c->attn_target_wgs, c->att_cap};
+  return AttnPlanCfg{mfma ? c->attn_chunk : 0, attn_per_head(c, sh), c->att_cap};
 }
 
 int run_step(cerberus_ctx* c, const cerberus_state* st, int batch, void* stream, int mode) {
@@ -680,7 +747,7 @@ int run_step(cerberus_ctx* c, const cerberus_state* st, int batch, void* stream,
   const int rows_max = (mode == ASSEMBLE_FORCE_AR) ? batch : batch * D.T;
 
   const AttnShape sh{D.T, batch, 0, 0};
-  HIP_TRY(launch_assemble(D, c->tree, rm, *st, c->taps, batch, mode, PromptArgs{}, attn_plan_cfg(c), s));
+  HIP_TRY(launch_assemble(D, c->tree, rm, *st, c->taps, batch, mode, PromptArgs{}, attn_plan_cfg(c, sh), s));
   GemmProb pd{};
   TRY(forward_rows(c, st, rows_max, c->tree, sh, &pd, s));
   TRY(run_lm_head(c, pd, nullptr, rows_max, s));
@@ -710,7 +777,7 @@ int run_prompt(cerberus_ctx* c, const cerberus_state* st, int batch, int seq, co
     const bool last = off + n >= n_tokens;
     const AttnShape sh{std::min(n, kPromptPiece), ceil_div(n, kPromptPiece), kPromptPiece, seq};
     HIP_TRY(launch_assemble(D, c->chain, rm, *st, c->taps, batch, ASSEMBLE_PROMPT, PromptArgs{tokens + off, n, seq, kPromptPiece, off == 0 ? 1 : 0, last ? 1 : 0},
-                            attn_plan_cfg(c), s));
+                            attn_plan_cfg(c, sh), s));
     GemmProb pd{};
     TRY(forward_rows(c, st, n, c->chain, sh, &pd, s));
     HIP_TRY(launch_prompt_commit(rm, *st, c->last_row, batch, seq, last ? 1 : 0, s));
@@ -857,7 +924,6 @@ int cerberus_init(cerberus_ctx** out, const cerberus_config* cfg, const cerberus
     }
   }
   if (D.dtype == CERBERUS_BF16) {
-    c->fused_grid = kFusedGrid;
     HIP_INIT(init_team_gemm());
     std::vector<int> tq, tg;
     fused_tables(D, c->fused_grid, tq, c->ns_qkv, tg, c->ns_gu);     // the same tables the workspace was laid out for
@@ -967,8 +1033,7 @@ int cerberus_bench_gemm(cerberus_ctx* ctx, int32_t kind, int32_t rows, void* str
                    ((kind == 100 && ctx->ns_qkv) || (kind == 102 && ctx->ns_gu));
     TeamPlan tp;   // (2 + NT: the team kernel with NT row tiles per workgroup)
     const GemmBatch* g = kind == 100 ? &ctx->p_qkv[0] : kind == 102 ? &ctx->p_gu[0] : kind == 103 ? &ctx->p_down[0] : kind == 104 ? &ctx->p_lm : nullptr;
-    const bool team = g && g->team_rows && ctx->gemm_team >= g->team_rows && rows > g->team_above && D.dtype == CERBERUS_BF16 && ctx->act_split == 1 &&
-                      ctx->fused_grid >= 8 && plan_team_gemm(rows, g->p[0].N, g->p[0].K, ctx->fused_grid, ctx->max_split, g->team_live != 0, 0, &tp);
+    const bool team = g && plan_team(ctx, *g, rows, 1, &tp);
     if (bytes) *bytes = f ? 1.0 : team ? 2.0 + tp.NT : 0.0;
     return CERBERUS_OK;
   }

@@ -78,7 +78,8 @@ struct RowMap {
                   // cache-range items, then its tree chunks), y = kv_len, z = (rows of the sequence << 16) | its
                   // first row, w = (cache-range items of the sequence << 16) | chunks per cache-range item;
                   // x = -1 from the end of the list on
-  int* seq_npi;   // [B or pieces] cache-range items of the sequence (of a prompt pass: of the piece)
+  int2* seq_items; // [B or pieces] of the sequence (of a prompt pass: of the piece): items of the sequences before it (where its
+                  // partials start), its cache-range items
   // prompt passes only: the rows of the pass that go on to the final norm and the LM head, and whether the prompt has ended
   // for want of room (see PromptArgs)
   int* tail;      // [3] first row, rows, ended
@@ -86,7 +87,7 @@ struct RowMap {
 
 struct AttnPlanCfg {
   int chunk;       // committed cache rows per chunk: cache-range items are cut in these units (0: no work list)
-  int target_wgs;  // the work list aims at this many workgroups over all heads
+  int per_head;    // the work list aims at this many cache-range items (and has at most one more per sequence, from rounding)
   int att_cap;     // entries of the list
 };
 
@@ -181,8 +182,9 @@ struct AttnArgs {
   const void* vtree; //            the tree keys are read from here, the cache only serves rows < L
   void* out;         // [rows][nH*dh] attention output (GEMM A operand; bf16: lo plane out_lo_off elements later)
   size_t out_lo_off;
-  float* part_o;     // [B][nH][n_items_max][Tpad][dh]; slot j of a (seq, head) belongs to the sequence's work item j
-  float* part_ml;    // [B][nH][n_items_max][Tpad][2]
+  float* part_o;     // [nH][grid_x][Tpad][dh]: one block of Tpad query rows per item of the work list, sequence by sequence
+  float* part_ml;    // [nH][grid_x][Tpad][2]
+  size_t part_rows;  // rows per head that the two have room for (grid_x * Tpad at most)
   RowMap rm;
   const unsigned long long* anc;   // [T][aw]
   int aw;            // mask words per node
@@ -193,8 +195,7 @@ struct AttnArgs {
   int seq0;          // prompt pass: the sequence whose cache the pieces share
   int batch, Bmax, nH, dh, cap;
   int chunk;         // committed cache rows per chunk of the work list
-  int n_items_max;   // partial slots of a (seq, head): cache chunks of the whole cache + tree items
-  int grid_x;        // workgroups along the item axis (the kernel strides over the list if it is longer)
+  int grid_x;        // workgroups along the item axis, at least as many as the list has items
   int att_cap;       // entries of the work list
   int rows_max;
   int* status;

@@ -159,23 +159,23 @@ __global__ __launch_bounds__(256) void k_assemble(const Dims D, const TreeDev tr
     int chunks = 0;
     for (int b = 0; b < nseq; ++b)
       if (rows_of(b) > 0) chunks += (len_of(b) + ap.chunk - 1) / ap.chunk;
-    const int per_head = max(1, ap.target_wgs / D.nH);
-    const int cps = min(0xffff, max(1, (chunks + per_head - 1) / per_head));
+    const int cps = min(0xffff, max(1, (chunks + ap.per_head - 1) / ap.per_head));
     // The cache ranges of all sequences come first, the short tree chunks last: workgroups start in list order, and the
     // short ones fill what the long ones leave at the end.
     auto ranges_of = [&](int b) { return rows_of(b) > 0 ? ((len_of(b) + ap.chunk - 1) / ap.chunk + cps - 1) / cps : 0; };
-    int n = 0, n_tree = 0;
+    int n = 0, n_tree = 0, slot = 0;
     for (int b = 0; b < nseq; ++b) n_tree += ranges_of(b);      // where the tree chunks start
     for (int b = 0; b < nseq; ++b) {
       const int Tb = rows_of(b), Lb = len_of(b);
       const int npi = ranges_of(b), ntree = (Tb + 63) / 64;
-      if (t == 0) rm.seq_npi[b] = npi;
+      if (t == 0) rm.seq_items[b] = make_int2(slot, npi);
       for (int j = t; j < npi + ntree; j += blockDim.x) {
         const int i = j < npi ? n + j : n_tree + j - npi;
         if (i < ap.att_cap) rm.att_item[i] = make_int4((b << 16) | j, Lb, (Tb << 16) | row0_of(b), (npi << 16) | cps);
       }
       n += npi;
       n_tree += ntree;
+      slot += npi + ntree;
     }
     n = n_tree;
     for (int i = n + t; i < ap.att_cap; i += blockDim.x) rm.att_item[i] = make_int4(-1, 0, 0, 0);

@@ -63,6 +63,19 @@ def test_workspace_bytes_and_host_validation(L):
         assert (B.cerberus_workspace_bytes(_cfg(), t4) > 0) == ok, n
 
 
+@pytest.mark.parametrize("name,dtype,tree,batch,capacity,limit", [
+    ("7b", B.CERBERUS_BF16, "p63", 1, 4224, 27.0e9), ("13b", B.CERBERUS_BF16, "p63", 1, 2304, 39.2e9),
+    ("7b", B.CERBERUS_BF16, "p63", 8, 4096, 27.7e9), ("7b", B.CERBERUS_BF16, "p63", 16, 8192, 28.8e9),
+    ("tiny", B.CERBERUS_F32, "tiny", 1, 256, 21e6), ("tiny", B.CERBERUS_F32, "tiny", 1, 4096, 27e6)])
+def test_workspace_is_what_the_weights_and_the_launches_need(L, name, dtype, tree, batch, capacity, limit):
+    """A prompt pass of 1152 rows takes its row buffers and the partial planes its own launches write, not those of an LM head
+    over as many rows; the attention partials follow the work list, not sequences times cache length; a small cache
+    has room for fewer pieces.  The repacked weights are 25.5, 37.9 and 0 GB of these."""
+    cfg = synth.make_config(name)
+    t, keep = B.make_tree(*synth.make_tree(tree, cfg["n_cerb_heads"]))
+    assert 0 < B.cerberus_workspace_bytes(B.make_config(cfg, dtype, batch, capacity), t) <= limit
+
+
 def test_init_rejects_null_arguments_without_a_gpu(L):
     parent, rank = synth.make_tree("tiny")
     tree, keep = B.make_tree(parent, rank)

@@ -205,3 +205,30 @@ def test_down_projection_of_a_large_batch(one_token):
         rep = H.compare_step(pair.cfg, out, st, taps, b, pair.T, B.CERBERUS_BF16, ost, tol=H.TOL_BF16)
         assert not rep.failures, f"seq {b}: " + "; ".join(rep.failures)
     pair.engine.close()
+
+
+@pytest.mark.parametrize("lens", [(8100, 8000), (130, 8190), (0, 7)])
+def test_attention_work_list_stays_within_the_partials(lens):
+    """16 heads and two sequences of up to 8190 committed rows (64 chunks each): the partials have room for the 64 + 2 ranges of the
+    default workgroup target, and a larger target (one range per chunk: 128) is cut back to that.  Every target against
+    the plain kernel, which has no list; the bar is that of the tiny shapes."""
+    print(f"committed rows {lens}", flush=True)
+    pair = H.Pair("tiny", B.CERBERUS_BF16, "rand65s3k4", seed=7, max_batch=2, kv_capacity=8320, d_model=1024, n_heads=16, head_dim=64)
+    taps, out = pair.taps(), {}
+    for mfma, target in ((0, 1024), (1, 1024), (1, 65536), (1, 1)):
+        pair.engine.set_param("attn_mfma", mfma)
+        pair.engine.set_param("attn_target_wgs", target)
+        st = pair.engine.new_state()
+        g = torch.Generator(device="cuda")
+        g.manual_seed(2)
+        for layer in st.kv:
+            layer.normal_(0.0, 1.0, generator=g)
+        st.kv_len.copy_(torch.tensor(lens, dtype=torch.int32))
+        st.cand.copy_(synth.make_candidates(pair.cfg, 2, seed=4))
+        pair.engine.verify_step(st, 2)
+        torch.cuda.synchronize()
+        assert int(st.status[0]) == 0
+        out[mfma, target] = taps.h_last.clone()
+    for key, got in out.items():
+        assert float((got - out[0, 1024]).abs().max()) <= H.TOL_BF16_TINY.hidden, key
+    pair.engine.close()
