@@ -30,12 +30,19 @@ constexpr int kSPT = 32;  // slabs per workgroup tile (8 waves x 4)
 __device__ __forceinline__ void team_dma16(const void* gptr, unsigned lds_addr) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(gptr) : "memory", "m0");
 }
-// 16 bytes per lane from a wave-uniform base.  The destination is an in/out operand on purpose: the register then
-// stays reserved for its ring slot from one load to the next, also while a load whose value nobody will use (a
+// 16 bytes per lane from each of four wave-uniform bases.  The destinations are in/out operands on purpose: the registers then
+// stay reserved for their ring slot from one load to the next, also while a load whose value nobody will use (a
 // clamped repeat at the end of a range) is in flight.  A destination the compiler believes dead would be handed
 // to other values and overwritten when the data arrives.
-__device__ __forceinline__ void team_wload(u32x4_t& d, unsigned voff, const void* sbase) {
-  asm volatile("global_load_dwordx4 %0, %1, %2" : "+v"(d) : "v"(voff), "s"(sbase) : "memory");
+// The wait states in front: a scalar register written by the vector unit (v_readfirstlane, or v_readlane where the compiler
+// reloads a spilled one) may be read as an address by a memory instruction five wait states later at the earliest.  The
+// compiler inserts them for its own loads but not inside inline assembly, where the load takes a stale base and can fault;
+// all four bases are operands of this block, so what they are computed with lies before its wait.
+__device__ __forceinline__ void team_wload4(u32x4_t (&d)[4], unsigned voff, const char* const (&sbase)[4]) {
+  asm volatile("s_nop 4\n\tglobal_load_dwordx4 %0, %4, %5\n\tglobal_load_dwordx4 %1, %4, %6\n\t"
+               "global_load_dwordx4 %2, %4, %7\n\tglobal_load_dwordx4 %3, %4, %8"
+               : "+v"(d[0]), "+v"(d[1]), "+v"(d[2]), "+v"(d[3])
+               : "v"(voff), "s"(sbase[0]), "s"(sbase[1]), "s"(sbase[2]), "s"(sbase[3]) : "memory");
 }
 // waits until at most N of this wave's loads are in flight; the slot's registers are operands so that nothing
 // that reads them moves above the wait
@@ -142,7 +149,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int j = 0; j < 4; ++j) Wr[r][j] = u32x4_t{0u, 0u, 0u, 0u};
 #define TEAM_W_ISSUE(slot, advance)                                                                             \
   {                                                                                                             \
-    _Pragma("unroll") for (int j = 0; j < 4; ++j) team_wload(Wr[slot][j], wlane, wsl[j] + (size_t)ksw * 1024);  \
+    team_wload4(Wr[slot], wlane + (unsigned)ksw * 1024, wsl);                                                   \
     if ((advance) && wissued + 1 < len * kKC) {                                                                 \
       ++wissued;                                                                                                \
       if (++ksw >= a.ksteps) { ksw = 0; ++cbw; TEAM_W_BASES() }                                                 \
