@@ -28,6 +28,7 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E bandwidth
 MFMA_PEAK_TFLOPS = 2500.0      # MI355X published dense bf16 MFMA rate
+PROMPT_PASS_ROWS = 1152        # rows that a pass of cerberus_prefill takes through the layers
 GEMM_KINDS = ["qkv", "attn_out", "ffn_gate_up", "ffn_down", "lm_head", "head_resblocks", "head_fc"]
 
 
@@ -269,8 +270,8 @@ def main() -> int:
     ap.add_argument("--no-cpu", action="store_true", help="skip the CPU-oracle baseline")
     ap.add_argument("--param", action="append", default=[], help="library tuning knob name=value")
     ap.add_argument("--prefill", type=int, default=0, metavar="N",
-                    help="time the prompt phase (cerberus_prefill) of N tokens from an empty cache; value is per pass of "
-                         "up to CERBERUS_MAX_TREE rows")
+                    help="time the prompt phase (cerberus_prefill) of N tokens from an empty cache; value is per call, the whole "
+                         "prompt (the roofline and mfma objects stay those of the tree's GEMM launches)")
     ap.add_argument("--decode", type=int, default=0, metavar="N",
                     help="time N chained steps per call (cerberus_decode: device-side gate, token log); value is per step")
     ap.add_argument("--tree", default=None, help="candidate tree: p63 (default, 64 nodes), p120 or p150 (top-10 per head)")
@@ -366,7 +367,6 @@ def main() -> int:
     per_call = max(args.decode, 1)
     if args.prefill:
         prompt_dev = synth.make_token_ids(args.prefill, cfg["vocab"], seed=4).cuda()
-        per_call = (args.prefill + B.CERBERUS_MAX_TREE - 1) // B.CERBERUS_MAX_TREE          # passes per call
 
     def step():
         st.kv_len.copy_(L_dev)          # every repetition sees the configured prefix lengths ...
@@ -448,7 +448,7 @@ def main() -> int:
         # where the step does not run those as whole-K fused launches); head GEMMs run the 16-row instance
         how = B.cerberus_bench_gemm(eng.ctx, 100 + kind, rows) if kind in (0, 2, 3, 4) else 0.0   # 1: whole-K fused, 2 + NT: team kernel
         fused_kind = kind in (0, 2) and how == 1.0
-        gemm[kname]["kernel"] = ("k_qkv_rope" if kind == 0 else "k_gate_up_swiglu") if fused_kind else "k_gemm_team<%d>" % int(how - 2) if how >= 2.0 else (
+        gemm[kname]["kernel"] = ("k_qkv_rope" if kind == 0 else "k_gate_up_swiglu") if fused_kind else "k_gemm_team<%d,false>" % int(how - 2) if how >= 2.0 else (
             "k_gemm_bf16<1,2,1,true>" if kind > 4 else "k_gemm_bf16_rows<1>" if rows > 256 and kind in (3, 4)
             else "k_gemm_bf16<4,2,1,%s>" % ("true" if rows <= 64 else "false"))
     # the roofline object covers the kernel of the layer stack that takes the most time in a step
@@ -498,8 +498,17 @@ def main() -> int:
             "frac_executed": round(2 * fl_total / (gemm_ms * 1e-3) / 1e12 / MFMA_PEAK_TFLOPS, 4),
             "note": "flops = 2*N*K*rows of every GEMM of the step; gemm_ms = their launches timed back to back with events; "
                     "executed counts both activation planes"}
+    fl_step = fl_total
+    if args.prefill:                    # the layers over the whole prompt, LM head over its last piece of up to 192 tokens
+        prompt_passes = -(-args.prefill // PROMPT_PASS_ROWS)
+        alg = algorithmic_bytes(cfg, args.prefill, 0)
+        alg["layer_weights"] *= prompt_passes
+        alg["total"] = sum(v for k, v in alg.items() if k != "total")
+        rows_step, fl_p = args.prefill, gemm_flops(cfg, args.prefill, head_rows)
+        fl_p["lm_head"] *= ((args.prefill - 1) % B.CERBERUS_MAX_TREE + 1) / args.prefill
+        fl_step = sum(fl_p.values())
     t_hbm = alg["total"] / (HBM_PEAK_GBS * 1e9)
-    t_mfma = 2 * fl_total / (MFMA_PEAK_TFLOPS * 1e12)
+    t_mfma = 2 * fl_step / (MFMA_PEAK_TFLOPS * 1e12)
     step_s = ms_per_step * 1e-3
 
     out = {
@@ -509,7 +518,7 @@ def main() -> int:
         "config": {"workload": (f"{name}-shape bf16, {T}-node tree, KV prefix {L}, batch 1, gate forced parallel"
                                 + (", independent (Medusa-style) heads" if args.medusa_heads else "")
                                 + (f", {args.decode} chained steps per call" if args.decode else "")
-                                + (f"; prompt phase of {args.prefill} tokens from an empty cache, {per_call} passes per call, "
+                                + (f"; prompt phase of {args.prefill} tokens from an empty cache, {prompt_passes} pass(es), value per call, "
                                    "tokens_per_s = prompt tokens" if args.prefill else "")
                                 if Bn == 1 and not args.ar else
                                 f"{name}-shape bf16, batch {Bn}, KV prefixes {Ls}, step kinds (1 = auto-regressive) {flags}, "
@@ -522,7 +531,7 @@ def main() -> int:
         "step_hbm_frac": round(alg["total"] / (ms_per_step * 1e-3) / (HBM_PEAK_GBS * 1e9), 4),
         "step_mfma_frac": round(t_mfma / step_s, 4),
         "step_bound": {"hbm_time_at_peak_ms": round(t_hbm * 1e3, 3), "mfma_time_at_peak_ms": round(t_mfma * 1e3, 3),
-                       "binding": "hbm" if t_hbm >= t_mfma else "mfma", "rows": rows_step, "sum_prefix": int(sum(Ls))},
+                       "binding": "hbm" if t_hbm >= t_mfma else "mfma", "rows": rows_step, "sum_prefix": 0 if args.prefill else int(sum(Ls))},
         "roofline": {"bound": "hbm", "kernel": dom + " (" + ", ".join(by_kernel[dom]["kinds"]) + ")",
                      "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4),

@@ -442,8 +442,8 @@ hipError_t launch_attention(const AttnArgs& a, int dtype, int use_mfma, hipStrea
   // their number a multiple of 8, an item ran on one XCD for every head, and the XCDs with the long items finished last
   // (half of the places stood empty over the launch).  This way every XCD gets each item for an eighth of the heads, long
   // items start first (the list's order), and the query blocks of an item read the same K/V rows from the same L2 soon
-  // after each other.  32 heads, 16 sequences of 256..2048 rows: 123 -> 98 us; 8 of 831..3312: 90 -> 76; a 1024-token
-  // prompt: 68 -> 57; one of 1024 with 121 tree rows: 20.9 -> 19.6.
+  // after each other.  32 heads, 16 sequences of 256..2048 rows: 123 -> 94..103 us (several runs); 8 of 831..3312: 90 ->
+  // 75..77; a 1024-token prompt: 68 -> 55..60; one of 1024 with 121 tree rows: 20.9 -> 19.6..19.9.
   dim3 grid(a.nH, a.tc_max, a.grid_x < 65535 ? a.grid_x : 65535);
   const int hpw = 128 / (a.dh / 4);
   dim3 cgrid(a.rows_max, (a.nH + hpw - 1) / hpw);

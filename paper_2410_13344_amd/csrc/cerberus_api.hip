@@ -529,7 +529,7 @@ int piece_split(const cerberus_ctx* c, const GemmBatch& plan) {
 // only past 256 rows: with two row blocks their extra planes cost what the kernel gains.  The down projection has
 // few columns, so few row blocks mean many teams and planes (8 planes at 640 rows, where the kernel gains nothing);
 // from seven row blocks on it takes 4 to 5 and wins: 162 us against 200 at 1024 rows of the 7B shape
-// (+ 7 us for the consumer of the planes).  How many of those rows are live the gate decides on the device, so its
+// (+ 5 us for the consumer of the planes).  How many of those rows are live the gate decides on the device, so its
 // teams and planes follow the live rows (see plan_team_gemm).  The O projection, with a third of the K for the same
 // planes, stays on the 64-row blocks (69 us + planes against 80).
 bool plan_team(const cerberus_ctx* c, const GemmBatch& g, int rows_max, int min_split, TeamPlan* tp) {
