@@ -382,16 +382,13 @@ __global__ __launch_bounds__(128) void k_attn_combine(const AttnArgs a) {
   const int r = blockIdx.x, h = blockIdx.y * HPW + threadIdx.x / LPH, t = (threadIdx.x % LPH) * 4;
   if (r >= *a.rm.n_rows || h >= a.nH) return;
   int b = a.rm.row_seq[r], node = a.rm.row_node[r];
-  int chunks;                                // tree chunks that this row's query block has a partial of
   if (a.piece) {
     b = node / a.piece;
     node -= b * a.piece;
-    chunks = (node >> 6) + 1;
-  } else {
-    chunks = (a.rm.seq_T[b] + 63) / 64;
   }
-  const int2 it = a.rm.seq_items[b];
-  const int nch = it.y + chunks;   // the sequence's cache-range items + tree chunks
+  const int4 it = a.rm.seq_items[b];
+  // the sequence's cache-range items + the tree chunks that this row's query block has a partial of
+  const int nch = it.y + (a.piece ? (node >> 6) + 1 : it.z);
   const size_t base = ((size_t)h * a.grid_x + it.x) * a.Tpad + node;
   constexpr int NB = 8;
   float M = -INFINITY, den = 0.f, num[4] = {0.f, 0.f, 0.f, 0.f};

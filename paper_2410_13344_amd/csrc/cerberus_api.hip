@@ -238,7 +238,7 @@ size_t layout(cerberus_ctx* c, unsigned char* base) {
   c->rm.row_pos = b.take<int>(Rmax);
   c->rm.row_tok = b.take<int>(Rmax);
   c->rm.att_item = b.take<int4>((size_t)c->att_cap);
-  c->rm.seq_items = b.take<int2>(std::max(B, kPromptPieces));
+  c->rm.seq_items = b.take<int4>(std::max(B, kPromptPieces));
   c->rm.tail = b.take<int>(3);
   c->last_row = b.take<int>(B);
   c->path = b.take<int>((size_t)B * (D.Hc + 1));

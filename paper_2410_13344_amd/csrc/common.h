@@ -78,8 +78,8 @@ struct RowMap {
                   // cache-range items, then its tree chunks), y = kv_len, z = (rows of the sequence << 16) | its
                   // first row, w = (cache-range items of the sequence << 16) | chunks per cache-range item;
                   // x = -1 from the end of the list on
-  int2* seq_items; // [B or pieces] of the sequence (of a prompt pass: of the piece): items of the sequences before it (where its
-                  // partials start), its cache-range items
+  int4* seq_items; // [B or pieces] of the sequence (of a prompt pass: of the piece): items of the sequences before it (where its
+                  // partials start), its cache-range items, its tree chunks
   // prompt passes only: the rows of the pass that go on to the final norm and the LM head, and whether the prompt has ended
   // for want of room (see PromptArgs)
   int* tail;      // [3] first row, rows, ended
