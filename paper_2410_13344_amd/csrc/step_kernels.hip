@@ -371,8 +371,7 @@ hipError_t launch_add_rmsnorm(const Dims& D, const RowMap& rm, float* x, const f
 // ---------------------------------------------------------------------------------------------
 // TILED (bf16 only): the GEMM input goes out in MFMA A-fragment order for the whole-K GEMMs: the 8 values of
 // row r at columns ks*32 + g*8.. form 16-byte piece ((ks*2 + plane)*4 + r/16)*64 + r%16 + 16*g, 64 rows in all.
-// DEV: the number of partial planes comes from the device (an instance of its own: 6.4 us where the test made it 6.5).
-template <typename T, int MAXS, bool TILED, bool DEV = false>
+template <typename T, int MAXS, bool TILED>
 __global__ __launch_bounds__(256) void k_add_gain(float* __restrict__ x, const float* __restrict__ part, int S,
                                                   const int* __restrict__ S_dev, size_t pstride,
                                                   const float* __restrict__ gain, T* __restrict__ out, size_t lo_off,
@@ -380,7 +379,7 @@ __global__ __launch_bounds__(256) void k_add_gain(float* __restrict__ x, const f
   __shared__ float sh[4];
   const int r = blockIdx.x, nb = gridDim.y;
   if (r >= *rm.n_rows) return;
-  if (DEV) S = *S_dev;
+  if (S_dev) S = *S_dev;
   const int c = (blockIdx.y * 256 + threadIdx.x) * 4;
   float ss = 0.f;
   if (c < d) {
@@ -418,14 +417,10 @@ hipError_t launch_add_gain(const Dims& D, const RowMap& rm, float* x, const floa
                            const float* gain, void* out, float* ssq, int rows_max, hipStream_t s, bool a_tiled) {
   const dim3 grid(rows_max, add_gain_blocks(D.d));
   if (a_tiled && (D.dtype == 0 || rows_max > 64)) return hipErrorInvalidValue;
-  if (S_dev && (D.dtype == 0 || a_tiled)) return hipErrorInvalidValue;
 #define CERB_CALL(MS)                                                                                                  \
   if (D.dtype == 0)                                                                                                    \
     hipLaunchKernelGGL((k_add_gain<float, MS, false>), grid, dim3(256), 0, s, x, part, S, S_dev, pstride, gain, (float*)out,  \
                        (size_t)0, ssq, rm, D.d);                                                                       \
-  else if (S_dev)                                                                                                      \
-    hipLaunchKernelGGL((k_add_gain<bf16_t, MS, false, true>), grid, dim3(256), 0, s, x, part, S, S_dev, pstride, gain, (bf16_t*)out, \
-                       (size_t)D.R64 * D.d, ssq, rm, D.d);                                                             \
   else if (a_tiled)                                                                                                    \
     hipLaunchKernelGGL((k_add_gain<bf16_t, MS, true>), grid, dim3(256), 0, s, x, part, S, S_dev, pstride, gain, (bf16_t*)out, \
                        (size_t)D.R64 * D.d, ssq, rm, D.d);                                                             \
