@@ -219,7 +219,8 @@ int cerberus_set_taps(cerberus_ctx *ctx, const cerberus_taps *taps);
  *                                              (bf16-rounded GEMM inputs: faster, less accurate)
  *   "attn_chunk"      (128 or 256, default 128) committed cache rows per round of an attention workgroup
  *   "attn_target_wgs" (1..65536, default 1024) workgroups the attention work list aims at (over all heads): the
- *                                              longer the sequences, the more rounds a workgroup walks
+ *                                              longer the sequences, the more rounds a workgroup walks; a target
+                                              above the default is cut back to the workspace's room for partials
  *   "attn_mfma"       (0 or 1, default 1)      0: plain attention kernel instead of the MFMA one
  *   "gemm_fused"      (0 or 1, default 1)      1: bf16 launches of up to 64 rows run QKV + RoPE + KV write and
  *                                              gate/up + SwiGLU as one whole-K launch each (where the shapes
