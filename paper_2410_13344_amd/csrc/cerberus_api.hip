@@ -630,6 +630,20 @@ int run_fused_gate_up(const cerberus_ctx* c, int l, hipStream_t s) {
   return CERBERUS_OK;
 }
 
+// Launches of more than 64 rows: gate/up with SwiGLU as one whole-K launch (see gemm_tile.hip)
+bool tile_launches(const cerberus_ctx* c, int rows_max) {
+  return c->use_fused && c->cfg.dtype == CERBERUS_BF16 && c->act_split == 1 && c->fused_grid > 0 && rows_max > 64 && rows_max <= (c->fused_grid - 2) * 128;
+}
+
+int run_tile_gate_up(const cerberus_ctx* c, int l, int rows_max, hipStream_t s) {
+  const Dims& D = c->D;
+  FusedGateUpArgs ga{};
+  ga.ssq = c->ssq; ga.nb = add_gain_blocks(D.d); ga.d = D.d; ga.eps = D.eps; ga.act = (bf16_t*)c->act; ga.lo_off = (size_t)c->R64 * D.Fpad; ga.Fpad = D.Fpad;
+  const TileGemmArgs ta{c->wgu[l], c->xn, kpad(c->cfg, D.d) / 32, D.F / 16, c->rm.n_rows, rows_max};
+  HIP_TRY(launch_tile_gate_up(ta, ga, c->fused_grid, s));
+  return CERBERUS_OK;
+}
+
 // How a launch's attention is cut: most rows of one sequence, sequences; prompt pass: rows per piece (each counts as a
 // sequence) and the sequence that owns the cache.
 struct AttnShape { int T, batch, piece, seq0; };
@@ -654,11 +668,12 @@ int forward_rows(cerberus_ctx* c, const cerberus_state* st, int rows_max, const 
   // launches of up to 64 rows: QKV + RoPE + KV write and gate/up + SwiGLU as one whole-K launch each
   const bool fused = c->use_fused && D.dtype == CERBERUS_BF16 && rows_max <= 64 && c->fused_grid > 0 && c->act_split == 1;
   const bool fq = fused && c->ns_qkv > 0, fg = fused && c->ns_gu > 0;
+  const bool tg = tile_launches(c, rows_max) && D.F % 16 == 0;
   // QKV of a prompt pass of several pieces (see kPromptPieces)
   const int qkv_split = sh.piece && rows_max > kPromptPiece ? piece_split(c, c->p_qkv[0]) : 1;
   for (int l = 0; l < D.n_layers; ++l) {
     HIP_TRY(launch_add_gain(D, rm, c->x, prev ? prev->out : nullptr, prev ? prev->S : 0, prev ? prev->S_dev : nullptr,
-                            prev ? (size_t)prev->out_rows * prev->N : 0, c->attn_norm[l], c->xn, c->ssq, rows_max, s, fq));
+                            prev ? (size_t)prev->out_rows * prev->N : 0, c->attn_norm[l], c->xn, c->ssq, rows_max, s, fq ? A_FRAG64 : A_ROWS));
     GemmProb pq, po, pg;
     void* kv_layer = (unsigned char*)st->kv + (size_t)l * kv_layer_bytes;
     if (fq) {
@@ -678,9 +693,12 @@ int forward_rows(cerberus_ctx* c, const cerberus_state* st, int rows_max, const 
     aa.rows_max = rows_max; aa.status = st->status;
     HIP_TRY(launch_attention(aa, D.dtype, c->use_mfma_attn, s));
     TRY(run_gemm(c, c->p_o[l], rm.n_rows, 0, rows_max, nullptr, 0, s, &po));
-    HIP_TRY(launch_add_gain(D, rm, c->x, po.out, po.S, po.S_dev, (size_t)po.out_rows * po.N, c->ffn_norm[l], c->xn, c->ssq, rows_max, s, fg));
+    HIP_TRY(launch_add_gain(D, rm, c->x, po.out, po.S, po.S_dev, (size_t)po.out_rows * po.N, c->ffn_norm[l], c->xn, c->ssq, rows_max, s,
+                            fg ? A_FRAG64 : tg ? A_FRAG : A_ROWS));
     if (fg) {
       TRY(run_fused_gate_up(c, l, s));
+    } else if (tg) {
+      TRY(run_tile_gate_up(c, l, rows_max, s));
     } else {
       TRY(run_gemm(c, c->p_gu[l], rm.n_rows, 0, rows_max, nullptr, 0, s, &pg));
       HIP_TRY(launch_swiglu(D, rm, pg.out, pg.S, (size_t)pg.out_rows * pg.N, c->act, c->ssq, rows_max, s));
@@ -925,6 +943,7 @@ int cerberus_init(cerberus_ctx** out, const cerberus_config* cfg, const cerberus
   }
   if (D.dtype == CERBERUS_BF16) {
     HIP_INIT(init_team_gemm());
+    HIP_INIT(init_tile_gemm());
     std::vector<int> tq, tg;
     fused_tables(D, c->fused_grid, tq, c->ns_qkv, tg, c->ns_gu);     // the same tables the workspace was laid out for
     if (c->ns_qkv) HIP_INIT(hipMemcpy(c->slabs_qkv, tq.data(), tq.size() * sizeof(int), hipMemcpyHostToDevice));

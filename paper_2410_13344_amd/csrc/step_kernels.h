@@ -54,16 +54,17 @@ hipError_t launch_add_rmsnorm(const Dims& D, const RowMap& rm, float* x, const f
                               const float* gain, void* out, float* out_f32, float* tap, const int* src0, int rows_max, hipStream_t s);
 // residual add + x * gain + per-block sums of x^2 (the RMSNorm scalar is applied by the consumer of the next GEMM)
 int add_gain_blocks(int d);   // sums per row
-// a_tiled: write the GEMM input in MFMA A-fragment order (64 rows, see FusedQkvArgs) instead of row-major planes
+// How a GEMM input lies in memory: row-major planes, or MFMA A-fragment order (bf16; see FusedQkvArgs and TileGemmArgs)
+enum { A_ROWS = 0, A_FRAG64 = 1, A_FRAG = 2 };
 hipError_t launch_add_gain(const Dims& D, const RowMap& rm, float* x, const float* part, int S, const int* S_dev, size_t pstride,
-                           const float* gain, void* out, float* ssq, int rows_max, hipStream_t s, bool a_tiled = false);
+                           const float* gain, void* out, float* ssq, int rows_max, hipStream_t s, int order = A_ROWS);
 hipError_t launch_rope_kv(const Dims& D, const RowMap& rm, const float* part, int S, size_t pstride,
                           const float2* rope_cs, void* q, void* kv_layer, void* ktree, void* vtree, const float* ssq,
                           int rows_max, hipStream_t s);
 // Whole-K GEMMs with fused epilogues (gemm_fused.hip), launches of up to 64 rows in bf16 mode.
 // At: the GEMM input in MFMA A-fragment order, piece [((ks * 2 + plane) * 4 + mt) * 64 + lane] = the 8 values
 // of row mt*16 + lane%16 at columns ks*32 + (lane/16)*8.., plane 0 = hi, 1 = lo (written by launch_add_gain
-// with a_tiled).  slabs: [grid][ns] 16-column slabs of every workgroup, -1 = none; positions (2p, 2p+1) form a pair.
+// in order A_FRAG64).  slabs: [grid][ns] 16-column slabs of every workgroup, -1 = none; positions (2p, 2p+1) form a pair.
 struct FusedQkvArgs {
   const void* W;            // [3d][K] in the stream order of this kernel's grid and slab table (launch_pack_stream)
   const void* At;
@@ -97,6 +98,16 @@ hipError_t launch_qkv_rope(const FusedQkvArgs& a, int ns, int grid, hipStream_t 
 hipError_t launch_gate_up_swiglu(const FusedGateUpArgs& a, int ns, int grid, hipStream_t s);
 size_t fused_stream_pieces(int ns, int grid, int ksteps);   // 16-byte pieces of a stream-order weight copy
 hipError_t launch_pack_stream(const void* packed, void* dst, const int* table, int ns, int grid, int ksteps, hipStream_t s);
+// Whole-K GEMMs with fused epilogues for more rows (gemm_tile.hip, bf16 mode).
+struct TileGemmArgs {
+  const void* W;            // pre-tiled weights: fragment (slab, k-step) is 1 KB at (slab * ksteps + ks) * 1024
+  const void* A;            // fragment (row tile, k-step, plane) is 1 KB at ((mt * ksteps + ks) * 2 + plane) * 1024 (A_FRAG)
+  int ksteps, pairs;        // padded K / 32 (a multiple of 8); slab pairs of the launch
+  const int* n_rows;        // device row count
+  int rows_cap;             // upper bound of it
+};
+hipError_t init_tile_gemm();   // once per device, before the first launch
+hipError_t launch_tile_gate_up(const TileGemmArgs& a, const FusedGateUpArgs& g, int grid, hipStream_t s);   // W, A, rows: of a
 hipError_t launch_swiglu(const Dims& D, const RowMap& rm, const float* part, int S, size_t pstride, void* act,
                          const float* ssq, int rows_max, hipStream_t s);
 hipError_t launch_row_argmax(const Dims& D, const RowMap& rm, const float* part, int S, size_t pstride, int* g,

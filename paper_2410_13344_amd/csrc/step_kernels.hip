@@ -369,9 +369,10 @@ hipError_t launch_add_rmsnorm(const Dims& D, const RowMap& rm, float* x, const f
 // split-K partials (k_rope_kv, k_swiglu) forms 1 / sqrt(mean x^2 + eps) from those sums and scales.
 // Four workgroups per row at d = 4096 instead of one.
 // ---------------------------------------------------------------------------------------------
-// TILED (bf16 only): the GEMM input goes out in MFMA A-fragment order for the whole-K GEMMs: the 8 values of
-// row r at columns ks*32 + g*8.. form 16-byte piece ((ks*2 + plane)*4 + r/16)*64 + r%16 + 16*g, 64 rows in all.
-template <typename T, int MAXS, bool TILED>
+// ORDER (bf16 only) A_FRAG64, A_FRAG: the GEMM input goes out in MFMA A-fragment order for the whole-K GEMMs: the 8 values of
+// row r at columns ks*32 + g*8.. form a 16-byte piece, number ((ks*2 + plane)*4 + r/16)*64 + r%16 + 16*g (64 rows in all) or
+// ((r/16*ksteps + ks)*2 + plane)*64 + r%16 + 16*g.
+template <typename T, int MAXS, int ORDER>
 __global__ __launch_bounds__(256) void k_add_gain(float* __restrict__ x, const float* __restrict__ part, int S,
                                                   const int* __restrict__ S_dev, size_t pstride,
                                                   const float* __restrict__ gain, T* __restrict__ out, size_t lo_off,
@@ -392,17 +393,18 @@ __global__ __launch_bounds__(256) void k_add_gain(float* __restrict__ x, const f
     if (MAXS > 0) *reinterpret_cast<float4*>(xr) = v;
     ss = v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
     const float o[4] = {v.x * g.x, v.y * g.y, v.z * g.z, v.w * g.w};
-    if (TILED && sizeof(T) == 2) {
+    if (ORDER != A_ROWS && sizeof(T) == 2) {
       union { bf16_t h[4]; uint2 u; } hi, lo;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         hi.h[e] = f32_to_bf16(o[e]);
         lo.h[e] = f32_to_bf16(o[e] - bf16_to_f32(hi.h[e]));
       }
-      const size_t piece = ((size_t)(c >> 5) * 8 + (r >> 4)) * 64 + (r & 15) + 16 * ((c & 31) >> 3);   // hi plane; lo: + 4 * 64
+      const size_t frag = ORDER == A_FRAG64 ? (size_t)(c >> 5) * 8 + (r >> 4) : ((size_t)(r >> 4) * (d >> 5) + (c >> 5)) * 2;   // of the hi plane
+      const size_t piece = frag * 64 + (r & 15) + 16 * ((c & 31) >> 3);
       unsigned char* base = reinterpret_cast<unsigned char*>(out) + (c & 7) * 2;
       *reinterpret_cast<uint2*>(base + piece * 16) = hi.u;
-      *reinterpret_cast<uint2*>(base + (piece + 256) * 16) = lo.u;
+      *reinterpret_cast<uint2*>(base + (piece + (ORDER == A_FRAG64 ? 4 : 1) * 64) * 16) = lo.u;
     } else {
       st_a4(out + (size_t)r * d + c, lo_off, o);       // d % 4 == 0: aligned
     }
@@ -414,19 +416,15 @@ __global__ __launch_bounds__(256) void k_add_gain(float* __restrict__ x, const f
 int add_gain_blocks(int d) { return (d + 1023) / 1024; }
 
 hipError_t launch_add_gain(const Dims& D, const RowMap& rm, float* x, const float* part, int S, const int* S_dev, size_t pstride,
-                           const float* gain, void* out, float* ssq, int rows_max, hipStream_t s, bool a_tiled) {
+                           const float* gain, void* out, float* ssq, int rows_max, hipStream_t s, int order) {
   const dim3 grid(rows_max, add_gain_blocks(D.d));
-  if (a_tiled && (D.dtype == 0 || rows_max > 64)) return hipErrorInvalidValue;
-#define CERB_CALL(MS)                                                                                                  \
-  if (D.dtype == 0)                                                                                                    \
-    hipLaunchKernelGGL((k_add_gain<float, MS, false>), grid, dim3(256), 0, s, x, part, S, S_dev, pstride, gain, (float*)out,  \
-                       (size_t)0, ssq, rm, D.d);                                                                       \
-  else if (a_tiled)                                                                                                    \
-    hipLaunchKernelGGL((k_add_gain<bf16_t, MS, true>), grid, dim3(256), 0, s, x, part, S, S_dev, pstride, gain, (bf16_t*)out, \
-                       (size_t)D.R64 * D.d, ssq, rm, D.d);                                                             \
-  else                                                                                                                 \
-    hipLaunchKernelGGL((k_add_gain<bf16_t, MS, false>), grid, dim3(256), 0, s, x, part, S, S_dev, pstride, gain, (bf16_t*)out,\
-                       (size_t)D.R64 * D.d, ssq, rm, D.d)
+  if (order != A_ROWS && (D.dtype == 0 || D.d % 32 || (order == A_FRAG64 && rows_max > 64))) return hipErrorInvalidValue;
+#define CERB_ARGS(T) x, part, S, S_dev, pstride, gain, (T*)out, sizeof(T) == 2 ? (size_t)D.R64 * D.d : 0, ssq, rm, D.d
+#define CERB_CALL(MS)                                                                                                        \
+  if (D.dtype == 0) hipLaunchKernelGGL((k_add_gain<float, MS, A_ROWS>), grid, dim3(256), 0, s, CERB_ARGS(float));            \
+  else if (order == A_FRAG64) hipLaunchKernelGGL((k_add_gain<bf16_t, MS, A_FRAG64>), grid, dim3(256), 0, s, CERB_ARGS(bf16_t)); \
+  else if (order == A_FRAG) hipLaunchKernelGGL((k_add_gain<bf16_t, MS, A_FRAG>), grid, dim3(256), 0, s, CERB_ARGS(bf16_t));  \
+  else hipLaunchKernelGGL((k_add_gain<bf16_t, MS, A_ROWS>), grid, dim3(256), 0, s, CERB_ARGS(bf16_t))
   CERB_S_BUCKET(S, CERB_CALL);
 #undef CERB_CALL
   return hipGetLastError();
