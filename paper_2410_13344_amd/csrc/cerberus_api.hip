@@ -248,7 +248,7 @@ size_t layout(cerberus_ctx* c, unsigned char* base) {
   c->g = b.take<int>(Rmax);
   c->x = b.take<float>((size_t)R64 * d);
   c->h_last = b.take<float>((size_t)c->lm_rows * d);
-  c->ssq = b.take<float>((size_t)R64 * add_gain_blocks(d));
+  c->ssq = b.take<float>((size_t)R64 * add_gain_blocks(d, A_FRAG));   // (the order with the most)
   const int planes = cfg.dtype == CERBERUS_BF16 ? 2 : 1;  // GEMM inputs: hi and lo plane in bf16 mode
   c->xn = b.take<unsigned char>((size_t)planes * R64 * d * el);
   c->q = b.take<unsigned char>((size_t)planes * R64 * d * el);
@@ -614,7 +614,7 @@ int run_fused_qkv(const cerberus_ctx* c, int l, void* kv_layer, hipStream_t s) {
   const Dims& D = c->D;
   FusedQkvArgs fa{};
   fa.W = c->st_qkv[l]; fa.At = c->xn; fa.slabs = c->slabs_qkv; fa.ksteps = kpad(c->cfg, D.d) / 32; fa.ssq = c->ssq;
-  fa.nb = add_gain_blocks(D.d); fa.rope_cs = c->rope_cs; fa.rm = c->rm; fa.q = (bf16_t*)c->q; fa.kv_layer = (bf16_t*)kv_layer;
+  fa.nb = add_gain_blocks(D.d, A_FRAG64); fa.rope_cs = c->rope_cs; fa.rm = c->rm; fa.q = (bf16_t*)c->q; fa.kv_layer = (bf16_t*)kv_layer;
   fa.ktree = (bf16_t*)c->ktree; fa.vtree = (bf16_t*)c->vtree; fa.lo_off = (size_t)c->R64 * D.d; fa.D = D;
   HIP_TRY(launch_qkv_rope(fa, c->ns_qkv, c->fused_grid, s));
   return CERBERUS_OK;
@@ -624,23 +624,54 @@ int run_fused_gate_up(const cerberus_ctx* c, int l, hipStream_t s) {
   const Dims& D = c->D;
   FusedGateUpArgs ga{};
   ga.W = c->st_gu[l]; ga.At = c->xn; ga.slabs = c->slabs_gu; ga.ksteps = kpad(c->cfg, D.d) / 32; ga.ssq = c->ssq;
-  ga.nb = add_gain_blocks(D.d); ga.d = D.d; ga.eps = D.eps; ga.rm = c->rm; ga.act = (bf16_t*)c->act;
+  ga.nb = add_gain_blocks(D.d, A_FRAG64); ga.d = D.d; ga.eps = D.eps; ga.rm = c->rm; ga.act = (bf16_t*)c->act;
   ga.lo_off = (size_t)c->R64 * D.Fpad; ga.Fpad = D.Fpad;
   HIP_TRY(launch_gate_up_swiglu(ga, c->ns_gu, c->fused_grid, s));
   return CERBERUS_OK;
 }
 
-// Launches of more than 64 rows: gate/up with SwiGLU as one whole-K launch (see gemm_tile.hip)
-bool tile_launches(const cerberus_ctx* c, int rows_max) {
-  return c->use_fused && c->cfg.dtype == CERBERUS_BF16 && c->act_split == 1 && c->fused_grid > 0 && rows_max > 64 && rows_max <= (c->fused_grid - 2) * 128;
+// Launches of more than `above` rows that run on the tile kernel (see gemm_tile.h): above 64 rows gate/up with SwiGLU, above 128
+// QKV with RoPE and the KV write, O and down as well.
+constexpr int kTileGateUp = 64, kTileAll = 128;
+bool tile_launches(const cerberus_ctx* c, int rows_max, int above) {
+  return c->use_fused && c->cfg.dtype == CERBERUS_BF16 && c->act_split == 1 && c->fused_grid > 0 && rows_max > above && rows_max <= (c->fused_grid - 2) * 128;
+}
+
+// The down projection's input: in fragment order where that is a tile launch too and K has no padding.  (The padding is zero
+// from init on and nobody writes it, which holds as long as every launch lays the rows out alike.)
+bool act_frag(const cerberus_ctx* c, int rows_max) { return tile_launches(c, rows_max, kTileAll) && c->D.F == c->D.Fpad; }
+
+int run_tile_qkv(const cerberus_ctx* c, int l, void* kv_layer, int rows_max, hipStream_t s) {
+  const Dims& D = c->D;
+  FusedQkvArgs fa{};
+  fa.ssq = c->ssq; fa.nb = add_gain_blocks(D.d, A_FRAG); fa.rope_cs = c->rope_cs; fa.rm = c->rm; fa.q = (bf16_t*)c->q; fa.kv_layer = (bf16_t*)kv_layer;
+  fa.ktree = (bf16_t*)c->ktree; fa.vtree = (bf16_t*)c->vtree; fa.lo_off = (size_t)c->R64 * D.d; fa.D = D;
+  const TileGemmArgs ta{c->wqkv[l], c->xn, kpad(c->cfg, D.d) / 32, 3 * D.d / 32, c->rm.n_rows, rows_max};
+  HIP_TRY(launch_tile_qkv(ta, fa, c->fused_grid, s));
+  return CERBERUS_OK;
 }
 
 int run_tile_gate_up(const cerberus_ctx* c, int l, int rows_max, hipStream_t s) {
   const Dims& D = c->D;
   FusedGateUpArgs ga{};
-  ga.ssq = c->ssq; ga.nb = add_gain_blocks(D.d); ga.d = D.d; ga.eps = D.eps; ga.act = (bf16_t*)c->act; ga.lo_off = (size_t)c->R64 * D.Fpad; ga.Fpad = D.Fpad;
+  ga.ssq = c->ssq; ga.nb = add_gain_blocks(D.d, A_FRAG); ga.d = D.d; ga.eps = D.eps; ga.act = (bf16_t*)c->act; ga.lo_off = act_frag(c, rows_max) ? 0 : (size_t)c->R64 * D.Fpad; ga.Fpad = D.Fpad;
   const TileGemmArgs ta{c->wgu[l], c->xn, kpad(c->cfg, D.d) / 32, D.F / 16, c->rm.n_rows, rows_max};
   HIP_TRY(launch_tile_gate_up(ta, ga, c->fused_grid, s));
+  return CERBERUS_OK;
+}
+
+// O and down (layer GEMM `plan`) of such a launch: planes for the consumer, as many as the rows that are live call for
+int run_tile_planes(const cerberus_ctx* c, const GemmBatch& plan, size_t lda, int rows_max, GemmProb* launched, hipStream_t s) {
+  GemmProb P = plan.p[0];
+  P.out_rows = (int)align_up((size_t)rows_max, 64);
+  P.out = c->part;
+  const int room = (int)std::min<size_t>(c->max_split, c->part_floats / ((size_t)P.out_rows * P.N));
+  TileGemmArgs ta{P.W, P.A, P.K / 32, P.N / 32, c->rm.n_rows, rows_max};
+  ta.max_splits = P.S = tile_plane_splits(ta.pairs, ta.ksteps, c->fused_grid, room);
+  ta.splits_out = c->down_planes; P.S_dev = c->down_planes;
+  ta.lda = lda; ta.lo_off = P.lo_off;
+  HIP_TRY(launch_tile_planes(ta, P.out, (size_t)P.out_rows * P.N, c->fused_grid, s));
+  *launched = P;
   return CERBERUS_OK;
 }
 
@@ -668,16 +699,18 @@ int forward_rows(cerberus_ctx* c, const cerberus_state* st, int rows_max, const 
   // launches of up to 64 rows: QKV + RoPE + KV write and gate/up + SwiGLU as one whole-K launch each
   const bool fused = c->use_fused && D.dtype == CERBERUS_BF16 && rows_max <= 64 && c->fused_grid > 0 && c->act_split == 1;
   const bool fq = fused && c->ns_qkv > 0, fg = fused && c->ns_gu > 0;
-  const bool tg = tile_launches(c, rows_max) && D.F % 16 == 0;
+  const bool tq = tile_launches(c, rows_max, kTileAll), tg = tile_launches(c, rows_max, kTileGateUp) && D.F % 16 == 0;
   // QKV of a prompt pass of several pieces (see kPromptPieces)
   const int qkv_split = sh.piece && rows_max > kPromptPiece ? piece_split(c, c->p_qkv[0]) : 1;
   for (int l = 0; l < D.n_layers; ++l) {
     HIP_TRY(launch_add_gain(D, rm, c->x, prev ? prev->out : nullptr, prev ? prev->S : 0, prev ? prev->S_dev : nullptr,
-                            prev ? (size_t)prev->out_rows * prev->N : 0, c->attn_norm[l], c->xn, c->ssq, rows_max, s, fq ? A_FRAG64 : A_ROWS));
+                            prev ? (size_t)prev->out_rows * prev->N : 0, c->attn_norm[l], c->xn, c->ssq, rows_max, s, fq ? A_FRAG64 : tq ? A_FRAG : A_ROWS));
     GemmProb pq, po, pg;
     void* kv_layer = (unsigned char*)st->kv + (size_t)l * kv_layer_bytes;
     if (fq) {
       TRY(run_fused_qkv(c, l, kv_layer, s));
+    } else if (tq) {
+      TRY(run_tile_qkv(c, l, kv_layer, rows_max, s));
     } else {
       TRY(run_gemm(c, c->p_qkv[l], rm.n_rows, 0, rows_max, nullptr, 0, s, &pq, qkv_split));
       HIP_TRY(launch_rope_kv(D, rm, pq.out, pq.S, (size_t)pq.out_rows * pq.N, c->rope_cs, c->q, kv_layer, c->ktree, c->vtree,
@@ -692,7 +725,8 @@ int forward_rows(cerberus_ctx* c, const cerberus_state* st, int rows_max, const 
     aa.grid_x = att_items(D, sh.batch, sh.T, c->attn_chunk, attn_per_head(c, sh));   // every item gets a workgroup per head
     aa.rows_max = rows_max; aa.status = st->status;
     HIP_TRY(launch_attention(aa, D.dtype, c->use_mfma_attn, s));
-    TRY(run_gemm(c, c->p_o[l], rm.n_rows, 0, rows_max, nullptr, 0, s, &po));
+    if (tq) TRY(run_tile_planes(c, c->p_o[l], D.d, rows_max, &po, s));
+    else TRY(run_gemm(c, c->p_o[l], rm.n_rows, 0, rows_max, nullptr, 0, s, &po));
     HIP_TRY(launch_add_gain(D, rm, c->x, po.out, po.S, po.S_dev, (size_t)po.out_rows * po.N, c->ffn_norm[l], c->xn, c->ssq, rows_max, s,
                             fg ? A_FRAG64 : tg ? A_FRAG : A_ROWS));
     if (fg) {
@@ -703,7 +737,8 @@ int forward_rows(cerberus_ctx* c, const cerberus_state* st, int rows_max, const 
       TRY(run_gemm(c, c->p_gu[l], rm.n_rows, 0, rows_max, nullptr, 0, s, &pg));
       HIP_TRY(launch_swiglu(D, rm, pg.out, pg.S, (size_t)pg.out_rows * pg.N, c->act, c->ssq, rows_max, s));
     }
-    TRY(run_gemm(c, c->p_down[l], rm.n_rows, 0, rows_max, nullptr, 0, s, &pd));
+    if (tq) TRY(run_tile_planes(c, c->p_down[l], act_frag(c, rows_max) ? 0 : D.Fpad, rows_max, &pd, s));
+    else TRY(run_gemm(c, c->p_down[l], rm.n_rows, 0, rows_max, nullptr, 0, s, &pd));
     prev = &pd;
   }
   return CERBERUS_OK;
@@ -943,7 +978,9 @@ int cerberus_init(cerberus_ctx** out, const cerberus_config* cfg, const cerberus
   }
   if (D.dtype == CERBERUS_BF16) {
     HIP_INIT(init_team_gemm());
-    HIP_INIT(init_tile_gemm());
+    HIP_INIT(init_tile_qkv());
+    HIP_INIT(init_tile_gate_up());
+    HIP_INIT(init_tile_planes());
     std::vector<int> tq, tg;
     fused_tables(D, c->fused_grid, tq, c->ns_qkv, tg, c->ns_gu);     // the same tables the workspace was laid out for
     if (c->ns_qkv) HIP_INIT(hipMemcpy(c->slabs_qkv, tq.data(), tq.size() * sizeof(int), hipMemcpyHostToDevice));

@@ -52,10 +52,10 @@ hipError_t launch_embed(const Dims& D, const RowMap& rm, const void* embed, floa
 // S_dev: if set, the number of partial planes is read from there (at most S)
 hipError_t launch_add_rmsnorm(const Dims& D, const RowMap& rm, float* x, const float* part, int S, const int* S_dev, size_t pstride,
                               const float* gain, void* out, float* out_f32, float* tap, const int* src0, int rows_max, hipStream_t s);
-// residual add + x * gain + per-block sums of x^2 (the RMSNorm scalar is applied by the consumer of the next GEMM)
-int add_gain_blocks(int d);   // sums per row
 // How a GEMM input lies in memory: row-major planes, or MFMA A-fragment order (bf16; see FusedQkvArgs and TileGemmArgs)
 enum { A_ROWS = 0, A_FRAG64 = 1, A_FRAG = 2 };
+// residual add + x * gain + per-block sums of x^2 (the RMSNorm scalar is applied by the consumer of the next GEMM)
+int add_gain_blocks(int d, int order);   // sums per row
 hipError_t launch_add_gain(const Dims& D, const RowMap& rm, float* x, const float* part, int S, const int* S_dev, size_t pstride,
                            const float* gain, void* out, float* ssq, int rows_max, hipStream_t s, int order = A_ROWS);
 hipError_t launch_rope_kv(const Dims& D, const RowMap& rm, const float* part, int S, size_t pstride,
@@ -90,7 +90,7 @@ struct FusedGateUpArgs {
   int nb, d;
   float eps;
   RowMap rm;
-  bf16_t* act;              // [rows][Fpad] hi, lo plane lo_off later
+  bf16_t* act;              // [rows][Fpad] hi, lo plane lo_off later (launch_tile_gate_up, lo_off 0: fragment order, Fpad / 32 k-steps)
   size_t lo_off;
   int Fpad;
 };
@@ -98,16 +98,26 @@ hipError_t launch_qkv_rope(const FusedQkvArgs& a, int ns, int grid, hipStream_t 
 hipError_t launch_gate_up_swiglu(const FusedGateUpArgs& a, int ns, int grid, hipStream_t s);
 size_t fused_stream_pieces(int ns, int grid, int ksteps);   // 16-byte pieces of a stream-order weight copy
 hipError_t launch_pack_stream(const void* packed, void* dst, const int* table, int ns, int grid, int ksteps, hipStream_t s);
-// Whole-K GEMMs with fused epilogues for more rows (gemm_tile.hip, bf16 mode).
+// Whole-K GEMMs with fused epilogues for more rows (gemm_tile.h, bf16 mode).
 struct TileGemmArgs {
   const void* W;            // pre-tiled weights: fragment (slab, k-step) is 1 KB at (slab * ksteps + ks) * 1024
   const void* A;            // fragment (row tile, k-step, plane) is 1 KB at ((mt * ksteps + ks) * 2 + plane) * 1024 (A_FRAG)
   int ksteps, pairs;        // padded K / 32 (a multiple of 8); slab pairs of the launch
   const int* n_rows;        // device row count
   int rows_cap;             // upper bound of it
+  // launch_tile_planes
+  int max_splits;           // most k ranges
+  int* splits_out;          // how many the launch made is left here: planes for the consumer to sum
+  size_t lda, lo_off;       // if lda: A is row-major [rows][lda] instead, the lo plane lo_off elements later
 };
-hipError_t init_tile_gemm();   // once per device, before the first launch
-hipError_t launch_tile_gate_up(const TileGemmArgs& a, const FusedGateUpArgs& g, int grid, hipStream_t s);   // W, A, rows: of a
+hipError_t init_tile_qkv();       // each once per device, before the first launch
+hipError_t init_tile_gate_up();
+hipError_t init_tile_planes();
+int tile_plane_splits(int pairs, int ksteps, int grid, int most);   // most k ranges whatever the row count
+// out[k range][row][pairs * 32]
+hipError_t launch_tile_planes(const TileGemmArgs& a, float* out, size_t pstride, int grid, hipStream_t s);
+hipError_t launch_tile_qkv(const TileGemmArgs& a, const FusedQkvArgs& f, int grid, hipStream_t s);           // W, A, k-steps and rows: of a
+hipError_t launch_tile_gate_up(const TileGemmArgs& a, const FusedGateUpArgs& g, int grid, hipStream_t s);
 hipError_t launch_swiglu(const Dims& D, const RowMap& rm, const float* part, int S, size_t pstride, void* act,
                          const float* ssq, int rows_max, hipStream_t s);
 hipError_t launch_row_argmax(const Dims& D, const RowMap& rm, const float* part, int S, size_t pstride, int* g,

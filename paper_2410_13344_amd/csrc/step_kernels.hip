@@ -369,10 +369,9 @@ hipError_t launch_add_rmsnorm(const Dims& D, const RowMap& rm, float* x, const f
 // split-K partials (k_rope_kv, k_swiglu) forms 1 / sqrt(mean x^2 + eps) from those sums and scales.
 // Four workgroups per row at d = 4096 instead of one.
 // ---------------------------------------------------------------------------------------------
-// ORDER (bf16 only) A_FRAG64, A_FRAG: the GEMM input goes out in MFMA A-fragment order for the whole-K GEMMs: the 8 values of
-// row r at columns ks*32 + g*8.. form a 16-byte piece, number ((ks*2 + plane)*4 + r/16)*64 + r%16 + 16*g (64 rows in all) or
-// ((r/16*ksteps + ks)*2 + plane)*64 + r%16 + 16*g.
-template <typename T, int MAXS, int ORDER>
+// TILED (bf16 only): the GEMM input goes out in MFMA A-fragment order for the whole-K GEMMs: the 8 values of
+// row r at columns ks*32 + g*8.. form 16-byte piece ((ks*2 + plane)*4 + r/16)*64 + r%16 + 16*g, 64 rows in all.
+template <typename T, int MAXS, bool TILED>
 __global__ __launch_bounds__(256) void k_add_gain(float* __restrict__ x, const float* __restrict__ part, int S,
                                                   const int* __restrict__ S_dev, size_t pstride,
                                                   const float* __restrict__ gain, T* __restrict__ out, size_t lo_off,
@@ -393,18 +392,17 @@ __global__ __launch_bounds__(256) void k_add_gain(float* __restrict__ x, const f
     if (MAXS > 0) *reinterpret_cast<float4*>(xr) = v;
     ss = v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
     const float o[4] = {v.x * g.x, v.y * g.y, v.z * g.z, v.w * g.w};
-    if (ORDER != A_ROWS && sizeof(T) == 2) {
+    if (TILED && sizeof(T) == 2) {
       union { bf16_t h[4]; uint2 u; } hi, lo;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         hi.h[e] = f32_to_bf16(o[e]);
         lo.h[e] = f32_to_bf16(o[e] - bf16_to_f32(hi.h[e]));
       }
-      const size_t frag = ORDER == A_FRAG64 ? (size_t)(c >> 5) * 8 + (r >> 4) : ((size_t)(r >> 4) * (d >> 5) + (c >> 5)) * 2;   // of the hi plane
-      const size_t piece = frag * 64 + (r & 15) + 16 * ((c & 31) >> 3);
+      const size_t piece = ((size_t)(c >> 5) * 8 + (r >> 4)) * 64 + (r & 15) + 16 * ((c & 31) >> 3);   // hi plane; lo: + 4 * 64
       unsigned char* base = reinterpret_cast<unsigned char*>(out) + (c & 7) * 2;
       *reinterpret_cast<uint2*>(base + piece * 16) = hi.u;
-      *reinterpret_cast<uint2*>(base + (piece + (ORDER == A_FRAG64 ? 4 : 1) * 64) * 16) = lo.u;
+      *reinterpret_cast<uint2*>(base + (piece + 256) * 16) = lo.u;
     } else {
       st_a4(out + (size_t)r * d + c, lo_off, o);       // d % 4 == 0: aligned
     }
@@ -413,23 +411,86 @@ __global__ __launch_bounds__(256) void k_add_gain(float* __restrict__ x, const f
   if (threadIdx.x == 0) ssq[(size_t)r * nb + blockIdx.y] = ss;
 }
 
-int add_gain_blocks(int d) { return (d + 1023) / 1024; }
+// The same for launches of more than 64 rows whose next GEMM is a tile launch: fragments of (row tile, k-step, plane), 1 KB each
+// (A_FRAG).  A workgroup takes 16 rows x 256 columns, a wave one fragment at a time of both planes, lane = row + 16 * (columns / 8):
+// reads are whole lines of x and the partials, stores 1 KB in one piece.  A row per workgroup as above stores pieces of 8
+// bytes: 38 and 28 us for a layer's two launches at 1024 rows, 17 and 15 at 323; this way 21 and 21, 14 and 14.
+template <int MAXS>
+__global__ __launch_bounds__(512) void k_add_gain_frag(float* __restrict__ x, const float* __restrict__ part, int S,
+                                                        const int* __restrict__ S_dev, size_t pstride, const float* __restrict__ gain,
+                                                        uint4* __restrict__ out, float* __restrict__ ssq, const RowMap rm, int d) {
+  __shared__ float sh[8][16];
+  const int rows = *rm.n_rows, r0 = blockIdx.x * 16;
+  if (r0 >= rows) return;
+  if (S_dev) S = *S_dev;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int r = r0 + (lane & 15), ks = blockIdx.y * 8 + wave, c = ks * 32 + (lane >> 4) * 8;
+  float ss = 0.f;
+  if (r < rows && c < d) {
+    float* xr = x + (size_t)r * d + c;
+    union { bf16_t h[8]; uint4 u; } hi, lo;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      float4 P[MAXS > 0 ? MAXS : 1];
+#pragma unroll
+      for (int s = 0; s < MAXS; ++s)
+        if (s < S) P[s] = *reinterpret_cast<const float4*>(part + s * pstride + (size_t)r * d + c + q * 4);
+      float4 v = *reinterpret_cast<const float4*>(xr + q * 4);
+      const float4 g = *reinterpret_cast<const float4*>(gain + c + q * 4);
+#pragma unroll
+      for (int s = 0; s < MAXS; ++s)
+        if (s < S) { v.x += P[s].x; v.y += P[s].y; v.z += P[s].z; v.w += P[s].w; }
+      if (MAXS > 0) *reinterpret_cast<float4*>(xr + q * 4) = v;
+      ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+      const float o[4] = {v.x * g.x, v.y * g.y, v.z * g.z, v.w * g.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        hi.h[q * 4 + e] = f32_to_bf16(o[e]);
+        lo.h[q * 4 + e] = f32_to_bf16(o[e] - bf16_to_f32(hi.h[q * 4 + e]));
+      }
+    }
+    uint4* f = out + ((size_t)blockIdx.x * (d >> 5) + ks) * 128 + lane;
+    f[0] = hi.u;
+    f[64] = lo.u;
+  }
+  ss += __shfl_xor(ss, 16);
+  ss += __shfl_xor(ss, 32);
+  if (lane < 16) sh[wave][lane] = ss;
+  __syncthreads();
+  if (threadIdx.x < 16 && r0 + (int)threadIdx.x < rows) {
+    float t = 0.f;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) t += sh[w][threadIdx.x];
+    ssq[(size_t)(r0 + threadIdx.x) * gridDim.y + blockIdx.y] = t;
+  }
+}
+int add_gain_blocks(int d, int order) { return order == A_FRAG ? (d + 255) / 256 : (d + 1023) / 1024; }
 
 hipError_t launch_add_gain(const Dims& D, const RowMap& rm, float* x, const float* part, int S, const int* S_dev, size_t pstride,
                            const float* gain, void* out, float* ssq, int rows_max, hipStream_t s, int order) {
-  const dim3 grid(rows_max, add_gain_blocks(D.d));
   if (order != A_ROWS && (D.dtype == 0 || D.d % 32 || (order == A_FRAG64 && rows_max > 64))) return hipErrorInvalidValue;
-#define CERB_ARGS(T) x, part, S, S_dev, pstride, gain, (T*)out, sizeof(T) == 2 ? (size_t)D.R64 * D.d : 0, ssq, rm, D.d
-#define CERB_CALL(MS)                                                                                                        \
-  if (D.dtype == 0) hipLaunchKernelGGL((k_add_gain<float, MS, A_ROWS>), grid, dim3(256), 0, s, CERB_ARGS(float));            \
-  else if (order == A_FRAG64) hipLaunchKernelGGL((k_add_gain<bf16_t, MS, A_FRAG64>), grid, dim3(256), 0, s, CERB_ARGS(bf16_t)); \
-  else if (order == A_FRAG) hipLaunchKernelGGL((k_add_gain<bf16_t, MS, A_FRAG>), grid, dim3(256), 0, s, CERB_ARGS(bf16_t));  \
-  else hipLaunchKernelGGL((k_add_gain<bf16_t, MS, A_ROWS>), grid, dim3(256), 0, s, CERB_ARGS(bf16_t))
+  if (order == A_FRAG) {
+    const dim3 grid((rows_max + 15) / 16, add_gain_blocks(D.d, order));
+#define CERB_CALL(MS) hipLaunchKernelGGL((k_add_gain_frag<MS>), grid, dim3(512), 0, s, x, part, S, S_dev, pstride, gain, (uint4*)out, ssq, rm, D.d)
+    CERB_S_BUCKET(S, CERB_CALL);
+#undef CERB_CALL
+    return hipGetLastError();
+  }
+  const dim3 grid(rows_max, add_gain_blocks(D.d, order));
+#define CERB_CALL(MS)                                                                                                  \
+  if (D.dtype == 0)                                                                                                    \
+    hipLaunchKernelGGL((k_add_gain<float, MS, false>), grid, dim3(256), 0, s, x, part, S, S_dev, pstride, gain, (float*)out,  \
+                       (size_t)0, ssq, rm, D.d);                                                                       \
+  else if (order == A_FRAG64)                                                                                          \
+    hipLaunchKernelGGL((k_add_gain<bf16_t, MS, true>), grid, dim3(256), 0, s, x, part, S, S_dev, pstride, gain, (bf16_t*)out, \
+                       (size_t)D.R64 * D.d, ssq, rm, D.d);                                                             \
+  else                                                                                                                 \
+    hipLaunchKernelGGL((k_add_gain<bf16_t, MS, false>), grid, dim3(256), 0, s, x, part, S, S_dev, pstride, gain, (bf16_t*)out,\
+                       (size_t)D.R64 * D.d, ssq, rm, D.d)
   CERB_S_BUCKET(S, CERB_CALL);
 #undef CERB_CALL
   return hipGetLastError();
 }
-
 // 1 / sqrt(mean x^2 + eps) of row r from the block sums k_add_gain left (summed in block order)
 __device__ __forceinline__ float row_rms_scale(const float* __restrict__ ssq, int r, int nb, int d, float eps) {
   float ss = 0.f;
@@ -486,7 +547,7 @@ __global__ void k_rope_kv(const float* __restrict__ part, int S, size_t pstride,
 hipError_t launch_rope_kv(const Dims& D, const RowMap& rm, const float* part, int S, size_t pstride,
                           const float2* rope_cs, void* q, void* kv_layer, void* ktree, void* vtree, const float* ssq,
                           int rows_max, hipStream_t s) {
-  const int nb = add_gain_blocks(D.d);
+  const int nb = add_gain_blocks(D.d, A_ROWS);
   dim3 grid(rows_max, D.nH), block(D.dh / 2);
   if (D.dtype == 0)
     hipLaunchKernelGGL((k_rope_kv<float>), grid, block, 0, s, part, S, pstride, rope_cs, rm, (float*)q, (size_t)0,
@@ -546,7 +607,7 @@ __global__ __launch_bounds__(256) void k_swiglu4(const float* __restrict__ part,
 
 hipError_t launch_swiglu(const Dims& D, const RowMap& rm, const float* part, int S, size_t pstride, void* act,
                          const float* ssq, int rows_max, hipStream_t s) {
-  const int nb = add_gain_blocks(D.d);
+  const int nb = add_gain_blocks(D.d, A_ROWS);
   if (rows_max > 64 && D.F % 4 == 0 && D.Fpad % 4 == 0 && pstride % 4 == 0) {
     dim3 grid4(rows_max, (D.F / 4 + 255) / 256);
     if (D.dtype == 0) hipLaunchKernelGGL((k_swiglu4<float>), grid4, dim3(256), 0, s, part, S, pstride, (float*)act, (size_t)0, rm, D.F, D.Fpad, ssq, nb, D.d, D.eps);
