@@ -632,7 +632,11 @@ int run_fused_gate_up(const cerberus_ctx* c, int l, hipStream_t s) {
 
 // Launches of more than `above` rows that run on the tile kernel (see gemm_tile.h): above 64 rows gate/up with SwiGLU, above 128
 // QKV with RoPE and the KV write, O and down as well.
-constexpr int kTileGateUp = 64, kTileAll = 128;
+// Where the whole-K kernel of up to 64 rows has no room for gate/up's slabs (13B), from 17 rows on (13B step, split-K with its
+// SwiGLU launch / tile kernel: 64 rows 10264 / 9953 us, 20 rows 7637 / 7539, 4 rows 6705 / 6818).
+// The others start at 129 rows: at 121 rows QKV, O and down take 50 + 21 + 38 us a layer on the tile kernel, 39 + 8 (rotation) + 18 +
+// 36 before; at 129 live rows 57 + 23 + 41 against 50 + 7 + 78 for the two.
+constexpr int kTileGateUp = 64, kTileGateUpWide = 16, kTileAll = 128;
 bool tile_launches(const cerberus_ctx* c, int rows_max, int above) {
   return c->use_fused && c->cfg.dtype == CERBERUS_BF16 && c->act_split == 1 && c->fused_grid > 0 && rows_max > above && rows_max <= (c->fused_grid - 2) * 128;
 }
@@ -699,7 +703,7 @@ int forward_rows(cerberus_ctx* c, const cerberus_state* st, int rows_max, const 
   // launches of up to 64 rows: QKV + RoPE + KV write and gate/up + SwiGLU as one whole-K launch each
   const bool fused = c->use_fused && D.dtype == CERBERUS_BF16 && rows_max <= 64 && c->fused_grid > 0 && c->act_split == 1;
   const bool fq = fused && c->ns_qkv > 0, fg = fused && c->ns_gu > 0;
-  const bool tq = tile_launches(c, rows_max, kTileAll), tg = tile_launches(c, rows_max, kTileGateUp) && D.F % 16 == 0;
+  const bool tq = tile_launches(c, rows_max, kTileAll), tg = tile_launches(c, rows_max, c->ns_gu ? kTileGateUp : kTileGateUpWide) && D.F % 16 == 0;
   // QKV of a prompt pass of several pieces (see kPromptPieces)
   const int qkv_split = sh.piece && rows_max > kPromptPiece ? piece_split(c, c->p_qkv[0]) : 1;
   for (int l = 0; l < D.n_layers; ++l) {
@@ -1093,6 +1097,11 @@ int cerberus_bench_gemm(cerberus_ctx* ctx, int32_t kind, int32_t rows, void* str
     if (bytes) *bytes = f ? 1.0 : team ? 2.0 + tp.NT : 0.0;
     return CERBERUS_OK;
   }
+  const bool tile_all = tile_launches(ctx, rows, kTileAll), tile_gu = tile_launches(ctx, rows, ctx->ns_gu ? kTileGateUp : kTileGateUpWide) && D.F % 16 == 0;
+  if (kind >= 200 && kind <= 206) {   // query: ... as a launch of the tile kernel?
+    if (bytes) *bytes = kind == 202 ? tile_gu : kind <= 203 && tile_all;
+    return CERBERUS_OK;
+  }
   const bool head_kind = kind == 5 || kind == 6;
   if (kind < 0 || kind > 6) return fail(CERBERUS_ERR_ARG, "kind out of 0..6");
   if (rows < 1 || rows > (head_kind ? D.Bmax : D.Bmax * D.T)) return fail(CERBERUS_ERR_ARG, "rows out of range");
@@ -1113,6 +1122,16 @@ int cerberus_bench_gemm(cerberus_ctx* ctx, int32_t kind, int32_t rows, void* str
   } else if (kind == 2 && fused && ctx->ns_gu) {
     for (int l = 0; l < D.n_layers; ++l) TRY(run_fused_gate_up(ctx, l, s));
     total = (double)D.n_layers * ((double)2 * D.F * D.d + (double)rows * D.d * 2) * ctx->elem;
+  } else if (kind == 2 ? tile_gu : kind <= 3 && tile_all) {
+    // the tile kernel, likewise over the last step's row map and without the cache write
+    const GemmProb& P = (kind == 0 ? ctx->p_qkv : kind == 1 ? ctx->p_o : kind == 2 ? ctx->p_gu : ctx->p_down)[0].p[0];
+    GemmProb launched;
+    for (int l = 0; l < D.n_layers; ++l) {
+      if (kind == 0) TRY(run_tile_qkv(ctx, l, nullptr, rows, s));
+      else if (kind == 2) TRY(run_tile_gate_up(ctx, l, rows, s));
+      else TRY(run_tile_planes(ctx, (kind == 1 ? ctx->p_o : ctx->p_down)[l], kind == 1 ? D.d : act_frag(ctx, rows) ? 0 : D.Fpad, rows, &launched, s));
+    }
+    total = (double)D.n_layers * ((double)P.N * P.K + (double)rows * P.K * 2) * ctx->elem;
   } else if (kind <= 3) {
     const std::vector<GemmBatch>& v = kind == 0 ? ctx->p_qkv : kind == 1 ? ctx->p_o : kind == 2 ? ctx->p_gu : ctx->p_down;
     for (int l = 0; l < D.n_layers; ++l) TRY(run(v[l]));

@@ -48,7 +48,7 @@ struct RopeEpi {
       bf16_t* plane = (sec == 0 ? planes_q : sec == 1 ? planes_k : planes_v) + (size_t)r * d + col;
       st_a4(plane, e.f.lo_off, y0);
       st_a4(plane + gap, e.f.lo_off, y1);
-      if (sec > 0) {
+      if (sec > 0 && e.f.kv_layer) {   // (the benchmark hook has no cache to write to)
         bf16_t* cr = e.f.kv_layer + (((size_t)((sec - 1) * D.Bmax + seq[i]) * D.nH + h) * D.cap + crow[i]) * dh + j;
         union { bf16_t h[4]; uint2 u; } k0, k1;
 #pragma unroll
