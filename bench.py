@@ -449,7 +449,7 @@ def main() -> int:
         how = B.cerberus_bench_gemm(eng.ctx, 100 + kind, rows) if kind in (0, 2, 3, 4) else 0.0   # 1: whole-K fused, 2 + NT: team kernel
         fused_kind = kind in (0, 2) and how == 1.0
         tile = kind <= 3 and B.cerberus_bench_gemm(eng.ctx, 200 + kind, rows) == 1.0
-        gemm[kname]["kernel"] = "k_gemm_tile<%s>" % ("RopeEpi", "PlaneEpi", "SwigluEpi", "PlaneEpi")[kind] if tile else ("k_qkv_rope" if kind == 0 else "k_gate_up_swiglu") if fused_kind else "k_gemm_team<%d,false>" % int(how - 2) if how >= 2.0 else (
+        gemm[kname]["kernel"] = "k_gemm_tile<%s>" % ("RopeEpi", "PlaneEpi<true>", "SwigluEpi", "PlaneEpi<%s>" % ("true" if cfg["d_ffn"] % 256 else "false"))[kind] if tile else ("k_qkv_rope" if kind == 0 else "k_gate_up_swiglu") if fused_kind else "k_gemm_team<%d,false>" % int(how - 2) if how >= 2.0 else (
             "k_gemm_bf16<1,2,1,true>" if kind > 4 else "k_gemm_bf16_rows<1>" if rows > 256 and kind in (3, 4)
             else "k_gemm_bf16<4,2,1,%s>" % ("true" if rows <= 64 else "false"))
     # the roofline object covers the kernel of the layer stack that takes the most time in a step

@@ -671,7 +671,7 @@ int run_tile_planes(const cerberus_ctx* c, const GemmBatch& plan, size_t lda, in
   P.out = c->part;
   const int room = (int)std::min<size_t>(c->max_split, c->part_floats / ((size_t)P.out_rows * P.N));
   TileGemmArgs ta{P.W, P.A, P.K / 32, P.N / 32, c->rm.n_rows, rows_max};
-  ta.max_splits = P.S = tile_plane_splits(ta.pairs, ta.ksteps, c->fused_grid, room);
+  ta.max_splits = P.S = tile_plane_splits(ta.pairs, ta.ksteps, c->fused_grid, room, lda != 0);
   ta.splits_out = c->down_planes; P.S_dev = c->down_planes;
   ta.lda = lda; ta.lo_off = P.lo_off;
   HIP_TRY(launch_tile_planes(ta, P.out, (size_t)P.out_rows * P.N, c->fused_grid, s));

@@ -17,10 +17,13 @@
 // us of the 57 at 121 rows); above that the matrix cores at the clock the load leaves them (1024 rows without any loads:
 // 250-265 us).
 //
-// The matrix cores round a running sum towards zero with every product, so the error of a sum grows with its length, and a
+// The matrix cores round a running sum with every product, so the error of a sum grows with its length, and a
 // cached element whose sum is off by little moves by a whole step of bf16 now and then.  So every 8 k-steps the sums move
-// over to a second set of accumulators.  Only where a wave's tile is 3 or 4 x 3 there are no registers for a second set: gate/up,
-// whose sums leave nothing in a cache, then sums K in one piece, QKV takes fewer pairs per round.
+// over to a second set of accumulators.  A wave's tile of 3 or 4 x 3 has registers for a second set only where its slab fragments
+// are refilled in place and the addresses of its loads are scalar (kWide): gate/up, and O and down where A lies in fragments,
+// whose sums move over every 32 k-steps there.  The others have no such tiles: QKV takes fewer pairs per round, row-major A more
+// k ranges.  (Without a second set sums of 3670 to 6912 columns of down were off by 2.9e-7 to 5.3e-7 of the result where all
+// products are positive, the others by 1e-7.)
 //
 // The products are W A^T: a lane then holds four consecutive columns of one row, which go out as one store per plane.
 #pragma once
@@ -35,10 +38,22 @@ namespace {   // (a copy per source that includes this, each with kernels of its
 constexpr int kTileLds = 160 * 1024;
 constexpr int kMaxPairs = 12;   // of a round: three per wave of 2 x 4
 constexpr int kSumSteps = 8;    // k-steps of a sum
-constexpr int kMaxTwo = 8;      // row tiles x pairs of a wave that leave room for two sets of accumulators
+constexpr int kSumStepsWide = 32;   // ... on a tile of more than
+constexpr int kMaxTwo = 8;      // row tiles x pairs of a wave, which leave room for two sets of slab fragments
 
 __device__ __forceinline__ void tile_dma16(const char* p, unsigned lds_addr) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(p) : "memory", "m0");
+}
+// The same from a wave-uniform address and a lane's offset.  The wait states in front: a scalar register written by the vector
+// unit (v_readfirstlane, or v_readlane where the compiler reloads a spilled one) may be read as an address five wait states later
+// at the earliest, and the compiler does not see to that inside inline assembly.
+__device__ __forceinline__ void tile_dma16(const char* base, unsigned off, unsigned lds_addr) {
+  asm volatile("s_nop 4\n\ts_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(off), "s"(base) : "memory", "m0");
+}
+__device__ __forceinline__ const char* tile_uniform(const char* p) {
+  const unsigned long v = reinterpret_cast<unsigned long>(p);
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v), hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
+  return reinterpret_cast<const char*>(((unsigned long)hi << 32) | lo);
 }
 
 // Row tiles [m0/16, m0/16 + nmt) by pairs [p0, p0 + np) of the launch
@@ -61,26 +76,35 @@ __device__ __forceinline__ void tile_run(const TileGemmArgs& a, const TileJob& J
   const unsigned ldsb = (unsigned)(unsigned long)((__attribute__((address_space(3))) const unsigned char*)lds);
 
   // ---- pieces q * 8 + wave of a stage (past the last one: that one once more, into a slot nobody reads)
+  constexpr bool SADDR = Epi::kWide;                           // src: the wave's address; else the lane's
   const char* src[CW];
   unsigned step[CW];
   auto bases = [&](int rd) {
     int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    asm volatile("" : "+v"(lane), "+s"(wave));                 // (nothing of this is kept in registers from round to round)
+    asm volatile("" : "+v"(lane));                             // (nothing of this is kept in registers from round to round)
+    asm volatile("" : "+s"(wave));
 #pragma unroll
     for (int q = 0; q < CW; ++q) {
       const int p = min(q * 8 + wave, KC * P1 - 1), kc = KC == 2 && p >= P1 ? 1 : 0, r = p - kc * P1;
       if (r < 2 * J.nmt) {
-        if (Epi::kSplit && a.lda) {   // 64 bytes of each of 16 rows
+        if (Epi::kRows) {   // 64 bytes of each of 16 rows
           src[q] = reinterpret_cast<const char*>(a.A) + ((r & 1) * a.lo_off + (size_t)min(J.m0 + (r >> 1) * 16 + (lane & 15), J.m1 - 1) * a.lda + (J.ks0 + kc) * 32 + (lane >> 4) * 8) * 2;
           step[q] = KC * 64;
+          continue;
         } else {
-          src[q] = reinterpret_cast<const char*>(a.A) + lane * 16 + ((size_t)((size_t)(J.m0 / 16 + (r >> 1)) * a.ksteps + J.ks0 + kc) * 2 + (r & 1)) * 1024;
+          src[q] = reinterpret_cast<const char*>(a.A) + ((size_t)((size_t)(J.m0 / 16 + (r >> 1)) * a.ksteps + J.ks0 + kc) * 2 + (r & 1)) * 1024;
           step[q] = KC * 2048;
         }
       } else {
         const int pos = r - 2 * J.nmt, pair = min(J.p0 + rd * J.perr + (pos >> 1), J.p0 + J.np - 1);
-        src[q] = reinterpret_cast<const char*>(a.W) + lane * 16 + ((size_t)epi.slab(pair, pos & 1) * a.ksteps + J.ks0 + kc) * 1024;
+        src[q] = reinterpret_cast<const char*>(a.W) + ((size_t)epi.slab(pair, pos & 1) * a.ksteps + J.ks0 + kc) * 1024;
         step[q] = KC * 1024;
+      }
+      if constexpr (SADDR) {
+        src[q] = tile_uniform(src[q]);
+        step[q] = __builtin_amdgcn_readfirstlane(step[q]);
+      } else {
+        src[q] += lane * 16;
       }
     }
   };
@@ -89,7 +113,13 @@ __device__ __forceinline__ void tile_run(const TileGemmArgs& a, const TileJob& J
   auto issue = [&](auto wraps) {                               // wraps: the stage may be a round's last one
     const unsigned l0 = __builtin_amdgcn_readfirstlane(ldsb + ibuf * SB + wave * 1024);
 #pragma unroll
-    for (int q = 0; q < CW; ++q) tile_dma16(src[q], l0 + q * 8192);
+    for (int q = 0; q < CW; ++q) {
+      if constexpr (SADDR) {
+        tile_dma16(src[q], lane * 16, l0 + q * 8192);
+      } else {
+        tile_dma16(src[q], l0 + q * 8192);
+      }
+    }
     ibuf = ibuf + 1 == D ? 0 : ibuf + 1;
     if (left > 1) {
       --left;
@@ -117,14 +147,15 @@ __device__ __forceinline__ void tile_run(const TileGemmArgs& a, const TileJob& J
     constexpr int RT = decltype(rtc)::value, NQ = decltype(nqc)::value, NW = 2 * NQ;
     const u32x4_t* la = lds + lane + t0 * 128;
     const u32x4_t* lw = lds + lane + (2 * J.nmt + cg * 2) * 64;
-    constexpr bool TWO = RT * NQ <= kMaxTwo;                   // a second set of accumulators
-    f32x4_t acc[RT][NW], tot[TWO ? RT : 1][NW];
+    constexpr bool WIDE = RT * NQ > kMaxTwo;                   // slab fragments are refilled in place
+    constexpr int SUM = (WIDE ? kSumStepsWide : kSumSteps) / KC;
+    f32x4_t acc[RT][NW], tot[RT][NW];
 #pragma unroll
     for (int i = 0; i < RT; ++i)
 #pragma unroll
-      for (int j = 0; j < NW; ++j) acc[i][j] = tot[TWO ? i : 0][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    int sum_left = kSumSteps / KC;
-    u32x4_t w[2][NW], fa[2][2];                                // this k-step's slabs and the next one's; a row tile and the next
+      for (int j = 0; j < NW; ++j) acc[i][j] = tot[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    int sum_left = SUM;
+    u32x4_t w[WIDE ? 1 : 2][NW], fa[2][2];                     // this k-step's slabs and the next one's; a row tile and the next
     auto rdw = [&](u32x4_t (&d)[NW], const u32x4_t* s, int j) { d[j] = s[(j >> 1) * (WC * 128) + (j & 1) * 64]; };
     const unsigned p1 = P1 * 64;
     for (int st = 0; st < nst; st += (KC == 1 ? 2 : 1)) {      // two k-steps per trip
@@ -151,37 +182,38 @@ __device__ __forceinline__ void tile_run(const TileGemmArgs& a, const TileJob& J
           const u32x4_t* nx = i + 1 < RT ? ca + (i + 1) * 128 : na;
           fa[cur ^ 1][0] = nx[0];
           fa[cur ^ 1][1] = nx[64];
+          if constexpr (!WIDE) {
 #pragma unroll
-          for (int j = i * NW / RT; j < (i + 1) * NW / RT; ++j) rdw(w[h ^ 1], nw, j);
+            for (int j = i * NW / RT; j < (i + 1) * NW / RT; ++j) rdw(w[h ^ 1], nw, j);
+          }
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int j = 0; j < NW; ++j) {
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, w[h][j]), __builtin_bit_cast(bf16x8_t, fa[cur][0]), acc[i][j], 0, 0, 0);
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, w[h][j]), __builtin_bit_cast(bf16x8_t, fa[cur][1]), acc[i][j], 0, 0, 0);
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, w[WIDE ? 0 : h][j]), __builtin_bit_cast(bf16x8_t, fa[cur][0]), acc[i][j], 0, 0, 0);
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, w[WIDE ? 0 : h][j]), __builtin_bit_cast(bf16x8_t, fa[cur][1]), acc[i][j], 0, 0, 0);
+            if constexpr (WIDE) {
+              if (i == RT - 1) rdw(w[0], nw, j);               // (its last product of this k-step is on its way)
+            }
             __builtin_amdgcn_sched_barrier(0);                 // (hi and lo of an accumulator back to back: 2-4 % less at 323 and 1024 rows)
           }
         }
       }
-      if constexpr (TWO) {
-        sum_left -= KC == 1 ? 2 : 1;
-        if (sum_left == 0) {
-          sum_left = kSumSteps / KC;
+      sum_left -= KC == 1 ? 2 : 1;
+      if (sum_left == 0) {
+        sum_left = SUM;
 #pragma unroll
-          for (int i = 0; i < RT; ++i)
+        for (int i = 0; i < RT; ++i)
 #pragma unroll
-            for (int j = 0; j < NW; ++j) {
-              tot[i][j] += acc[i][j];
-              acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-            }
-        }
+          for (int j = 0; j < NW; ++j) {
+            tot[i][j] += acc[i][j];
+            acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+          }
       }
     }
-    if constexpr (TWO) {
 #pragma unroll
-      for (int i = 0; i < RT; ++i)
+    for (int i = 0; i < RT; ++i)
 #pragma unroll
-        for (int j = 0; j < NW; ++j) tot[i][j] += acc[i][j];
-    }
+      for (int j = 0; j < NW; ++j) tot[i][j] += acc[i][j];
     // a lane holds row t * 16 + (lane & 15), columns (lane >> 4) * 4 .. + 3 of a slab
     int ln = lane;
     asm volatile("" : "+v"(ln));                               // (keeps the address arithmetic out of the loop)
@@ -192,16 +224,17 @@ __device__ __forceinline__ void tile_run(const TileGemmArgs& a, const TileJob& J
       const int r = J.m0 + (t0 + i) * 16 + (ln & 15);
       if (r < J.m1) {
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) row.store(epi, i, r, J.split, J.p0 + rd * J.perr + cg + WC * q, (ln >> 4) * 4, TWO ? tot[TWO ? i : 0][2 * q] : acc[i][2 * q], TWO ? tot[TWO ? i : 0][2 * q + 1] : acc[i][2 * q + 1]);
+        for (int q = 0; q < NQ; ++q) row.store(epi, i, r, J.split, J.p0 + rd * J.perr + cg + WC * q, (ln >> 4) * 4, tot[i][2 * q], tot[i][2 * q + 1]);
       }
     }
+    __builtin_amdgcn_wave_barrier();                           // (lanes meet here, not where the cases below do: what they share stays in scalar registers)
   };
   for (int rd = 0; rd < J.rounds; ++rd) {
     const int nq = (min(J.np - rd * J.perr, J.perr) - cg + WC - 1) / WC;   // pairs cg, cg + WC, ... of the round (at most 0: none)
     // (the fewest row tiles and pairs of a workgroup with such a wave, and the case is compiled only where they can occur)
 #define TILE_CASE(R, Q)                                                                                                      \
   case R * 4 + Q:                                                                                                            \
-    if constexpr (R <= 8 / WR && (Epi::kOneSum || R * Q <= kMaxTwo) && KC * 2 * (WR * (R - 1) + 1 + WC * (Q - 1) + 1) <= 8 * CW) {                                 \
+    if constexpr (R <= 8 / WR && (Epi::kWide || R * Q <= kMaxTwo) && KC * 2 * (WR * (R - 1) + 1 + WC * (Q - 1) + 1) <= 8 * CW) {                                 \
       multiply(std::integral_constant<int, R>{}, std::integral_constant<int, Q>{}, rd);                                      \
       break;                                                                                                                 \
     }                                                                                                                        \
@@ -219,9 +252,10 @@ __device__ __forceinline__ void tile_run(const TileGemmArgs& a, const TileJob& J
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");            // nothing of this wave is in flight when it ends
 }
 
-// k ranges of a launch with `slots` workgroups per row block: as many as leave a workgroup about eight pairs
-__host__ __device__ __forceinline__ int tile_splits(int pairs, int ksteps, int slots, int most) {
-  const int groups = (pairs + 7) / 8, S = (2 * slots + groups) / (2 * groups);
+// k ranges of a launch with `slots` workgroups per row block: as many as leave a workgroup about eight pairs, and no more than
+// that where its waves have no room for wide tiles
+__host__ __device__ __forceinline__ int tile_splits(int pairs, int ksteps, int slots, int most, bool wide) {
+  const int groups = (pairs + 7) / 8, S = wide ? (2 * slots + groups) / (2 * groups) : slots / groups;
   return max(1, min(min(S, most), min(slots, ksteps / 8)));
 }
 
@@ -238,7 +272,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // consecutive workgroup ids go to the 8 XCDs in turn: logical ids put the row blocks of a column group on one XCD
   const int G = gridDim.x, L = ((int)blockIdx.x & 7) * (G >> 3) + ((int)blockIdx.x >> 3);
   const int slot = L / RB, rb = L - slot * RB;
-  const int S = Epi::kSplit ? tile_splits(a.pairs, a.ksteps, G / RB, a.max_splits) : 1;
+  const int S = Epi::kSplit ? tile_splits(a.pairs, a.ksteps, G / RB, a.max_splits, Epi::kWide) : 1;
   if (Epi::kSplit && blockIdx.x == 0 && threadIdx.x == 0) *a.splits_out = S;
   const int groups = G / RB / S, split = slot / groups, grp = slot - split * groups;   // (the groups of a k range share A)
   TileJob J;
@@ -252,9 +286,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   J.split = split;
   J.ks0 = a.ksteps / 8 * split / S * 8;
   J.nks = a.ksteps / 8 * (split + 1) / S * 8 - J.ks0;
-  const int most = !Epi::kOneSum && J.nmt > 4 ? 8 : kMaxPairs;
+  const int most = !Epi::kWide && J.nmt > 4 ? 8 : kMaxPairs;
   J.rounds = (J.np + most - 1) / most;
   J.perr = (J.np + J.rounds - 1) / J.rounds;
+  // (the quotients above come out of vector registers)
+  for (int* v : {&J.m0, &J.m1, &J.nmt, &J.p0, &J.np, &J.rounds, &J.perr, &J.ks0, &J.nks, &J.split}) *v = __builtin_amdgcn_readfirstlane(*v);
   // a k-step's reads from LDS: 2 x 4 waves read the row tiles four times and the slabs twice, 4 x 2 the other way round
   const bool tall = J.perr <= 6 && J.nmt >= J.perr;
   const int P1 = 2 * (J.nmt + J.perr);                        // pieces per k-step, at most 40

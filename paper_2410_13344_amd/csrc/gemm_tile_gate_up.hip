@@ -8,7 +8,8 @@ namespace {
 // gate and up of the same columns: act = silu(g) * u
 struct SwigluEpi {
   static constexpr bool kSplit = false;
-  static constexpr bool kOneSum = true;    // the largest tiles may sum K in one piece
+  static constexpr bool kRows = false;
+  static constexpr bool kWide = true;
   const float* ssq;
   int nb, d, fslabs, Fpad;
   float eps;

@@ -5,9 +5,10 @@ namespace cerb {
 
 namespace {
 
-// fp32 planes, one per k range, for the consumer to sum
+// fp32 planes, one per k range, for the consumer to sum.  ROWS: A is row-major, with the addresses of its lanes in vector registers
+template <bool ROWS>
 struct PlaneEpi {
-  static constexpr bool kSplit = true, kOneSum = true;
+  static constexpr bool kSplit = true, kRows = ROWS, kWide = !ROWS;
   float* out;
   size_t pstride;
   int N;
@@ -25,13 +26,17 @@ struct PlaneEpi {
 
 }  // namespace
 
-hipError_t init_tile_planes() { return tile_init<PlaneEpi>(); }
+hipError_t init_tile_planes() {
+  const hipError_t e = tile_init<PlaneEpi<false>>();
+  return e == hipSuccess ? tile_init<PlaneEpi<true>>() : e;
+}
 
-int tile_plane_splits(int pairs, int ksteps, int grid, int most) { return tile_splits(pairs, ksteps, grid, most); }
+int tile_plane_splits(int pairs, int ksteps, int grid, int most, bool rows) { return tile_splits(pairs, ksteps, grid, most, !rows); }
 
 hipError_t launch_tile_planes(const TileGemmArgs& a, float* out, size_t pstride, int grid, hipStream_t s) {
   if (a.max_splits < 1 || !a.splits_out || pstride % 4) return hipErrorInvalidValue;
-  return tile_launch(a, PlaneEpi{out, pstride, a.pairs * 32}, grid, s);
+  if (a.lda) return tile_launch(a, PlaneEpi<true>{out, pstride, a.pairs * 32}, grid, s);
+  return tile_launch(a, PlaneEpi<false>{out, pstride, a.pairs * 32}, grid, s);
 }
 
 }  // namespace cerb

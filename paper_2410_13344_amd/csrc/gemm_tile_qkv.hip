@@ -9,7 +9,8 @@ namespace {
 // heads, two neighbouring v slabs
 struct RopeEpi {
   static constexpr bool kSplit = false;
-  static constexpr bool kOneSum = false;
+  static constexpr bool kRows = false;
+  static constexpr bool kWide = false;
   FusedQkvArgs f;
   __device__ __forceinline__ int slab(int pair, int which) const {
     const int spd = f.D.d / 16, sph = f.D.dh / 16, sec = pair / (spd / 2), t = pair - sec * (spd / 2);

@@ -113,7 +113,7 @@ struct TileGemmArgs {
 hipError_t init_tile_qkv();       // each once per device, before the first launch
 hipError_t init_tile_gate_up();
 hipError_t init_tile_planes();
-int tile_plane_splits(int pairs, int ksteps, int grid, int most);   // most k ranges whatever the row count
+int tile_plane_splits(int pairs, int ksteps, int grid, int most, bool rows);   // most k ranges whatever the row count; rows: A is row-major
 // out[k range][row][pairs * 32]
 hipError_t launch_tile_planes(const TileGemmArgs& a, float* out, size_t pstride, int grid, hipStream_t s);
 hipError_t launch_tile_qkv(const TileGemmArgs& a, const FusedQkvArgs& f, int grid, hipStream_t s);           // W, A, k-steps and rows: of a

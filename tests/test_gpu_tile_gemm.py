@@ -77,3 +77,43 @@ def test_a_wide_qkv_runs_in_rounds():
         mm = H.kv_mismatch(got[2][b].double().cpu().numpy(), want[2][b].double().cpu().numpy(), TOL)
         assert mm is None, (b, mm)
     pair.engine.close()
+
+
+@pytest.mark.parametrize("model,tree,batch", [("7b", "p63", 11), ("7b", "rand100s1k6", 11), ("7b", "p63", 16), ("13b", "rand100s1k6", 6), ("13b", "p63", 16)])
+def test_sums_of_the_down_projection_stay_short(model, tree, batch):
+    """A projection of known result with all its products positive, K = 11008 and 13824: token rows of one constant, FFN
+    activations of one constant (the gate's exponential underflows), random positive weights.  A sum rounds its running value with
+    every product, so what a column is off by shows how many products it was summed over in one piece: n roundings of at most
+    half a unit, each of a value no larger than the result, have a standard deviation below 2^-24 sqrt(n / 3).  The 54 sums of 8
+    k-steps, or the sums of 32 with 64 roundings of a fifth of the result or less, the planes, the residual and the norm count
+    for fewer than 55; sums of 3670 to 6912 columns in one piece have 230 to 432."""
+    cfg = synth.make_config(model, n_layers=1, vocab=256, n_cerb_heads=4, n_resblocks=1, special_block=-1, topk=6)
+    d, F, e = cfg["d_model"], cfg["d_ffn"], 1.2421875                    # (e: eight significant bits, exact in bf16)
+    W = synth.make_weights(cfg, seed=0, dtype=torch.bfloat16, device="cuda")
+    layer = W["layers"][0]
+    for t in (W["embed"], W["final_norm"], layer["attn_norm"], layer["ffn_norm"]):
+        t.fill_(1.0)
+    W["embed"].mul_(e)
+    for name in ("wqkv", "wo", "w_gate_up"):
+        layer[name].zero_()                                              # attention adds nothing
+    layer["w_gate_up"][:F, 0], layer["w_gate_up"][F:, 0] = 32.0, e / 32  # silu(32) = 32 to the last bit
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    layer["w_down"].copy_((torch.rand(d, F, device="cuda", generator=g) + 1.0) * 2.0 ** -9)
+    layer["w_down"][0] = 0                                               # column 0 stays at e: what the others are measured by
+    parent, rank = synth.make_tree(tree, cfg["n_cerb_heads"])
+    engine = B.Engine(cfg, W, parent, rank, B.CERBERUS_BF16, batch, 256)
+    taps = B.DeviceTaps(cfg, batch, len(parent))
+    engine.set_taps(taps)
+    st = engine.new_state()
+    engine.verify_step(st, batch)
+    torch.cuda.synchronize()
+    assert int(st.status.abs().sum()) == 0
+    h = taps.h_last.double()
+    want = layer["w_down"][1:].double().sum(1)
+    off = (h[:, 1:] / h[:, :1] - 1.0) / want[None]                       # one constant, but for the error of the sums
+    off = off / off.median() - 1.0
+    slabs = off[:, 15:].reshape(off.shape[0], -1, 16).square().mean((0, 2)).sqrt()
+    print(f"{model}, {off.shape[0]} rows: largest error of a slab {float(slabs.max()):.2e}", flush=True)
+    assert float(slabs.max()) <= 2.0 ** -24 * (55 / 3) ** 0.5
+    engine.close()

@@ -79,7 +79,7 @@ def test_the_scan_sees_a_stale_base():
     assert not stale_bases("v_readfirstlane_b32 s4, v0\ns_add_u32 s4, s4, s8\n" + late.split("\n", 1)[1])
 
 
-@pytest.mark.parametrize("source", ["gemm_team.hip", "attention.hip"])
+@pytest.mark.parametrize("source", ["gemm_team.hip", "gemm_tile_gate_up.hip", "gemm_tile_planes.hip", "attention.hip"])
 def test_inline_loads_wait_for_their_scalar_base(source):
     cmd = [build.hipcc(), *build.FLAGS, "-S", "--offload-device-only", os.path.join(build.CSRC, source), "-o", "-"]
     listing = subprocess.run(cmd, capture_output=True, text=True, check=True).stdout
