@@ -232,8 +232,8 @@ int cerberus_set_param(cerberus_ctx *ctx, const char *name, int32_t value);
  * one kind exactly as a step launches them for `rows` rows, reading whatever the activation
  * buffers hold; results land in scratch.  kind: 0 QKV, 1 attention output, 2 FFN gate/up,
  * 3 FFN down, 4 LM head, 5 head Resblocks (all stages), 6 head FC.  Where a step of `rows` rows runs the
- * QKV or gate/up projection as a whole-K fused launch, so does the hook (over the rows of the last
- * step's row map, which must have had that many; without the cache write).  Writes to *bytes (HOST, may
+ * QKV or gate/up projection as a whole-K fused launch of up to 64 rows, so does the hook (over the rows of the
+ * last step's row map, which must have had that many); the QKV projection leaves its cache write out.  Writes to *bytes (HOST, may
  * be NULL) the weight + activation bytes the launches read once each.  kind + 100 launches nothing
  * and writes 1.0 if a step of `rows` rows runs that kind as a whole-K fused launch of up to 64 rows, 2.0 + row tiles if the
  * split-K plan hands it to the team kernel, else 0.0; kind + 200 writes 1.0 if it runs on the tile kernel, whatever

@@ -645,32 +645,33 @@ bool tile_launches(const cerberus_ctx* c, int rows_max, int above) {
 // from init on and nobody writes it, which holds as long as every launch lays the rows out alike.)
 bool act_frag(const cerberus_ctx* c, int rows_max) { return tile_launches(c, rows_max, kTileAll) && c->D.F == c->D.Fpad; }
 
-int run_tile_qkv(const cerberus_ctx* c, int l, void* kv_layer, int rows_max, hipStream_t s) {
+// n_rows of the three: the device row count, or null for rows_max rows
+int run_tile_qkv(const cerberus_ctx* c, int l, void* kv_layer, const int* n_rows, int rows_max, hipStream_t s) {
   const Dims& D = c->D;
   FusedQkvArgs fa{};
   fa.ssq = c->ssq; fa.nb = add_gain_blocks(D.d, A_FRAG); fa.rope_cs = c->rope_cs; fa.rm = c->rm; fa.q = (bf16_t*)c->q; fa.kv_layer = (bf16_t*)kv_layer;
   fa.ktree = (bf16_t*)c->ktree; fa.vtree = (bf16_t*)c->vtree; fa.lo_off = (size_t)c->R64 * D.d; fa.D = D;
-  const TileGemmArgs ta{c->wqkv[l], c->xn, kpad(c->cfg, D.d) / 32, 3 * D.d / 32, c->rm.n_rows, rows_max};
+  const TileGemmArgs ta{c->wqkv[l], c->xn, kpad(c->cfg, D.d) / 32, 3 * D.d / 32, n_rows, rows_max};
   HIP_TRY(launch_tile_qkv(ta, fa, c->fused_grid, s));
   return CERBERUS_OK;
 }
 
-int run_tile_gate_up(const cerberus_ctx* c, int l, int rows_max, hipStream_t s) {
+int run_tile_gate_up(const cerberus_ctx* c, int l, const int* n_rows, int rows_max, hipStream_t s) {
   const Dims& D = c->D;
   FusedGateUpArgs ga{};
   ga.ssq = c->ssq; ga.nb = add_gain_blocks(D.d, A_FRAG); ga.d = D.d; ga.eps = D.eps; ga.act = (bf16_t*)c->act; ga.lo_off = act_frag(c, rows_max) ? 0 : (size_t)c->R64 * D.Fpad; ga.Fpad = D.Fpad;
-  const TileGemmArgs ta{c->wgu[l], c->xn, kpad(c->cfg, D.d) / 32, D.F / 16, c->rm.n_rows, rows_max};
+  const TileGemmArgs ta{c->wgu[l], c->xn, kpad(c->cfg, D.d) / 32, D.F / 16, n_rows, rows_max};
   HIP_TRY(launch_tile_gate_up(ta, ga, c->fused_grid, s));
   return CERBERUS_OK;
 }
 
 // O and down (layer GEMM `plan`) of such a launch: planes for the consumer, as many as the rows that are live call for
-int run_tile_planes(const cerberus_ctx* c, const GemmBatch& plan, size_t lda, int rows_max, GemmProb* launched, hipStream_t s) {
+int run_tile_planes(const cerberus_ctx* c, const GemmBatch& plan, size_t lda, const int* n_rows, int rows_max, GemmProb* launched, hipStream_t s) {
   GemmProb P = plan.p[0];
   P.out_rows = (int)align_up((size_t)rows_max, 64);
   P.out = c->part;
   const int room = (int)std::min<size_t>(c->max_split, c->part_floats / ((size_t)P.out_rows * P.N));
-  TileGemmArgs ta{P.W, P.A, P.K / 32, P.N / 32, c->rm.n_rows, rows_max};
+  TileGemmArgs ta{P.W, P.A, P.K / 32, P.N / 32, n_rows, rows_max};
   ta.max_splits = P.S = tile_plane_splits(ta.pairs, ta.ksteps, c->fused_grid, room, lda != 0);
   ta.splits_out = c->down_planes; P.S_dev = c->down_planes;
   ta.lda = lda; ta.lo_off = P.lo_off;
@@ -714,7 +715,7 @@ int forward_rows(cerberus_ctx* c, const cerberus_state* st, int rows_max, const 
     if (fq) {
       TRY(run_fused_qkv(c, l, kv_layer, s));
     } else if (tq) {
-      TRY(run_tile_qkv(c, l, kv_layer, rows_max, s));
+      TRY(run_tile_qkv(c, l, kv_layer, rm.n_rows, rows_max, s));
     } else {
       TRY(run_gemm(c, c->p_qkv[l], rm.n_rows, 0, rows_max, nullptr, 0, s, &pq, qkv_split));
       HIP_TRY(launch_rope_kv(D, rm, pq.out, pq.S, (size_t)pq.out_rows * pq.N, c->rope_cs, c->q, kv_layer, c->ktree, c->vtree,
@@ -729,19 +730,19 @@ int forward_rows(cerberus_ctx* c, const cerberus_state* st, int rows_max, const 
     aa.grid_x = att_items(D, sh.batch, sh.T, c->attn_chunk, attn_per_head(c, sh));   // every item gets a workgroup per head
     aa.rows_max = rows_max; aa.status = st->status;
     HIP_TRY(launch_attention(aa, D.dtype, c->use_mfma_attn, s));
-    if (tq) TRY(run_tile_planes(c, c->p_o[l], D.d, rows_max, &po, s));
+    if (tq) TRY(run_tile_planes(c, c->p_o[l], D.d, rm.n_rows, rows_max, &po, s));
     else TRY(run_gemm(c, c->p_o[l], rm.n_rows, 0, rows_max, nullptr, 0, s, &po));
     HIP_TRY(launch_add_gain(D, rm, c->x, po.out, po.S, po.S_dev, (size_t)po.out_rows * po.N, c->ffn_norm[l], c->xn, c->ssq, rows_max, s,
                             fg ? A_FRAG64 : tg ? A_FRAG : A_ROWS));
     if (fg) {
       TRY(run_fused_gate_up(c, l, s));
     } else if (tg) {
-      TRY(run_tile_gate_up(c, l, rows_max, s));
+      TRY(run_tile_gate_up(c, l, rm.n_rows, rows_max, s));
     } else {
       TRY(run_gemm(c, c->p_gu[l], rm.n_rows, 0, rows_max, nullptr, 0, s, &pg));
       HIP_TRY(launch_swiglu(D, rm, pg.out, pg.S, (size_t)pg.out_rows * pg.N, c->act, c->ssq, rows_max, s));
     }
-    if (tq) TRY(run_tile_planes(c, c->p_down[l], act_frag(c, rows_max) ? 0 : D.Fpad, rows_max, &pd, s));
+    if (tq) TRY(run_tile_planes(c, c->p_down[l], act_frag(c, rows_max) ? 0 : D.Fpad, rm.n_rows, rows_max, &pd, s));
     else TRY(run_gemm(c, c->p_down[l], rm.n_rows, 0, rows_max, nullptr, 0, s, &pd));
     prev = &pd;
   }
@@ -1123,13 +1124,14 @@ int cerberus_bench_gemm(cerberus_ctx* ctx, int32_t kind, int32_t rows, void* str
     for (int l = 0; l < D.n_layers; ++l) TRY(run_fused_gate_up(ctx, l, s));
     total = (double)D.n_layers * ((double)2 * D.F * D.d + (double)rows * D.d * 2) * ctx->elem;
   } else if (kind == 2 ? tile_gu : kind <= 3 && tile_all) {
-    // the tile kernel, likewise over the last step's row map and without the cache write
+    // the tile kernel over `rows` rows, whatever the last step had (sequences and positions, which the QKV epilogue reads, are those
+    // of its row map, zero where no step has been); without the cache write
     const GemmProb& P = (kind == 0 ? ctx->p_qkv : kind == 1 ? ctx->p_o : kind == 2 ? ctx->p_gu : ctx->p_down)[0].p[0];
     GemmProb launched;
     for (int l = 0; l < D.n_layers; ++l) {
-      if (kind == 0) TRY(run_tile_qkv(ctx, l, nullptr, rows, s));
-      else if (kind == 2) TRY(run_tile_gate_up(ctx, l, rows, s));
-      else TRY(run_tile_planes(ctx, (kind == 1 ? ctx->p_o : ctx->p_down)[l], kind == 1 ? D.d : act_frag(ctx, rows) ? 0 : D.Fpad, rows, &launched, s));
+      if (kind == 0) TRY(run_tile_qkv(ctx, l, nullptr, nullptr, rows, s));
+      else if (kind == 2) TRY(run_tile_gate_up(ctx, l, nullptr, rows, s));
+      else TRY(run_tile_planes(ctx, (kind == 1 ? ctx->p_o : ctx->p_down)[l], kind == 1 ? D.d : act_frag(ctx, rows) ? 0 : D.Fpad, nullptr, rows, &launched, s));
     }
     total = (double)D.n_layers * ((double)P.N * P.K + (double)rows * P.K * 2) * ctx->elem;
   } else if (kind <= 3) {

@@ -262,7 +262,7 @@ __host__ __device__ __forceinline__ int tile_splits(int pairs, int ksteps, int s
 template <typename Epi>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gemm_tile(const TileGemmArgs a, const Epi epi) {
   extern __shared__ __attribute__((aligned(16))) u32x4_t tile_lds[];
-  const int rows = min(*a.n_rows, a.rows_cap);
+  const int rows = a.n_rows ? min(*a.n_rows, a.rows_cap) : a.rows_cap;
   if (rows <= 0) return;
   // Row blocks: one up to 64 rows, else two or as many as 128 rows each take.  gate/up of the 7B shape, one and two blocks: 64
   // rows 45.6 / 48.9 us, 121 rows 72.6 / 57.4 (the slabs of two workgroups share a fetch from HBM, and 64 rows make stages of

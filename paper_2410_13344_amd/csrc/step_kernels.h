@@ -103,7 +103,7 @@ struct TileGemmArgs {
   const void* W;            // pre-tiled weights: fragment (slab, k-step) is 1 KB at (slab * ksteps + ks) * 1024
   const void* A;            // fragment (row tile, k-step, plane) is 1 KB at ((mt * ksteps + ks) * 2 + plane) * 1024 (A_FRAG)
   int ksteps, pairs;        // padded K / 32 (a multiple of 8); slab pairs of the launch
-  const int* n_rows;        // device row count
+  const int* n_rows;        // device row count; null: rows_cap rows
   int rows_cap;             // upper bound of it
   // launch_tile_planes
   int max_splits;           // most k ranges

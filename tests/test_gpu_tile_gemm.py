@@ -117,3 +117,24 @@ def test_sums_of_the_down_projection_stay_short(model, tree, batch):
     print(f"{model}, {off.shape[0]} rows: largest error of a slab {float(slabs.max()):.2e}", flush=True)
     assert float(slabs.max()) <= 2.0 ** -24 * (55 / 3) ** 0.5
     engine.close()
+
+
+@pytest.mark.parametrize("kind,columns,least", [(0, 768, 1), (1, 256, 4), (2, 688, 1), (3, 256, 4)])
+def test_benchmark_hook_runs_the_rows_it_is_asked_for(kind, columns, least):
+    """192 rows asked for after a step that had three: the launch still reads and writes all of them, as the bytes it reports say.
+    Nearly every byte of a value changes where a buffer takes other results, so `least` bytes per output element of half
+    of the rows are a lower bound, three rows' worth of up to eight planes far below it."""
+    pair = H.Pair("tiny", B.CERBERUS_BF16, "p63", seed=9, max_batch=3, kv_capacity=256, topk=10)
+    st = pair.engine.new_state()
+    st.cand.copy_(synth.make_candidates(pair.cfg, 3, seed=4))
+    assert B.cerberus_bench_gemm(pair.engine.ctx, 200 + kind, 192) == 1.0           # on the tile kernel
+    pair.engine.verify_step(st, 3)
+    pair.engine.ar_step(st, 3)
+    torch.cuda.synchronize()
+    before = pair.engine.workspace.clone()
+    B.cerberus_bench_gemm(pair.engine.ctx, kind, 192)
+    torch.cuda.synchronize()
+    changed = int((pair.engine.workspace != before).sum())
+    print(f"kind {kind}: {changed} bytes changed", flush=True)
+    assert changed >= 96 * columns * least
+    pair.engine.close()
