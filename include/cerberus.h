@@ -235,9 +235,8 @@ int cerberus_set_param(cerberus_ctx *ctx, const char *name, int32_t value);
  * QKV or gate/up projection as a whole-K fused launch of up to 64 rows, so does the hook (over the rows of the
  * last step's row map, which must have had that many); the QKV projection leaves its cache write out.  Writes to *bytes (HOST, may
  * be NULL) the weight + activation bytes the launches read once each.  kind + 100 launches nothing
- * and writes 1.0 if a step of `rows` rows runs that kind as a whole-K fused launch of up to 64 rows, 2.0 + row tiles if the
- * split-K plan hands it to the team kernel, else 0.0; kind + 200 writes 1.0 if it runs on the tile kernel, whatever
- * that plan says, else 0.0.  */
+ * and writes 1.0 if a step of `rows` rows runs that kind as a whole-K fused launch of up to 64 rows, 2.0 + row tiles if
+ * on the team kernel, else 0.0; kind + 200 writes 1.0 if it runs on the tile kernel, else 0.0.  */
 int cerberus_bench_gemm(cerberus_ctx *ctx, int32_t kind, int32_t rows, void *stream, double *bytes);
 
 /* Text of the last error raised on this thread (never NULL).                                   */

@@ -1089,18 +1089,19 @@ int cerberus_accept_noalloc(cerberus_ctx* ctx, const int32_t* node_argmax, const
 int cerberus_bench_gemm(cerberus_ctx* ctx, int32_t kind, int32_t rows, void* stream, double* bytes) {
   if (!ctx) return fail(CERBERUS_ERR_ARG, "null context");
   const Dims& D = ctx->D;
+  const bool tile_all = tile_launches(ctx, rows, kTileAll), tile_gu = tile_launches(ctx, rows, ctx->ns_gu ? kTileGateUp : kTileGateUpWide) && D.F % 16 == 0;
+  auto tile = [&](int k) { return k == 2 ? tile_gu : k <= 3 && tile_all; };
   if (kind >= 100 && kind <= 106) {   // query: would a step of this many rows run the kind as a whole-K fused launch?
     const bool f = ctx->use_fused && D.dtype == CERBERUS_BF16 && rows >= 1 && rows <= 64 && ctx->fused_grid > 0 && ctx->act_split == 1 &&
                    ((kind == 100 && ctx->ns_qkv) || (kind == 102 && ctx->ns_gu));
     TeamPlan tp;   // (2 + NT: the team kernel with NT row tiles per workgroup)
     const GemmBatch* g = kind == 100 ? &ctx->p_qkv[0] : kind == 102 ? &ctx->p_gu[0] : kind == 103 ? &ctx->p_down[0] : kind == 104 ? &ctx->p_lm : nullptr;
-    const bool team = g && plan_team(ctx, *g, rows, 1, &tp);
+    const bool team = g && !tile(kind - 100) && plan_team(ctx, *g, rows, 1, &tp);
     if (bytes) *bytes = f ? 1.0 : team ? 2.0 + tp.NT : 0.0;
     return CERBERUS_OK;
   }
-  const bool tile_all = tile_launches(ctx, rows, kTileAll), tile_gu = tile_launches(ctx, rows, ctx->ns_gu ? kTileGateUp : kTileGateUpWide) && D.F % 16 == 0;
   if (kind >= 200 && kind <= 206) {   // query: ... as a launch of the tile kernel?
-    if (bytes) *bytes = kind == 202 ? tile_gu : kind <= 203 && tile_all;
+    if (bytes) *bytes = tile(kind - 200);
     return CERBERUS_OK;
   }
   const bool head_kind = kind == 5 || kind == 6;
@@ -1123,7 +1124,7 @@ int cerberus_bench_gemm(cerberus_ctx* ctx, int32_t kind, int32_t rows, void* str
   } else if (kind == 2 && fused && ctx->ns_gu) {
     for (int l = 0; l < D.n_layers; ++l) TRY(run_fused_gate_up(ctx, l, s));
     total = (double)D.n_layers * ((double)2 * D.F * D.d + (double)rows * D.d * 2) * ctx->elem;
-  } else if (kind == 2 ? tile_gu : kind <= 3 && tile_all) {
+  } else if (tile(kind)) {
     // the tile kernel over `rows` rows, whatever the last step had (sequences and positions, which the QKV epilogue reads, are those
     // of its row map, zero where no step has been); without the cache write
     const GemmProb& P = (kind == 0 ? ctx->p_qkv : kind == 1 ? ctx->p_o : kind == 2 ? ctx->p_gu : ctx->p_down)[0].p[0];

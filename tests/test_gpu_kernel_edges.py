@@ -180,14 +180,17 @@ def test_long_prompts_match_the_oracle(dtype, n_prompt):
 
 @pytest.mark.parametrize("one_token", [(), (0, 2, 3, 5, 6, 7, 9, 10, 12, 13, 15), tuple(range(16)), tuple(range(1, 16)),
                                        tuple(range(15)), (0, 1, 2, 4, 5, 6, 7, 9, 10, 11, 13, 14, 15)])
-def test_down_projection_of_a_large_batch(one_token):
-    """16 sequences of a 192-node tree at d = 1024: the down projection runs on the team kernel (two column blocks, from 10 teams
-    at the bound to 16 with few rows), with all 3072 rows, with 971, 589 and 207 of them and with 16, where every sequence
+@pytest.mark.parametrize("fused", [0, 1])
+def test_down_projection_of_a_large_batch(fused, one_token):
+    """16 sequences of a 192-node tree at d = 1024: the down projection runs on the tile kernel, or with gemm_fused 0 on the team
+    kernel (two column blocks, from 10 teams at the bound to 16 with few rows), with all 3072 rows, with 971, 589 and 207 of them and with 16, where every sequence
     brings one; the consumer sums as many planes as the launch took.  One workgroup per (item, head) of sequences of many lengths in
     attention.  Every row of every sequence against the oracle; the bars are those of the 7B shape, whose sums are longer."""
-    print(f"down projection, one-token sequences {one_token}", flush=True)
+    print(f"down projection, one-token sequences {one_token}, gemm_fused {fused}", flush=True)
     pair = H.Pair("tiny", B.CERBERUS_BF16, "bfs4x192", seed=4, max_batch=16, kv_capacity=512, d_model=1024, n_heads=8, head_dim=128, d_ffn=1000)
-    assert B.cerberus_bench_gemm(pair.engine.ctx, 103, 16 * pair.T) >= 2.0          # the team kernel takes it
+    pair.engine.set_param("gemm_fused", fused)
+    assert B.cerberus_bench_gemm(pair.engine.ctx, 203, 16 * pair.T) == fused         # the tile kernel takes it
+    assert (B.cerberus_bench_gemm(pair.engine.ctx, 103, 16 * pair.T) >= 2.0) == (fused == 0)     # or the team kernel
     assert B.cerberus_bench_gemm(pair.engine.ctx, 103, 768) == 0.0
     taps, st = pair.taps(), pair.engine.new_state()
     osts = []

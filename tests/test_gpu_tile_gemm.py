@@ -138,3 +138,13 @@ def test_benchmark_hook_runs_the_rows_it_is_asked_for(kind, columns, least):
     print(f"kind {kind}: {changed} bytes changed", flush=True)
     assert changed >= 96 * columns * least
     pair.engine.close()
+
+
+def test_hook_names_the_team_kernel_only_where_a_step_runs_it():
+    """gemm_fused 0 keeps the tile kernel out: gate/up of 192 rows is then the team kernel's, as its own plan says."""
+    pair = H.Pair("tiny", B.CERBERUS_BF16, "p63", seed=9, max_batch=3, kv_capacity=256, topk=10)
+    query = lambda kind: B.cerberus_bench_gemm(pair.engine.ctx, kind, 192)
+    assert (query(102), query(202)) == (0.0, 1.0)
+    pair.engine.set_param("gemm_fused", 0)
+    assert query(102) > 2.0 and query(202) == 0.0
+    pair.engine.close()
