@@ -109,16 +109,17 @@ def test_long_prompts_run_several_pieces_per_pass(dtype, attn_mfma, n_prompt, L0
     pair.engine.close()
 
 
-@pytest.mark.parametrize("team", [3, 0])
+@pytest.mark.parametrize("fused,team", [(1, 3), (0, 3), (0, 0)])   # the tile kernel, the team kernel, 64-row blocks
 @pytest.mark.parametrize("n_prompt", [193, 256, 384, 385, 640, 1024, 1152])
-def test_cache_rows_of_a_long_prompt_are_as_close_to_the_oracle_as_piece_by_piece(n_prompt, team):
+def test_cache_rows_of_a_long_prompt_are_as_close_to_the_oracle_as_piece_by_piece(n_prompt, fused, team):
     """One layer of the 7B width (K = 4096): the cache rows are the QKV projection of the embeddings, whose products are exact
     in the hi and lo planes, so an element differs from the rounded oracle where the error of its fp32 sum crosses a
     rounding boundary, in proportion to that error.  In a pass of several pieces there are to be no more of them than where
     every piece runs on its own: 500 to 3269 of 1.6 to 9 million, whose independent draws differ by 2.5 to 6 % (one standard
     deviation); bar 10 %.  Planes that sum over three quarters of K have 17 % more, over all of K 27 %."""
-    print(f"prompt of {n_prompt}, gemm_team {team}", flush=True)
+    print(f"prompt of {n_prompt}, gemm_fused {fused}, gemm_team {team}", flush=True)
     pair = H.Pair("7b", B.CERBERUS_BF16, "root", seed=3, kv_capacity=1152, n_layers=1, d_ffn=256, vocab=1024, n_cerb_heads=1, special_block=-1)
+    pair.engine.set_param("gemm_fused", fused)
     pair.engine.set_param("gemm_team", team)
     tokens = synth.make_token_ids(n_prompt, 1024, seed=8)
     kv = orc.new_kv(pair.cfg, n_prompt)
@@ -137,16 +138,19 @@ def test_cache_rows_of_a_long_prompt_are_as_close_to_the_oracle_as_piece_by_piec
     pair.engine.close()
 
 
-@pytest.mark.parametrize("dtype,n_prompt", [(B.CERBERUS_F32, 700), (B.CERBERUS_BF16, 230), (B.CERBERUS_BF16, 384), (B.CERBERUS_BF16, 700), (B.CERBERUS_BF16, 1153)])
-def test_long_prompts_match_the_oracle(dtype, n_prompt):
+@pytest.mark.parametrize("dtype,n_prompt,fused", [(B.CERBERUS_F32, 700, 1), (B.CERBERUS_BF16, 230, 1), (B.CERBERUS_BF16, 384, 1), (B.CERBERUS_BF16, 700, 1),
+                                                  (B.CERBERUS_BF16, 1153, 1), (B.CERBERUS_BF16, 384, 0), (B.CERBERUS_BF16, 1153, 0)])
+def test_long_prompts_match_the_oracle(dtype, n_prompt, fused):
     """Six layers of width 1024, passes of several pieces against the oracle's causal forward over pieces of 192 tokens, its
     cache rounded to the storage type between them: every cache row, the tapped rows, entropy, the heads' logits, the
-    pending token."""
-    print(f"prompt of {n_prompt}, dtype {dtype}", flush=True)
+    pending token; the layers on the tile kernel (gate/up of this width on the team kernel) and, with gemm_fused 0, on the team
+    kernel and the 64-row blocks, QKV with its sums limited."""
+    print(f"prompt of {n_prompt}, dtype {dtype}, gemm_fused {fused}", flush=True)
     P = B.CERBERUS_MAX_TREE
     tol = H.TOL_F32 if dtype == B.CERBERUS_F32 else H.TOL_BF16
     pair = H.Pair("tiny", dtype, "p63", seed=6, kv_capacity=1280, topk=6, n_layers=6, d_model=1024, n_heads=8, head_dim=128, d_ffn=1000,
                   entropy_threshold=float("inf"))
+    pair.engine.set_param("gemm_fused", fused)
     cfg = pair.cfg
     tokens = synth.make_token_ids(n_prompt, cfg["vocab"], seed=9)
     ost = {"kv": orc.new_kv(cfg, n_prompt)}

@@ -784,14 +784,16 @@ def test_tiny_tuning_knobs_do_not_change_results(params):
     pair.engine.close()
 
 
-@pytest.mark.parametrize("nsub_rows,team", [(4, 3), (2, 1), (2, 0)])
-def test_tiny_maximum_batch_and_tree(nsub_rows, team):
+@pytest.mark.parametrize("fused,nsub_rows,team", [(1, 0, 3), (0, 4, 3), (0, 2, 1), (0, 2, 0)])
+def test_tiny_maximum_batch_and_tree(fused, nsub_rows, team):
     """The largest launch the library takes: 16 sequences, a 192-node tree (three mask words, three
     query blocks and tree chunks), 13 of them running the whole tree and 3 a single row: 2499 packed
-    rows, 40 row blocks in every GEMM (with either instance of the GEMM for several row blocks; gate/up,
-    QKV and the LM head on the team kernel, 23 row blocks of 112 rows, only gate/up, or everything on
-    the same kernel).  Every row of every sequence is compared."""
+    rows.  The layers on the tile kernel (20 row blocks of 128 rows) and the LM head on the team kernel;
+    with gemm_fused 0: gate/up, QKV, down and the LM head on the team kernel, 23 row blocks of 112 rows, only
+    gate/up, or everything on the 64-row blocks, 40 in every GEMM, with either instance of theirs.
+    Every row of every sequence is compared."""
     pair = H.Pair("tiny", BF16, "bfs4x192", seed=0, max_batch=16, kv_capacity=384)
+    pair.engine.set_param("gemm_fused", fused)
     pair.engine.set_param("gemm_nsub_rows", nsub_rows)
     pair.engine.set_param("gemm_team", team)
     cfg = pair.cfg
@@ -819,13 +821,15 @@ def test_tiny_maximum_batch_and_tree(nsub_rows, team):
     pair.engine.close()
 
 
+@pytest.mark.parametrize("fused", [1, 0])
 @pytest.mark.parametrize("flags", [(0, 0, 0), (1, 0, 1), (1, 1, 1), (0, 1, 0)])
-def test_tiny_row_counts_below_the_launch_bound(flags):
+def test_tiny_row_counts_below_the_launch_bound(flags, fused):
     """The launches of a step are planned for batch x tree rows (3 x 192 = 576 here); how many rows there are
-    is decided on the device by the gate flags: 576, 194, 3 or 385.  The GEMM for many rows forms its row
-    blocks and teams from that count, and its consumers sum the planned number of partial planes whatever
-    it is.  Every row of every sequence is compared."""
+    is decided on the device by the gate flags: 576, 194, 3 or 385.  The tile kernel forms its row blocks and k
+    ranges from that count, the team kernel (gemm_fused 0) its row blocks and teams; consumers sum the planes that
+    the launch took, or the planned number.  Every row of every sequence is compared."""
     pair = H.Pair("tiny", BF16, "bfs4x192", seed=0, max_batch=3, kv_capacity=384)
+    pair.engine.set_param("gemm_fused", fused)
     cfg = pair.cfg
     taps = pair.taps()
     st = pair.engine.new_state()
@@ -846,7 +850,7 @@ def test_tiny_row_counts_below_the_launch_bound(flags):
         rep = H.compare_step(cfg, out, st, taps, b, pair.T, BF16, ost, tol=H.TOL_BF16_TINY)
         worst = max(worst, rep.max_logit_err)
         assert not rep.failures, f"flags {flags}, seq {b}: " + "; ".join(rep.failures)
-    say(f"  flags {flags}, {sum(o['T'] for o in outs)} rows of 576: worst logits err {worst:.2e}")
+    say(f"  flags {flags}, gemm_fused {fused}, {sum(o['T'] for o in outs)} rows of 576: worst logits err {worst:.2e}")
     pair.engine.close()
 
 
