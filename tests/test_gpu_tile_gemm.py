@@ -17,25 +17,44 @@ TOL = H.TOL_BF16_TINY
 
 
 def _forward(pair, batch, lens, flags, fused):
-    """One verify step from random caches; every float output and the rows the step wrote."""
+    """One verify step from random caches, every tree accepting along a deepest branch: every float output, the cache rows of all
+    nodes (those of the accepted path moved up, in either run alike), the tokens accepted.  No other cache row may change."""
     pair.engine.set_param("gemm_fused", fused)
-    taps, st = pair.taps(), pair.engine.new_state()
+    taps, st = pair.taps(forced_argmax=True), pair.engine.new_state()
     g = torch.Generator(device="cuda")
     g.manual_seed(7)
     for layer in st.kv:
         layer.normal_(0.0, 1.0, generator=g)
+    start = st.kv.clone()
+    cand = synth.make_candidates(pair.cfg, batch, seed=4)
     st.kv_len.copy_(torch.tensor(lens, dtype=torch.int32))
     st.gate_flag.copy_(torch.tensor(flags, dtype=torch.int32))
     st.root_token.copy_(synth.make_token_ids(batch, pair.cfg["vocab"], seed=4))
-    st.cand.copy_(synth.make_candidates(pair.cfg, batch, seed=4))
+    st.cand.copy_(cand)
+    depths = [0] * pair.T
+    for node in range(1, pair.T):
+        depths[node] = depths[pair.parent[node]] + 1
+    path = [depths.index(max(depths))]                                  # from the root to the first deepest node
+    while path[0]:
+        path.insert(0, pair.parent[path[0]])
+    forced = torch.full((batch, pair.T), -1, dtype=torch.int32)
+    for b in range(batch):
+        for depth, (node, child) in enumerate(zip(path, path[1:])):
+            forced[b, node] = cand[b, depth, pair.rank[child]]
+    taps.forced_node_argmax.copy_(forced.flatten())
     taps.logits.zero_()
     taps.h_last.zero_()
     pair.engine.verify_step(st, batch)
     torch.cuda.synchronize()
     assert int(st.status.abs().sum()) == 0
     rows = [1 if f else pair.T for f in flags]
-    kv = [st.kv[:, :, b, :, n:n + (1 if f else min(pair.T, int(st.accept_len[b])))] for b, (n, f) in enumerate(zip(lens, flags))]
-    return taps.logits.clone(), taps.h_last.clone(), [k.clone() for k in kv], rows
+    accepted = st.accept_len[:batch].tolist()
+    assert accepted == [1 if f else len(path) for f in flags] and len(path) > 2
+    kv = []
+    for b, (n, r) in enumerate(zip(lens, rows)):
+        assert torch.equal(st.kv[:, :, b, :, :n], start[:, :, b, :, :n]) and torch.equal(st.kv[:, :, b, :, n + r:], start[:, :, b, :, n + r:])
+        kv.append(st.kv[:, :, b, :, n:n + r].clone())
+    return taps.logits.clone(), taps.h_last.clone(), kv, rows
 
 
 # rows live / planned: 65 (gate/up alone) ... 1024; few live rows of a large bound; odd row tiles and row blocks of unequal size
@@ -76,6 +95,20 @@ def test_a_wide_qkv_runs_in_rounds():
     for b in range(16):
         mm = H.kv_mismatch(got[2][b].double().cpu().numpy(), want[2][b].double().cpu().numpy(), TOL)
         assert mm is None, (b, mm)
+    pair.engine.close()
+
+
+@pytest.mark.parametrize("nodes", [16, 17, 33, 63, 64])
+def test_a_gate_up_too_wide_for_the_whole_k_kernel(nodes):
+    """FFN of 13824 columns: more slabs than the whole-K kernel of up to 64 rows has room for, so from 17 rows on gate/up runs on the
+    tile kernel, the other projections as in any small launch."""
+    pair = H.Pair("tiny", B.CERBERUS_BF16, f"rand{nodes}s7k6", seed=9, max_batch=1, kv_capacity=256, topk=10, d_ffn=13824)
+    assert pair.T == nodes
+    assert [B.cerberus_bench_gemm(pair.engine.ctx, 200 + kind, nodes) for kind in range(4)] == [0.0, 0.0, float(nodes > 16), 0.0]
+    got, want = _forward(pair, 1, [29], [0], 1), _forward(pair, 1, [29], [0], 0)
+    assert float((got[0] - want[0]).abs().max()) <= TOL.logits and float((got[1] - want[1]).abs().max()) <= TOL.hidden
+    mm = H.kv_mismatch(got[2][0].double().cpu().numpy(), want[2][0].double().cpu().numpy(), TOL)
+    assert mm is None, mm
     pair.engine.close()
 
 
