@@ -207,14 +207,16 @@ int cerberus_set_taps(cerberus_ctx *ctx, const cerberus_taps *taps);
  *                                              fills >= 90 % of them in one round is preferred; 0 = off
  *   "gemm_uneven_split" (0 or 1, default 0)    1: take the split the target gives even if it does not divide K
  *   "gemm_nsub"       (2 or 4, default 2)      16-column slabs per wave (64*nsub columns per workgroup)
- *   "gemm_nsub_rows"  (0, 2 or 4, default 0)   the same for launches of more than 64 rows (several row blocks);
+ *   "gemm_nsub_rows"  (0, 2 or 4, default 0)   the same for split-K launches of more than 64 rows (several row blocks);
  *                                              4 runs one workgroup per CU with the whole register file; 0 picks
  *                                              4 for the down projection and the LM head past 256 rows, else 2
- *   "gemm_team"       (0..3, default 3)        bf16 launches of more than 128 rows run, on the kernel that deals
- *                                              (column block, k) ranges to teams of one workgroup per 128-row
- *                                              block: 1 the gate/up projection, 2 also QKV and 3 also the LM head
- *                                              (these two only past 256 rows) and the down projection (past 768);
- *                                              0: everything on the 64-row blocks of the split-K kernel
+ *   "gemm_team"       (0..3, default 3)        bf16 launches of more than 128 rows that "gemm_fused" leaves to split-K
+ *                                              run, on the kernel that deals (column block, k) ranges to teams of one
+ *                                              workgroup per 128-row block: 1 the gate/up projection, 2 also QKV and 3
+ *                                              also the LM head (these two only past 256 rows) and the down
+ *                                              projection (past 768); 0: everything on the 64-row blocks of the
+ *                                              split-K kernel.  With "gemm_fused" 1 that leaves the LM head, and gate/up
+ *                                              where 16 does not divide d_ffn
  *   "act_split"       (0 or 1, default 1)      1: GEMM inputs as hi + lo bf16 planes; 0: hi plane only
  *                                              (bf16-rounded GEMM inputs: faster, less accurate)
  *   "attn_chunk"      (128 or 256, default 128) committed cache rows per round of an attention workgroup
@@ -222,10 +224,13 @@ int cerberus_set_taps(cerberus_ctx *ctx, const cerberus_taps *taps);
  *                                              longer the sequences, the more rounds a workgroup walks; a target
                                               above the default is cut back to the workspace's room for partials
  *   "attn_mfma"       (0 or 1, default 1)      0: plain attention kernel instead of the MFMA one
- *   "gemm_fused"      (0 or 1, default 1)      1: bf16 launches of up to 64 rows run QKV + RoPE + KV write and
- *                                              gate/up + SwiGLU as one whole-K launch each (where the shapes
- *                                              allow: at most 6 slabs of 16 columns per compute unit); 0: split-K
- *                                              GEMM plus a separate RoPE / SwiGLU launch, as for larger launches */
+ *   "gemm_fused"      (0 or 1, default 1)      1: bf16 launches (act_split 1) run QKV + RoPE + KV write and gate/up +
+ *                                              SwiGLU as one whole-K launch each: up to 64 rows where the shapes allow
+ *                                              (at most 6 slabs of 16 columns per compute unit); on the tile kernel
+ *                                              gate/up above 64 rows (above 16 where it has more slabs than that) and
+ *                                              QKV, and with it O and down in ranges of K, above 128 rows; 0: split-K
+ *                                              GEMMs plus a separate RoPE / SwiGLU launch at every row count, on the
+ *                                              kernels that gemm_team and gemm_nsub_rows choose                    */
 int cerberus_set_param(cerberus_ctx *ctx, const char *name, int32_t value);
 
 /* Benchmark hook: enqueues back to back, for every layer (or head stage), the GEMM launches of

@@ -110,9 +110,10 @@ namespace {
 // the error of a plane of the QKV projection grows with the length of its sum.  A pass of 192 rows cuts K in three; over 1024
 // rows the same GEMM has work enough without, and with sums over three quarters of K the cache rows and logits of a
 // 1024-token prompt were 4 and 11 % further from float64 (2-norm) than piece by piece, the heads' logits of a 230-token one twice as far.
-// So a pass of several pieces sums its QKV planes over no longer ranges than a pass of one piece: 1.07e-3 against 1.08e-3 on
-// the cache rows of 1024 tokens, at a cost of 1.1 of 30.8 ms for the larger planes.  The length of the other projections' sums
-// made no difference.
+// So with split-K launches (gemm_fused 0) a pass of several pieces sums its QKV planes over no longer ranges than a pass of one
+// piece: 1.07e-3 against 1.08e-3 on the cache rows of 1024 tokens, at a cost of 1.1 of 30.8 ms for the larger planes.  The tile
+// kernel sums QKV in pieces of 256 columns at any row count.  The length of the other projections' sums made no difference
+// to cache rows and logits.
 constexpr int kPromptPiece = CERBERUS_MAX_TREE, kPromptPieces = 6;
 
 constexpr int kFusedMaxGrid = 512, kFusedMaxNs = 6;
@@ -523,7 +524,8 @@ int piece_split(const cerberus_ctx* c, const GemmBatch& plan) {
   return g.p[0].S;
 }
 
-// Above 128 rows the problems the planner marked (wide weights: gate/up, QKV, the LM head, in the order of what
+// (Launches that the tile kernel does not take: the LM head; of the layers, gate/up where 16 does not divide the FFN width, and all
+// with gemm_fused 0.)  Above 128 rows the problems the planner marked (wide weights: gate/up, QKV, the LM head, in the order of what
 // they gain; the knob says how far down that list to go) run on the team kernel, which streams the weights once
 // per team of row blocks; its partial planes are the split of the launch.  QKV and the LM head change over
 // only past 256 rows: with two row blocks their extra planes cost what the kernel gains.  The down projection has
@@ -705,7 +707,7 @@ int forward_rows(cerberus_ctx* c, const cerberus_state* st, int rows_max, const 
   const bool fused = c->use_fused && D.dtype == CERBERUS_BF16 && rows_max <= 64 && c->fused_grid > 0 && c->act_split == 1;
   const bool fq = fused && c->ns_qkv > 0, fg = fused && c->ns_gu > 0;
   const bool tq = tile_launches(c, rows_max, kTileAll), tg = tile_launches(c, rows_max, c->ns_gu ? kTileGateUp : kTileGateUpWide) && D.F % 16 == 0;
-  // QKV of a prompt pass of several pieces (see kPromptPieces)
+  // split-K QKV of a prompt pass of several pieces (see kPromptPieces)
   const int qkv_split = sh.piece && rows_max > kPromptPiece ? piece_split(c, c->p_qkv[0]) : 1;
   for (int l = 0; l < D.n_layers; ++l) {
     HIP_TRY(launch_add_gain(D, rm, c->x, prev ? prev->out : nullptr, prev ? prev->S : 0, prev ? prev->S_dev : nullptr,

@@ -1,5 +1,6 @@
-// GEMM for launches of more than 128 rows whose weights are wide (the gate/up projection): out[p] += A W^T, bf16
-// hi + lo activation planes, pre-tiled bf16 weights, fp32 partial planes for the consumer to sum.
+// GEMM for launches of more than 128 rows whose weights are wide: out[p] += A W^T, bf16 hi + lo activation planes, pre-tiled
+// bf16 weights, fp32 partial planes for the consumer to sum.  It runs the LM head past 256 rows, and gate/up, QKV and down where the
+// tile kernel does not take them.
 //
 // One workgroup of 8 waves per CU.  The rows are cut into RB row blocks of at most 128 rows; a wave owns all
 // 16 * NT rows of its workgroup's row block and 64 columns (NT x 4 accumulators), the 8 waves sit side by side: a
