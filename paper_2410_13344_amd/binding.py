@@ -139,7 +139,7 @@ def _ptr_array(tensors):
 
 def make_weights(W: dict):
     """W: the dict of device tensors produced by synth.make_weights.  Returns (struct, keepalive)."""
-    keep = [W["embed"], W["final_norm"], W["lm_head"]]   # a context reads `embed` (fp32 mode: every matrix) where it lies
+    keep = []
 
     def arr(ts):
         p, a = _ptr_array(ts)
