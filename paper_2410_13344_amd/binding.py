@@ -138,7 +138,9 @@ def _ptr_array(tensors):
 
 
 def make_weights(W: dict):
-    """W: the dict of device tensors produced by synth.make_weights.  Returns (struct, keepalive)."""
+    """W: the dict of device tensors produced by synth.make_weights.  Returns (struct, keepalive).  The keepalive holds the
+    matrices of the layers and the heads until cerberus_init is done with them; `embed` (fp32 mode: `lm_head` too), which a context
+    reads at the caller's address on every step, is the caller's to keep alive, as the header says."""
     keep = []
 
     def arr(ts):
@@ -268,7 +270,8 @@ class DeviceTaps:
 
 
 class Engine:
-    """A context plus the buffers that must outlive it."""
+    """A context plus the buffers that must outlive it, but for W["embed"] (fp32 mode: and W["lm_head"]): keep W for as long as
+    the engine runs.  An engine whose dict is gone reads whatever the allocator puts there next."""
 
     def __init__(self, cfg: dict, W: dict, parent, rank, dtype: int, max_batch: int, kv_capacity: int):
         if not torch.cuda.is_available():
