@@ -637,7 +637,8 @@ int run_fused_gate_up(const cerberus_ctx* c, int l, hipStream_t s) {
 // Where the whole-K kernel of up to 64 rows has no room for gate/up's slabs (13B), from 17 rows on (13B step, split-K with its
 // SwiGLU launch / tile kernel: 64 rows 10264 / 9953 us, 20 rows 7637 / 7539, 4 rows 6705 / 6818).
 // The others start at 129 rows: at 121 rows QKV, O and down take 50 + 21 + 38 us a layer on the tile kernel, 39 + 8 (rotation) + 18 +
-// 36 before; at 129 live rows 57 + 23 + 41 against 50 + 7 + 78 for the two.
+// 36 before; at 129 live rows 57 + 23 + 41 against 50 + 7 + 78 for the two.  Both lines hold at 13B: steps of 65 to 128 rows take
+// 0.93-0.97 of the time without the tile kernel, 129 to 192 rows 0.86-0.89 (7B 0.95-0.97 and 0.92-0.95).
 constexpr int kTileGateUp = 64, kTileGateUpWide = 16, kTileAll = 128;
 bool tile_launches(const cerberus_ctx* c, int rows_max, int above) {
   return c->use_fused && c->cfg.dtype == CERBERUS_BF16 && c->act_split == 1 && c->fused_grid > 0 && rows_max > above && rows_max <= (c->fused_grid - 2) * 128;

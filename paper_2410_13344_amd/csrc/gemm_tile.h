@@ -1,5 +1,6 @@
 // Whole-K GEMMs with fused epilogues for launches of more than 64 rows (bf16 mode): the QKV projection with RoPE and the KV
-// write, and the gate/up projection with SwiGLU.
+// write, and the gate/up projection with SwiGLU.  The O and down projections, with few columns, run on the same tiles over ranges of
+// K and leave fp32 planes.
 //
 // A workgroup of 8 waves per compute unit owns a row block (at most 128 rows) and a few 16-column slabs over the full K, so
 // there are no partial planes: the epilogue works on finished sums and no consumer kernel follows.  Row blocks and column
@@ -12,15 +13,16 @@
 // k-step are read from LDS while this one is multiplied, across the barrier between stages too (a stage has landed for
 // everyone one barrier before its turn).  What that is worth, gate/up of the 7B shape (K = 4096, N = 22016), bare kernel: 323
 // rows 149 us with the reads in front of the products, 116 with them a k-step ahead; 121 rows 71 and 57; 1024 rows 330 and
-// 306.  A stage is 40 pieces of 1 KB at most; small tiles take two k-steps per stage (121 rows 57 us, with one 71).  Bounds: up
-// to about 256 rows what the L2s and HBM deliver into a compute unit (A and the slabs come in at 13-15 TB/s over the chip, 53
-// us of the 57 at 121 rows); above that the matrix cores at the clock the load leaves them (1024 rows without any loads:
-// 250-265 us).
+// 306.  A stage is 40 pieces of 1 KB at most; small tiles take two k-steps per stage (121 rows 57 us, with one 71).  Bounds: at
+// 121 rows what the L2s and HBM deliver into a compute unit (A and the slabs come in at 13-15 TB/s over the chip, 53 us of the
+// 57); at 1024 rows the matrix cores at the clock the load leaves them (250-265 us without any loads).  In between neither alone:
+// at 323 rows gate/up brings in 1.03 GB in 114-116 us (9 TB/s) with the matrix cores busy 42 % of the time, QKV 0.78 GB in 82 us
+// with 33 %; loads and products add up more than they overlap.
 //
 // The matrix cores round a running sum with every product, so the error of a sum grows with its length, and a
 // cached element whose sum is off by little moves by a whole step of bf16 now and then.  So every 8 k-steps the sums move
 // over to a second set of accumulators.  A wave's tile of 3 or 4 x 3 has registers for a second set only where its slab fragments
-// are refilled in place and the addresses of its loads are scalar (kWide): gate/up, and O and down where A lies in fragments,
+// are refilled in place and the addresses of its loads are scalar (kWide): gate/up, and down where its input lies in fragments,
 // whose sums move over every 32 k-steps there.  The others have no such tiles: QKV takes fewer pairs per round, row-major A more
 // k ranges.  (Without a second set sums of 3670 to 6912 columns of down were off by 2.9e-7 to 5.3e-7 of the result where all
 // products are positive, the others by 1e-7.)
